@@ -190,9 +190,9 @@ typedef struct {
     double absorbed_thin;  /* part of `absorbed` deposited by the optically thin fill
                               (section 2.6); the rays alone conserve photons:
                               emitted = (absorbed - absorbed_thin) + escaped */
-    uint64_t deposits;     /* fixed-point deposits issued as atomics, one per cell and merge
-                              window after crossings of the same cell are summed on chip (each
-                              covers the cell's bins in one memory request) */
+    uint64_t deposits;     /* 64-byte lines of the fixed-point field added to, each the eight
+                              cells of a 2x2x2 tile in one bin and one memory request, after
+                              the crossings of a merge window are summed on chip */
     uint64_t kernel_crossings; /* batched: crossings of the persistent trace kernel alone */
     uint64_t kernel_deposits;  /* batched: deposits of the persistent trace kernel alone */
 } arc_ledger;
@@ -239,12 +239,12 @@ arc_status arc_get_field(arc_ctx* ctx, int64_t* dst, int64_t count, void* stream
 
 /* Measurement only (no paper counterpart): the device's rate of the two random memory
  * requests a crossing makes, on the buffers of the last arc_trace (2 to 4 bins, else
- * ARC_E_ARG), for holding the trace kernel against. `items` random cells among the first
+ * ARC_E_ARG), for holding the trace kernel against. `items` random places among the first
  * `cells` of the blocked layout (0 = all of them; a counter-based hash of the index and
- * `seed`) each take (1) one deposit: an int64 atomic add to every bin of the cell, issued by
- * adjacent lanes of one instruction as the tracer issues them, and (2) one 16-byte opacity
- * gather. Best of three timings of each, per second. Overwrites the fixed-point field
- * (arc_get_field then fails until the next trace). Blocks. */
+ * `seed`) each take (1) one deposit: int64 atomic adds to the eight words of a 64-byte field
+ * line, issued by adjacent lanes of one instruction as the tracer issues them, and (2) one
+ * 16-byte opacity gather of a cell. Best of three timings of each, per second. Overwrites the
+ * fixed-point field (arc_get_field then fails until the next trace). Blocks. */
 arc_status arc_probe_requests(arc_ctx* ctx, int64_t items, int64_t cells, uint64_t seed, void* stream,
                               double* deposits_per_s, double* gathers_per_s);
 

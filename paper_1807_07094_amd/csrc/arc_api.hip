@@ -24,12 +24,11 @@ struct arc_ctx {
     std::string err;
     // grid-sized buffers
     size_t ncell_cap = 0;
-    int nbp_cap = 0;
     void* kappa = nullptr;             // float or float4 per cell
     size_t kappa_bytes = 0;
-    unsigned long long* J = nullptr;   // [cell][nbp]
+    unsigned long long* J = nullptr;   // [tile][bin][8 cells]
     size_t J_bytes = 0;
-    unsigned long long* M = nullptr;   // conserving correction: moved photons, [cell][2][nbp]
+    unsigned long long* M = nullptr;   // conserving correction: moved photons, [tile][2][bin][8]
     size_t M_bytes = 0;
     // source table
     SourceRec* src = nullptr;
@@ -60,7 +59,7 @@ struct arc_ctx {
     hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     bool timed_kernel = false;  // ev[4], ev[5] bracket the dominant trace kernel
     // last trace
-    int last_nb = 0, last_nbp = 0, last_nx = 0, last_ny = 0, last_nbx8 = 0, last_nby8 = 0;
+    int last_nb = 0, last_nx = 0, last_ny = 0, last_nbx8 = 0, last_nby8 = 0;
     size_t last_ncell = 0;
     bool last_moved = false;  // the last trace filled M
     bool have_field = false;
@@ -300,7 +299,7 @@ namespace {
 // Everything one trace launches with. Zero-filled before use so that its bytes (padding
 // included) can serve as the key of the recorded graphs.
 struct TracePlan {
-    int nb, nbp, lmax;
+    int nb, lmax;
     size_t ncell;
     int nbx8, nby8, nbz8;
     double uj[kMaxBins];
@@ -374,13 +373,11 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     hipStream_t st = (hipStream_t)p->stream;
     HIP_TRY(c, hipSetDevice(c->device));
     const int nb = b->nbins;
-    const int nbp = nb == 1 ? 1 : (nb == 2 ? 2 : 4);
     const size_t ncell = (size_t)g->nx * g->ny * g->nz;
     const int nbx8 = (g->nx + 7) / 8, nby8 = (g->ny + 7) / 8, nbz8 = (g->nz + 7) / 8;
     const size_t nblocked = (size_t)nbx8 * nby8 * nbz8 * 512;  // cells of the blocked layout
     if (nblocked > 2147483648ull) return fail(c, ARC_E_UNSUPPORTED, "blocked grid exceeds 2^31 cells");
     P.nb = nb;
-    P.nbp = nbp;
     P.lmax = lmax;
     P.ncell = ncell;
     P.nbx8 = nbx8;
@@ -423,9 +420,9 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     {
         const size_t kb = nblocked * (nb == 1 ? sizeof(float) : sizeof(float4));
         HIP_TRY(c, grow(&c->kappa, &c->kappa_bytes, kb));
-        HIP_TRY(c, grow(&c->J, &c->J_bytes, nblocked * nbp * sizeof(unsigned long long)));
+        HIP_TRY(c, grow(&c->J, &c->J_bytes, nblocked * nb * sizeof(unsigned long long)));
         if (p->correction == ARC_CORR_CONSERVING)
-            HIP_TRY(c, grow(&c->M, &c->M_bytes, nblocked * 2 * nbp * sizeof(unsigned long long)));
+            HIP_TRY(c, grow(&c->M, &c->M_bytes, nblocked * 2 * nb * sizeof(unsigned long long)));
         if (s->n > c->src_cap) {
             void* old[] = {c->src, c->src_pos, c->src_ndot, c->src_order, c->src_rthin, c->r_out};
             for (void* q : old)
@@ -466,7 +463,6 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     oa.kappa4 = nb == 1 ? nullptr : (float4*)c->kappa;
     oa.J = c->J;
     oa.M = p->correction == ARC_CORR_CONSERVING ? c->M : nullptr;
-    oa.nbp = nbp;
     oa.errflag = c->errflag;
 
     TraceArgs& A = P.A;
@@ -484,7 +480,6 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     A.kappa1 = oa.kappa1;
     A.kappa4 = oa.kappa4;
     A.J = c->J;
-    A.nbp = nbp;
     A.src = c->src;
     A.dirs = c->dirs;
     for (int l = 0; l < kMaxLevels; ++l) A.dir_off[l] = l < c->dirs_levels ? c->dir_off[l] : 0;
@@ -502,7 +497,6 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
 
     FinalizeArgs& fa = P.fa;
     fa.nb = nb;
-    fa.nbp = nbp;
     fa.nx = g->nx;
     fa.ny = g->ny;
     fa.nz = g->nz;
@@ -530,7 +524,6 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     if (thin) {
         ThinFillArgs& tf = P.tf;
         tf.nb = nb;
-        tf.nbp = nbp;
         tf.nsrc = s->r_thin && max_r > 0.0 ? s->n : 0;
         // blocks per source: about 8192 cells of the largest bounding box each, a power of two
         const double box = std::pow(2.0 * max_r + 2.0, 3.0);
@@ -856,7 +849,6 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
     }
 
     c->last_nb = P.nb;
-    c->last_nbp = P.nbp;
     c->last_ncell = P.ncell;
     c->last_nx = P.A.nx;
     c->last_ny = P.A.ny;
@@ -1002,7 +994,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
             best = std::min(best, led.ms_trace);
         }
         HIP_TRY(c, launch_zero_u64(c->sums, 2, st));
-        const size_t words = (size_t)P.nbx8 * P.nby8 * P.nbz8 * 512 * P.nbp;
+        const size_t words = (size_t)P.nbx8 * P.nby8 * P.nbz8 * 512 * P.nb;
         HIP_TRY(c, launch_field_checksum(c->J, words, c->sums, st));
         if (P.A.M) HIP_TRY(c, launch_field_checksum(P.A.M, 2 * words, c->sums, st));
         unsigned long long h[2];
@@ -1103,8 +1095,8 @@ arc_status arc_get_field(arc_ctx* c, int64_t* dst, int64_t count, void* stream)
         return fail(c, ARC_E_ARG, "dst too small (needs %lld entries)", (long long)(parts * c->last_ncell * c->last_nb));
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    HIP_TRY(c, launch_get_field(c->J, c->last_moved ? c->M : nullptr, c->last_nb, c->last_nbp, c->last_nx,
-                                c->last_ny, c->last_nbx8, c->last_nby8, (uint32_t)c->last_ncell, (long long*)dst, st));
+    HIP_TRY(c, launch_get_field(c->J, c->last_moved ? c->M : nullptr, c->last_nb, c->last_nx, c->last_ny,
+                                c->last_nbx8, c->last_nby8, (uint32_t)c->last_ncell, (long long*)dst, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     return ARC_OK;
 }
@@ -1121,11 +1113,13 @@ arc_status arc_probe_requests(arc_ctx* c, int64_t items, int64_t cells, uint64_t
                               (uint64_t)((c->last_ncell / ((size_t)c->last_nx * c->last_ny) + 7) / 8);
     if (cells < 0) return fail(c, ARC_E_ARG, "cells must be >= 0");
     const uint64_t ncell = cells > 0 ? std::min<uint64_t>((uint64_t)cells, nblocked) : nblocked;
+    // whole tiles of the field: eight cells, a line per bin
+    const uint64_t nline = std::max<uint64_t>(1, ncell / 8) * (uint64_t)c->last_nb;
     float ms = 0.0f;
     double best_d = 0.0, best_g = 0.0;
     for (int rep = 0; rep < 3; ++rep) {
         HIP_TRY(c, hipEventRecord(c->ev[0], st));
-        HIP_TRY(c, launch_probe_deposits(c->J, c->last_nbp, c->last_nb, ncell, (uint64_t)items, seed + rep, c->cus, st));
+        HIP_TRY(c, launch_probe_deposits(c->J, nline, (uint64_t)items, seed + rep, c->cus, st));
         HIP_TRY(c, hipEventRecord(c->ev[1], st));
         HIP_TRY(c, launch_probe_gathers((const float4*)c->kappa, ncell, (uint64_t)items, seed + rep, (float*)c->acc,
                                         c->cus, st));

@@ -39,17 +39,24 @@ __host__ __device__ __forceinline__ uint32_t blocked_index(int x, int y, int z, 
     return (b << 9) | m;
 }
 
+// Place of a cell's bin in a fixed-point field of `lines` 64-byte lines per 2x2x2 tile, line b of
+// the tile holding bin b of its eight cells (the low three bits of the blocked index).
+__host__ __device__ __forceinline__ size_t field_word(uint32_t cell, int lines, int b)
+{
+    return ((size_t)(cell >> 3) * (size_t)lines + (size_t)b) * 8u + (cell & 7u);
+}
+
 // A crossing's deposit: the cell (blocked index) and the amount of every bin in field units,
 // rounded to the field's integers when the wave deposits it.
 template <int NB>
 struct Dep {
-    uint32_t cell;        // kNoCell: nothing to deposit
+    uint32_t cell;        // always a valid index, also where there is nothing to deposit
     float v[NB];
 };
 
 enum Counter : int {
     kCrossings = 0, kRays, kSplits, kTerminated, kEscapedRays, kSpills, kTreeCount, kQueueOverflow,
-    kDeposits,  // (cell, bins) deposit items issued as atomics after the wave-level merge
+    kDeposits,  // 64-byte field lines added to after the wave-level merge
     kCrossingsPre, kDepositsPre,  // crossings and deposits before the persistent launch
     kNumCounters
 };
@@ -89,8 +96,7 @@ struct TraceArgs {
     float tau_term;            // +inf = never terminate
     const float* kappa1;       // nb == 1: optical depth per cell length, [cell] (blocked order)
     const float4* kappa4;      // nb > 1: [cell] (bins in x, y, z, w) (blocked order)
-    unsigned long long* J;     // fixed-point field [cell][nbp] (blocked order)
-    int nbp;                   // padded bins per cell in J (1, 2 or 4)
+    unsigned long long* J;     // fixed-point field [tile][nb][8] (blocked order, field_word)
     const SourceRec* src;
     const float4* dirs;        // HEALPix centres of every level, concatenated
     long long dir_off[kMaxLevels];
@@ -100,7 +106,7 @@ struct TraceArgs {
     long long tree_cap;
     int corr;                  // geometric correction: 0 none, 1 f_c, 2 f_c + secondary, 3 f_c^2
     // corr == 2: photons moved into a cell by the secondary correction (eq:correction2), in two
-    // limbs per bin, [cell][limb][nbp]: limb 0 in units of 2^20 u_J,b, limb 1 in units of
+    // limbs per bin, [tile][limb][nb][8]: limb 0 in units of 2^20 u_J,b, limb 1 in units of
     // 2^-12 u_J,b
     unsigned long long* M;
     // optically thin approximation (section 2.6): the bin of lowest photon energy, and per
@@ -111,34 +117,54 @@ struct TraceArgs {
 
 constexpr float kTauThin = 0.1f;  // optical depth that bounds the optically thin sphere
 
+// The blocked cell index is the sum of one term per axis. Every workgroup that traces keeps the
+// terms of the three axes in LDS (nx + ny + nz words, axis after axis), and a ray carries the
+// addresses of its cell's three entries: a step moves one address, and the index costs three LDS
+// reads and an add (computing a term takes ten VALU instructions, which bound the trace).
+typedef const volatile kLds char* TermAddr;
+
+struct Terms {
+    TermAddr base[3];      // entry of coordinate 0 along each axis
+    __device__ __forceinline__ bool inside(int i, TermAddr p, int n) const
+    {
+        return (uint32_t)(p - base[i]) < 4u * (uint32_t)n;
+    }
+};
+
+__device__ __forceinline__ uint32_t term_at(TermAddr p) { return *(const volatile kLds uint32_t*)p; }
+
 // Per-lane ray state. Along axis i the ray meets its next cell boundary at
 // t_i = a_i / e_i, where e_i = |d_i| and a_i is the (exact, lattice-valued) distance of
-// that boundary from the source; crossing the boundary adds 1 to a_i. The blocked cell
-// index is the sum of one term per axis, refreshed only for the axes that move.
+// that boundary from the source; crossing the boundary adds 1 to a_i.
 template <int NB>
 struct Ray {
     float e[3];           // |d_i|
     float ie[3];          // 1 / |d_i| (hardware reciprocal, within 1 ulp), +inf if d_i == 0
     float a[3];           // next-boundary distance along each axis (exact)
-    int c[3];             // current cell
-    int step[3];          // +1, -1 or 0
-    uint32_t ix[3];       // per-axis terms of the blocked cell index
+    TermAddr o[3];        // index term of the current cell along each axis
+    int step[3];          // bytes to the next cell's term: +4, -4 or 0
     float thi, tlo;       // current path length (double-float)
     float tend;           // split radius or +inf
+    float tlim;           // just below the split radius and the way out of the grid
     float tau[NB], taulo[NB];
     float w[NB];          // scale_b * 4^-level
     uint32_t src, lp;
 };
 
-struct LaneStats {
-    uint32_t crossings, rays, splits, terminated, escaped;
-    double esc[kMaxBins];
+// Counts of a wave (wave-uniform, from ballots) and, per lane, crossings and photons lost.
+struct WaveStats {
+    unsigned long long rays, splits, terminated, escaped;
+    uint32_t crossings;    // per lane
+    double esc[kMaxBins];  // per lane
     __device__ void clear()
     {
-        crossings = rays = splits = terminated = escaped = 0;
+        rays = splits = terminated = escaped = 0;
+        crossings = 0;
         for (int b = 0; b < kMaxBins; ++b) esc[b] = 0.0;
     }
 };
+
+__device__ __forceinline__ unsigned long long count_lanes(bool p) { return (unsigned long long)__popcll(__builtin_amdgcn_ballot_w64(p)); }
 
 // ---------------------------------------------------------------------------------
 // Exact arithmetic helpers. All operands are non-negative FP32 values.
@@ -193,6 +219,19 @@ __device__ __forceinline__ uint32_t axis_term(const TraceArgs& A, int i, int v)
     return blk9 * (((uint32_t)A.nbx8 * (uint32_t)A.nby8) & 0x1FFFFu) + m;
 }
 
+// Fills the workgroup's table of index terms (nx + ny + nz words at `table`); all threads of the
+// workgroup call it, and a barrier follows before the first use.
+__device__ __forceinline__ Terms make_terms(const TraceArgs& A, uint32_t* table)
+{
+    for (int k = threadIdx.x; k < A.nx + A.ny + A.nz; k += blockDim.x)
+        table[k] = k < A.nx ? axis_term(A, 0, k) : (k < A.nx + A.ny ? axis_term(A, 1, k - A.nx) : axis_term(A, 2, k - A.nx - A.ny));
+    Terms t;
+    t.base[0] = (TermAddr)table;
+    t.base[1] = t.base[0] + 4 * A.nx;
+    t.base[2] = t.base[1] + 4 * A.ny;
+    return t;
+}
+
 // Non-negative float to the nearest int64 (v < 2^63): two exact 32-bit halves.
 __device__ __forceinline__ long long round_to_i64(float v)
 {
@@ -223,9 +262,11 @@ __device__ __forceinline__ void record_tree(const TraceArgs& A, uint32_t src, ui
 // optically thin approximation (THIN, section 2.6) a ray starts no closer than its source's
 // thin radius; a ray whose split radius does not lie beyond that start splits at once (it is
 // returned active with thi >= tend and crosses nothing).
-// Returns false (and books the escape) when the start point lies outside the grid.
+// Returns false (and books the escape's photons; the caller counts it) when the start point lies
+// outside the grid.
 template <int NB, bool THIN, class Rec>
-__device__ __forceinline__ bool ray_init(const TraceArgs& A, const Rec& r, Ray<NB>& ray, LaneStats& st)
+__device__ __forceinline__ bool ray_init(const TraceArgs& A, const Terms& terms, const Rec& r, Ray<NB>& ray,
+                                         WaveStats& st)
 {
     ray.src = r.src;
     ray.lp = r.lp;
@@ -247,25 +288,28 @@ __device__ __forceinline__ bool ray_init(const TraceArgs& A, const Rec& r, Ray<N
         ray.taulo[b] = r.taulo[b];
         ray.w[b] = s.scale[b] * lw;
     }
-    st.rays++;
     if constexpr (THIN) {
         if (!(t0 < ray.tend)) return true;  // splits at once
     }
     bool inside = true;
+    float texit = ray.tend;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const int c = start_index(xs[i], t0, d[i]);
-        ray.c[i] = c;
+        const int n = i == 0 ? A.nx : (i == 1 ? A.ny : A.nz);
+        ray.o[i] = terms.base[i] + 4 * c;
         ray.e[i] = fabsf(d[i]);
         ray.ie[i] = d[i] != 0.0f ? __builtin_amdgcn_rcpf(ray.e[i]) : INFINITY;
-        ray.step[i] = d[i] > 0.0f ? 1 : (d[i] < 0.0f ? -1 : 0);
+        ray.step[i] = d[i] > 0.0f ? 4 : (d[i] < 0.0f ? -4 : 0);
         // d_i = 0: the distance to the upper face (no boundary is met along this axis; the
         // geometric correction reads the position from it)
         ray.a[i] = d[i] < 0.0f ? xs[i] - (float)c : (float)(c + 1) - xs[i];
-        const int n = i == 0 ? A.nx : (i == 1 ? A.ny : A.nz);
+        // the wall of the grid along this axis is met at the float product the traversal will form
+        const float wall = d[i] < 0.0f ? xs[i] : (float)n - xs[i];
+        texit = fminf(texit, d[i] != 0.0f ? wall * ray.ie[i] : INFINITY);
         inside = inside && c >= 0 && c < n;
-        ray.ix[i] = inside ? axis_term(A, i, c) : 0u;
     }
+    ray.tlim = texit * 0.999998f;
     if (!inside) {
         float ts = 0.0f;
 #pragma unroll
@@ -277,7 +321,6 @@ __device__ __forceinline__ bool ray_init(const TraceArgs& A, const Rec& r, Ray<N
         // a ray that starts outside the grid while still thin bounds the thin radius by its start
         if constexpr (THIN)
             if (ts < kTauThin) atomicMin(A.r_out + ray.src, __float_as_uint(t0));
-        st.escaped++;
     }
     return inside;
 }
@@ -296,12 +339,10 @@ __device__ __forceinline__ void kappa_at(const TraceArgs& A, uint32_t cell, floa
     }
 }
 
-// A piece of a ray inside one cell: blocked cell index, length, and what happens at its
-// end (kContinue: next cell; kSplit: the split radius; kEscape: the ray leaves the grid).
+// A piece of a ray inside one cell: blocked cell index and length.
 struct Seg {
     uint32_t cell;
     float ds;
-    int event;
     uint32_t nb;  // geometric correction: neighbour that receives the moved share (kNoCell: none)
     float fc;     // geometric correction: share the cell keeps (1: uncorrected)
     float t1;     // path length at the segment's end (high part)
@@ -321,7 +362,8 @@ constexpr double kFaceTie = 1e-9;
 // FP64 from the exact boundary numerators; faces within kFaceTie count as tied, and ties go
 // to the lower axis, then the lower face.
 template <int NB>
-__device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB>& ray, float nhi, float nlo, Seg& sg)
+__device__ __forceinline__ void geom_correction(const TraceArgs& A, const Terms& terms, const Ray<NB>& ray, float nhi,
+                                                float nlo, Seg& sg)
 {
     sg.nb = kNoCell;
     sg.fc = 1.0f;
@@ -354,132 +396,130 @@ __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB
         // the neighbour's per-axis term replaces the cell's along `axis` (static indices only:
         // a runtime index into the ray's arrays would move them to scratch memory)
         bool inside = true;
-        uint32_t nb = sg.cell;
+        TermAddr oc = ray.o[0], on = ray.o[0];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             if (i == axis) {
-                const int ca = ray.c[i] + side;
-                const int na = i == 0 ? A.nx : (i == 1 ? A.ny : A.nz);
-                inside = ca >= 0 && ca < na;
-                if (inside) nb = nb - ray.ix[i] + axis_term(A, i, ca);
+                oc = ray.o[i];
+                on = oc + 4 * side;
+                inside = terms.inside(i, on, i == 0 ? A.nx : (i == 1 ? A.ny : A.nz));
             }
         }
         if (!inside) return;  // no neighbour inside: the cell keeps everything
-        sg.nb = nb;
+        sg.nb = sg.cell - term_at(oc) + term_at(on);
     }
     sg.fc = fc;
 }
 
 // Geometry of the next segment (section 2.4: the step to the next x, y or z boundary, or
-// to the split radius), advancing the ray's position and cell.
+// to the split radius), advancing the ray's position and cell. Returns what happens at its end
+// (kContinue: next cell; kSplit: the split radius; kEscape: the ray leaves the grid).
 //
 // Geometric decisions are exact: boundary times are compared through the reciprocal
 // products a_i / e_i, whose relative error is below 2e-7, and any comparison closer than
-// 1e-6 is settled exactly with cmp_prod (a_i e_j vs a_j e_i). The winning axis is picked
-// with conditional moves (a runtime index into the per-ray arrays would move them to
-// scratch memory).
+// 1e-6 is settled exactly with cmp_prod (a_i e_j vs a_j e_i). The middle of the three times
+// says whether any comparison is that close. The split radius and the grid's walls are looked
+// at only within 2e-6 of the nearer of them (tlim): a boundary met before that is neither, so
+// an ordinary step is about thirty instructions (a bundle's lanes reach their ends together).
 template <int NB, int PREC, bool CORR = false>
-__device__ __forceinline__ Seg geom_next(const TraceArgs& A, Ray<NB>& ray)
+__device__ __forceinline__ int geom_next(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, Seg& sg)
 {
     constexpr float kNear = 1.000001f;
+    // values of their own: a select between members of the ray is turned into an indexed access
+    // to it, which would move it to scratch memory
+    const float a0 = ray.a[0], a1 = ray.a[1], a2 = ray.a[2];
+    const float e0 = ray.e[0], e1 = ray.e[1], e2 = ray.e[2];
     // a_i > 0 always, and ie_i = +inf where d_i = 0, so those axes give t_i = +inf
-    const float t0 = ray.a[0] * ray.ie[0];
-    const float t1 = ray.a[1] * ray.ie[1];
-    const float t2 = ray.a[2] * ray.ie[2];
-    // the selects follow the comparisons themselves, not an axis number (a select chain on
-    // w == 0, w == 1 is turned into an indexed access to the ray, which lives in scratch)
-    const bool b1 = t1 < t0;
-    float tw = b1 ? t1 : t0;
-    float aw = b1 ? ray.a[1] : ray.a[0];
-    float ew = b1 ? ray.e[1] : ray.e[0];
-    float iew = b1 ? ray.ie[1] : ray.ie[0];
-    const bool b2 = t2 < tw;
-    tw = b2 ? t2 : tw;
-    aw = b2 ? ray.a[2] : aw;
-    ew = b2 ? ray.e[2] : ew;
-    iew = b2 ? ray.ie[2] : iew;
-    int w = b2 ? 2 : (b1 ? 1 : 0);
-    int mask = b2 ? 4 : (b1 ? 2 : 1);
-    bool at_end;
+    const float t0 = a0 * ray.ie[0];
+    const float t1 = a1 * ray.ie[1];
+    const float t2 = a2 * ray.ie[2];
+    float tw = fminf(fminf(t0, t1), t2);
+    // axes whose boundary the step crosses
+    bool m0 = t0 <= tw, m1 = t1 <= tw, m2 = t2 <= tw;
     if constexpr (PREC == 0) {
-        const bool near = (w != 0 && t0 <= tw * kNear) || (w != 1 && t1 <= tw * kNear) || (w != 2 && t2 <= tw * kNear);
-        if (near) {
-            // exact argmin and ties: t_i < t_j  <=>  a_i e_j < a_j e_i
-            int ww = -1;
-            float ab = 0.0f, eb = 0.0f, ib = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                if (ray.e[i] > 0.0f && (ww < 0 || cmp_prod(ray.a[i], eb, ab, ray.e[i]) < 0)) {
-                    ww = i;
-                    ab = ray.a[i];
-                    eb = ray.e[i];
-                    ib = ray.ie[i];
-                }
+        if (__builtin_amdgcn_fmed3f(t0, t1, t2) <= tw * kNear) {
+            // exact argmin and ties: t_i < t_j  <=>  a_i e_j < a_j e_i (an axis with e = 0 has no
+            // boundary)
+            float ab = a0, eb = e0;
+            tw = t0;
+            if (e1 > 0.0f && (!(eb > 0.0f) || cmp_prod(a1, eb, ab, e1) < 0)) {
+                ab = a1;
+                eb = e1;
+                tw = t1;
             }
-            w = ww;
-            mask = 0;
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                if (ray.e[i] > 0.0f && cmp_prod(ray.a[i], eb, ab, ray.e[i]) == 0) mask |= 1 << i;
-            aw = ab;
-            ew = eb;
-            iew = ib;
-            tw = aw * iew;
+            if (e2 > 0.0f && (!(eb > 0.0f) || cmp_prod(a2, eb, ab, e2) < 0)) {
+                ab = a2;
+                eb = e2;
+                tw = t2;
+            }
+            m0 = e0 > 0.0f && cmp_prod(a0, eb, ab, e0) == 0;
+            m1 = e1 > 0.0f && cmp_prod(a1, eb, ab, e1) == 0;
+            m2 = e2 > 0.0f && cmp_prod(a2, eb, ab, e2) == 0;
         }
-        if (ray.tend > tw * kNear)
-            at_end = false;
-        else if (ray.tend * kNear < tw)
-            at_end = true;
-        else
-            at_end = cmp_prod(ray.tend, ew, aw, 1.0f) <= 0;
-    } else {
-        if (w != 0 && t0 == tw) mask |= 1;
-        if (w != 1 && t1 == tw) mask |= 2;
-        if (w != 2 && t2 == tw) mask |= 4;
-        at_end = ray.tend <= tw;
     }
-    // next path length as a double-float, and the segment length ds = t_next - t_cur
-    float nhi, nlo;
-    if (at_end) {
-        nhi = ray.tend;
-        nlo = 0.0f;
-    } else {
-        nhi = tw;
-        nlo = PREC == 0 ? __builtin_fmaf(-nhi, ew, aw) * iew : 0.0f;
+    const bool lim = tw >= ray.tlim;
+    bool at_end = false;
+    if (lim) {
+        asm volatile("");
+        if constexpr (PREC == 0) {
+            const float aw = m0 ? a0 : (m1 ? a1 : a2);
+            const float ew = m0 ? e0 : (m1 ? e1 : e2);
+            at_end = !(ray.tend > tw * kNear) && (ray.tend * kNear < tw || cmp_prod(ray.tend, ew, aw, 1.0f) <= 0);
+        } else {
+            at_end = ray.tend <= tw;
+        }
     }
-    Seg sg;
+    sg.cell = term_at(ray.o[0]) + term_at(ray.o[1]) + term_at(ray.o[2]);
+    // next path length as a double-float: the low part from the lowest crossed axis. With the
+    // correction the position must not move before its distances are taken.
+    float nhi = tw, nlo = 0.0f;
+    if constexpr (PREC == 0) {
+        if (m2) nlo = __builtin_fmaf(-tw, e2, a2) * ray.ie[2];
+        if (m1) nlo = __builtin_fmaf(-tw, e1, a1) * ray.ie[1];
+        if (m0) nlo = __builtin_fmaf(-tw, e0, a0) * ray.ie[0];
+    }
+    if constexpr (CORR) {
+        const float chi = at_end ? ray.tend : nhi, clo = at_end ? 0.0f : nlo;
+        geom_correction(A, terms, ray, chi, clo, sg);
+    }
+    if (m2) {
+        asm volatile("");
+        ray.a[2] += 1.0f;
+        ray.o[2] += ray.step[2];
+    }
+    if (m1) {
+        asm volatile("");
+        ray.a[1] += 1.0f;
+        ray.o[1] += ray.step[1];
+    }
+    if (m0) {
+        asm volatile("");
+        ray.a[0] += 1.0f;
+        ray.o[0] += ray.step[0];
+    }
+    int ev = kContinue;
+    if (lim) {
+        if (at_end) {
+            nhi = ray.tend;
+            nlo = 0.0f;
+            ev = kSplit;
+        } else if (!(terms.inside(0, ray.o[0], A.nx) && terms.inside(1, ray.o[1], A.ny) && terms.inside(2, ray.o[2], A.nz))) {
+            ev = kEscape;
+        }
+    }
+    // ds = t_next - t_cur. The difference's rounding error in three operations: exact where
+    // nhi >= thi, and where rounding put nhi below thi the difference itself is exact.
     if constexpr (PREC == 0) {
         const float s = nhi - ray.thi;
-        const float bb = s - nhi;
-        const float err = (nhi - (s - bb)) + (-ray.thi - bb);
+        const float err = -ray.thi - (s - nhi);
         sg.ds = s + (err + (nlo - ray.tlo));
     } else {
         sg.ds = nhi - ray.thi;
     }
-    sg.cell = ray.ix[0] + ray.ix[1] + ray.ix[2];
     sg.t1 = nhi;
-    if constexpr (CORR) geom_correction(A, ray, nhi, nlo, sg);
     ray.thi = nhi;
     ray.tlo = nlo;
-    if (at_end) {
-        sg.event = kSplit;
-        return sg;
-    }
-    bool inside = true;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        if (mask & (1 << i)) {
-            const int c = ray.c[i] + ray.step[i];
-            ray.c[i] = c;
-            ray.a[i] += 1.0f;
-            const int n = i == 0 ? A.nx : (i == 1 ? A.ny : A.nz);
-            const bool in = c >= 0 && c < n;
-            inside = inside && in;
-            if (in) ray.ix[i] = axis_term(A, i, c);
-        }
-    }
-    sg.event = inside ? kContinue : kEscape;
-    return sg;
+    return ev;
 }
 
 // Section 2.6: the least path length at which the ray's depth in the softest bin reaches
@@ -495,6 +535,25 @@ __device__ __forceinline__ void thin_reach(const TraceArgs& A, const Ray<NB>& ra
     }
 }
 
+// Bins of a pass that can still add to the field (wave-uniform, one bit per bin). A bin whose
+// photons are all but gone in every lane is left out: with photons S = w T at the start of the
+// pass a crossing adds at most S ds <= sqrt(3) S, or 173 S more where it terminates, which
+// rounds to zero field units once S is below kLiveMin, and S only falls. With the geometric
+// correction the largest of a crossing's deposits is 2 S 2^12 (the moved photons' low limb) or
+// 16 (sqrt(3) + 173) S. Optical depths are kept for every bin (termination, escape and children
+// need them). The soft bins go first: at 256^3 x 1024 sources 1.4 of the three bins are live in
+// the mean, and the trace runs 1.3 times as fast as with all three.
+constexpr float kLiveMin = 0.0009765625f;             // 2^-10
+constexpr float kLiveMinCorr = 0.000030517578125f;    // 2^-15
+template <int NB>
+__device__ __forceinline__ uint32_t live_bins(const Ray<NB>& ray, bool active, const float (&T)[NB], float least)
+{
+    uint32_t live = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) live |= __builtin_amdgcn_ballot_w64(active && ray.w[b] * T[b] >= least) ? 1u << b : 0u;
+    return live;
+}
+
 // Photons of one segment (section 2.4, eq:ion per bin): the amount v_b = S ds g(dtau) for the
 // cell in field units, attenuation (compensated tau), then the termination test (a
 // terminating crossing adds the rest of the photons, S / kappa, to v_b) and, with THIN, the
@@ -502,73 +561,61 @@ __device__ __forceinline__ void thin_reach(const TraceArgs& A, const Ray<NB>& ra
 // (one exponential per bin and crossing): with S = w T_b the photons entering the cell, the
 // cell absorbs S (1 - e^-dtau) = w (T_b - T'_b), so v_b = w (T_b - T'_b) / kappa_b, and below
 // dtau = 0.25, where that difference would cancel, S ds g(dtau) with g's Taylor series
-// (truncation < 5e-8 relative). An escaping ray leaves its remaining photons w T'_b in esc.
-// Returns kTerminate, kSplit, kEscape or kContinue.
+// (truncation < 5e-8 relative). v_b and T_b are kept for the live bins only. Returns whether
+// the ray terminates here.
 template <int NB, int PREC, bool THIN>
-__device__ __forceinline__ int attenuate_seg(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
-                                             LaneStats& st, float v[NB], float (&T)[NB], float (&esc)[NB])
+__device__ __forceinline__ bool attenuate_seg(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
+                                              uint32_t live, float v[NB], float (&T)[NB])
 {
-    bool term = A.tau_term < INFINITY;
     float ts = 0.0f, dts = 0.0f, ks = 1.0f;
-    float rk[NB];
+    float dtau[NB], taup[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const float dtau = kap[b] * sg.ds;
+        dtau[b] = kap[b] * sg.ds;
         if constexpr (THIN) {
             if (b == A.ksoft) {
                 ts = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
-                dts = dtau;
+                dts = dtau[b];
                 ks = kap[b];
             }
         }
         if constexpr (PREC == 0) {
-            const float s = ray.tau[b] + dtau;
-            const float bb = s - ray.tau[b];
-            ray.taulo[b] += (ray.tau[b] - (s - bb)) + (dtau - bb);
+            // the sum's rounding error, exact from the larger of the two terms
+            const float s = ray.tau[b] + dtau[b];
+            ray.taulo[b] += fminf(ray.tau[b], dtau[b]) - (s - fmaxf(ray.tau[b], dtau[b]));
             ray.tau[b] = s;
         } else {
-            ray.tau[b] += dtau;
+            ray.tau[b] += dtau[b];
         }
-        const float taup = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
-        const float Tn = transmission(taup);
+        taup[b] = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
+    }
+    float least = taup[0], thin = dtau[0];
+#pragma unroll
+    for (int b = 1; b < NB; ++b) {
+        least = fminf(least, taup[b]);
+        thin = fminf(thin, dtau[b]);
+    }
+    // (tau_term is +inf where rays never terminate)
+    const bool term = least >= A.tau_term && thin >= kDtauTermMin && A.tau_term < INFINITY;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (!(live & (1u << b))) continue;
+        asm volatile("");  // a branch, not selects: the point is to skip the work
+        const float Tn = transmission(taup[b]);
         // 1 / kappa (hardware reciprocal): used where dtau >= 0.25 or on termination (dtau >= 0.01)
-        rk[b] = __builtin_amdgcn_rcpf(kap[b]);
+        const float rk = __builtin_amdgcn_rcpf(kap[b]), x = dtau[b];
         const float g = __builtin_fmaf(
-            dtau, __builtin_fmaf(dtau, __builtin_fmaf(dtau, __builtin_fmaf(dtau, __builtin_fmaf(dtau, -1.0f / 720.0f, 1.0f / 120.0f), -1.0f / 24.0f), 1.0f / 6.0f), -0.5f),
+            x, __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, -1.0f / 720.0f, 1.0f / 120.0f), -1.0f / 24.0f), 1.0f / 6.0f), -0.5f),
             1.0f);
         const float series = ((ray.w[b] * T[b]) * sg.ds) * g;
-        const float lost = (ray.w[b] * (T[b] - Tn)) * rk[b];
-        v[b] = dtau < 0.25f ? series : lost;
+        const float lost = (ray.w[b] * (T[b] - Tn)) * rk;
+        v[b] = x < 0.25f ? series : lost;
         T[b] = Tn;
-        term = term && taup >= A.tau_term && dtau >= kDtauTermMin;
+        // termination: absorb what is left in this cell, field += remaining photons / opacity
+        if (term) v[b] = __builtin_fmaf(ray.w[b] * Tn, rk, v[b]);
     }
-    st.crossings++;
     if constexpr (THIN) thin_reach<NB>(A, ray, sg, ts, dts, ks);
-    if (term) {
-        // absorb what is left in this cell: field += remaining photons / opacity
-#pragma unroll
-        for (int b = 0; b < NB; ++b) v[b] = __builtin_fmaf(ray.w[b] * T[b], rk[b], v[b]);
-        st.terminated++;
-        return kTerminate;
-    }
-    if (sg.event == kSplit) {
-        st.splits++;
-        return kSplit;
-    }
-    if (sg.event == kEscape) {
-        float tsp = 0.0f;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            esc[b] = ray.w[b] * T[b];
-            if (b == A.ksoft) tsp = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
-        }
-        // a ray that leaves the grid while still thin bounds the thin radius by its exit
-        if constexpr (THIN)
-            if (tsp < kTauThin) atomicMin(A.r_out + ray.src, __float_as_uint(sg.t1));
-        st.escaped++;
-        return kEscape;
-    }
-    return kContinue;
+    return term;
 }
 
 // Transmission e^-tau of every bin of a ray at its current depth.
@@ -579,24 +626,28 @@ __device__ __forceinline__ void ray_transmission(const Ray<NB>& ray, float (&T)[
     for (int b = 0; b < NB; ++b) T[b] = transmission(PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b]);
 }
 
-// Photons an escaping lane carried out of the grid, into the FP64 ledger (once per pass).
-template <int NB>
-__device__ __forceinline__ void book_escape(int ev, const float (&esc)[NB], LaneStats& st)
-{
-    if (ev == kEscape) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) st.esc[b] += (double)esc[b];
-    }
-}
-
-// A segment's deposit into its own cell.
+// A lane's event of the pass into the wave's counts; the photons an escaping lane carried out of
+// the grid go into the FP64 ledger.
 template <int NB, int PREC, bool THIN>
-__device__ __forceinline__ int deposit_seg(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
-                                           LaneStats& st, Dep<NB>& dep, float (&T)[NB], float (&esc)[NB])
+__device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ray<NB>& ray, WaveStats& st)
 {
-    const int ev = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, st, dep.v, T, esc);
-    dep.cell = sg.cell;
-    return ev;
+    st.splits += count_lanes(ev == kSplit);
+    st.terminated += count_lanes(ev == kTerminate);
+    st.escaped += count_lanes(ev == kEscape);
+    if (ev == kEscape) {
+        float T[NB];
+        ray_transmission<NB, PREC>(ray, T);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) st.esc[b] += (double)(ray.w[b] * T[b]);
+        // a ray that leaves the grid while still thin bounds the thin radius by its exit
+        if constexpr (THIN) {
+            float tsp = 0.0f;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if (b == A.ksoft) tsp = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
+            if (tsp < kTauThin) atomicMin(A.r_out + ray.src, __float_as_uint(ray.thi));
+        }
+    }
 }
 
 // Limbs of the moved-photon field: mv = hi 2^20 + lo 2^-12 (units of u_J,b). A crossing's lo
@@ -634,15 +685,15 @@ constexpr float kMovedRatioJ = 16.0f;
 // with no absorber of the bin (kappa_nb = 0) leaves the share in the cell. Modes 1 and 3
 // drop the removed share. dj and dm name the neighbour only when some bin uses them.
 template <int NB, int PREC, bool THIN>
-__device__ __forceinline__ int deposit_seg_corr(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
-                                                const float kapn[NB], LaneStats& st, Dep<NB>& dep, Dep<NB>& dj,
-                                                Dep<NB>& dm, float (&T)[NB], float (&esc)[NB])
+__device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
+                                                 const float kapn[NB], uint32_t live, Dep<NB>& dep, Dep<NB>& dj,
+                                                 Dep<NB>& dm, bool& use_j, bool& use_m, float (&T)[NB])
 {
     float v[NB];
-    const int ev = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, st, v, T, esc);
-    bool use_j = false, use_m = false;
+    const bool term = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, live, v, T);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+        if (!(live & (1u << b))) continue;
         float keep = v[b], mj = 0.0f, mm = 0.0f;
         if (sg.fc < 1.0f) {
             if (sg.nb == kNoCell) {
@@ -663,30 +714,21 @@ __device__ __forceinline__ int deposit_seg_corr(const TraceArgs& A, Ray<NB>& ray
         dj.v[b] = mj;
         dm.v[b] = mm;
     }
-    dep.cell = sg.cell;
-    dj.cell = use_j ? sg.nb : kNoCell;
-    dm.cell = use_m ? sg.nb : kNoCell;
-    return ev;
+    return term;
 }
 
-// Segments whose geometry is computed ahead of their deposits (opacity loads in flight
-// per lane), and segments of each lane whose deposits the wave merges together: the merge
-// window of four (256 crossings) fits the LDS of three waves per SIMD beside the family
-// stacks, and the kernel's time follows the atomic items it leaves (1024^3 x 16384 sources:
-// windows of two and ten segments ahead, 0.273 items per crossing and 715 ms; windows of four
-// and eight ahead, 0.236 and 686 ms; twelve ahead, 682 ms). With thin spheres the extra state
-// leaves room for eight only (twelve spill registers).
-#ifndef ARC_SEG_AHEAD
-#define ARC_SEG_AHEAD 12
-#endif
-constexpr int kSegAhead = ARC_SEG_AHEAD;
-constexpr int kSegAheadThin = 8;
-template <bool THIN>
-constexpr int seg_ahead() { return THIN ? kSegAheadThin : kSegAhead; }
-#ifndef ARC_DEP_WINDOW
-#define ARC_DEP_WINDOW 4
-#endif
-constexpr int kDepWindow = ARC_DEP_WINDOW;
+// Segments whose geometry is computed ahead of their deposits (opacity loads in flight per
+// lane), and segments of each lane whose deposits the wave merges together. VALU issue bounds the
+// trace (90% at 256^3 x 1024 sources: 3.9 wave-instructions per crossing, 46 of 64 lanes active),
+// so both are flat over a wide range there (persistent launch, ms; lines per crossing): twelve
+// ahead with windows of 4, 6 and 12: 29.9, 29.0 and 29.6; 0.116, 0.103 and 0.090; eight ahead
+// with windows of 4 and 8: 30.2 and 29.3. Wider windows make fewer lines, but more of their
+// tiles want the same table entry. With the geometric correction two opacities per segment leave
+// room for four.
+constexpr int kSegAhead = 12;
+constexpr int kDepWindow = 6;
+constexpr int kSegAheadCorr = 4;
+constexpr int kDepWindowCorr = 4;
 
 // Up to K crossings of one lane per pass: the geometry of K segments is computed first
 // and their opacities are loaded together (K loads in flight per lane), then the
@@ -695,109 +737,131 @@ constexpr int kDepWindow = ARC_DEP_WINDOW;
 // the source's thin sphere) splits at once, without a crossing.
 // Returns the lane's final event of the pass (kContinue if the ray goes on).
 template <int NB, int PREC, int K, bool THIN, class Depositor>
-__device__ __forceinline__ int trace_pass(const TraceArgs& A, Ray<NB>& ray, bool active, LaneStats& st,
-                                          Depositor& deposit)
+__device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, bool active,
+                                          WaveStats& st, Depositor& deposit)
 {
     Seg sg[K];
-    bool have[K];
+    int nseg = 0;  // segments of the lane (a count, not K lane masks: those spill)
     bool go = active;
     int ev = kContinue;
     if constexpr (THIN) {
         if (active && !(ray.thi < ray.tend)) {
             go = false;
             ev = kSplit;
-            st.splits++;
         }
     }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        have[j] = go;
+        sg[j].cell = 0u;
         if (go) {
-            sg[j] = geom_next<NB, PREC>(A, ray);
-            go = sg[j].event == kContinue;
+            ev = geom_next<NB, PREC>(A, terms, ray, sg[j]);
+            nseg = j + 1;
+            go = ev == kContinue;
         }
     }
     // the gathers are issued unconditionally (cell 0 for a lane without the segment), so that
     // no branch separates them and each deposit waits for its own gather only
     float kap[K][NB];
 #pragma unroll
-    for (int j = 0; j < K; ++j) kappa_at<NB>(A, have[j] ? sg[j].cell : 0u, kap[j]);
-    float T[NB], esc[NB];
+    for (int j = 0; j < K; ++j) kappa_at<NB>(A, sg[j].cell, kap[j]);
+    float T[NB];
     ray_transmission<NB, PREC>(ray, T);
+    const uint32_t live = live_bins<NB>(ray, active, T, kLiveMin);
     // every gather is consumed before the pass issues its first atomic (a wait for a gather
     // issued before an unknown number of atomics would wait for all of them)
     static_assert(K % kDepWindow == 0, "whole windows per pass");
     Dep<NB> dep[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        dep[j].cell = kNoCell;
-        if (have[j] && ev == kContinue) ev = deposit_seg<NB, PREC, THIN>(A, ray, sg[j], kap[j], st, dep[j], T, esc);
+        dep[j].cell = sg[j].cell;
+        if (j < nseg && attenuate_seg<NB, PREC, THIN>(A, ray, sg[j], kap[j], live, dep[j].v, T)) {
+            nseg = j + 1;
+            ev = kTerminate;
+        }
     }
+    st.crossings += (uint32_t)nseg;
 #pragma unroll
-    for (int j0 = 0; j0 < K; j0 += kDepWindow) deposit.template add<kWhole>(dep + j0, A.J, A.nbp);
-    book_escape<NB>(ev, esc, st);
+    for (int j0 = 0; j0 < K; j0 += kDepWindow) {
+        bool on[kDepWindow];
+#pragma unroll
+        for (int w = 0; w < kDepWindow; ++w) on[w] = j0 + w < nseg;
+        deposit.template add<kWhole, kDepWindow>(dep + j0, on, live, A.J, NB);
+    }
+    book_events<NB, PREC, THIN>(A, ev, ray, st);
     return ev;
 }
 
 // trace_pass with the geometric correction: up to K crossings per lane, the neighbours'
 // opacities loaded with the cells'. The crossings' cells form windows, as without the
 // correction; in mode 2 their neighbours' high limbs, then their low limbs, form two more.
-#ifndef ARC_SEG_AHEAD_CORR
-#define ARC_SEG_AHEAD_CORR 4
-#endif
-constexpr int kSegAheadCorr = ARC_SEG_AHEAD_CORR;
 template <int NB, int PREC, int K, bool THIN, class Depositor>
-__device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, Ray<NB>& ray, bool active, LaneStats& st,
-                                               Depositor& deposit)
+__device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, bool active,
+                                               WaveStats& st, Depositor& deposit)
 {
-    static_assert(K % kDepWindow == 0, "whole windows per pass");
+    static_assert(K % kDepWindowCorr == 0, "whole windows per pass");
     Seg sg[K];
-    bool have[K];
+    int nseg = 0;  // segments of the lane (a count, not K lane masks: those spill)
     bool go = active;
     int ev = kContinue;
     if constexpr (THIN) {
         if (active && !(ray.thi < ray.tend)) {
             go = false;
             ev = kSplit;
-            st.splits++;
         }
     }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        have[j] = go;
+        sg[j].cell = 0u;
+        sg[j].nb = kNoCell;
         if (go) {
-            sg[j] = geom_next<NB, PREC, true>(A, ray);
-            go = sg[j].event == kContinue;
+            ev = geom_next<NB, PREC, true>(A, terms, ray, sg[j]);
+            nseg = j + 1;
+            go = ev == kContinue;
         }
     }
     float kap[K][NB], kapn[K][NB];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const bool hn = have[j] && sg[j].nb != kNoCell;
-        kappa_at<NB>(A, have[j] ? sg[j].cell : 0u, kap[j]);
+        const bool hn = sg[j].nb != kNoCell;
+        kappa_at<NB>(A, sg[j].cell, kap[j]);
         kappa_at<NB>(A, hn ? sg[j].nb : 0u, kapn[j]);
 #pragma unroll
         for (int b = 0; b < NB; ++b) kapn[j][b] = hn ? kapn[j][b] : 0.0f;
     }
-    float T[NB], esc[NB];
+    float T[NB];
     ray_transmission<NB, PREC>(ray, T);
+    const uint32_t live = live_bins<NB>(ray, active, T, kLiveMinCorr);
     Dep<NB> dep[K], dj[K], dm[K];
+    bool use_j[K], use_m[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        dep[j].cell = dj[j].cell = dm[j].cell = kNoCell;
-        if (have[j] && ev == kContinue)
-            ev = deposit_seg_corr<NB, PREC, THIN>(A, ray, sg[j], kap[j], kapn[j], st, dep[j], dj[j], dm[j], T, esc);
-    }
-#pragma unroll
-    for (int j = 0; j < K; j += kDepWindow) {
-        deposit.template add<kWhole>(dep + j, A.J, A.nbp);
-        if (A.corr == 2) {
-            deposit.template add<kWhole>(dj + j, A.J, A.nbp);
-            deposit.template add<kMovedHi>(dm + j, A.M, 2 * A.nbp);
-            deposit.template add<kMovedLo>(dm + j, A.M + A.nbp, 2 * A.nbp);
+        use_j[j] = use_m[j] = false;
+        dep[j].cell = sg[j].cell;
+        dj[j].cell = dm[j].cell = sg[j].nb != kNoCell ? sg[j].nb : 0u;
+        if (j < nseg && deposit_seg_corr<NB, PREC, THIN>(A, ray, sg[j], kap[j], kapn[j], live, dep[j], dj[j], dm[j],
+                                                         use_j[j], use_m[j], T)) {
+            nseg = j + 1;
+            ev = kTerminate;
         }
     }
-    book_escape<NB>(ev, esc, st);
+    st.crossings += (uint32_t)nseg;
+#pragma unroll
+    for (int j = 0; j < K; j += kDepWindowCorr) {
+        bool on[kDepWindowCorr], onj[kDepWindowCorr], onm[kDepWindowCorr];
+#pragma unroll
+        for (int w = 0; w < kDepWindowCorr; ++w) {
+            on[w] = j + w < nseg;
+            onj[w] = use_j[j + w];
+            onm[w] = use_m[j + w];
+        }
+        deposit.template add<kWhole, kDepWindowCorr>(dep + j, on, live, A.J, NB);
+        if (A.corr == 2) {
+            deposit.template add<kWhole, kDepWindowCorr>(dj + j, onj, live, A.J, NB);
+            deposit.template add<kMovedHi, kDepWindowCorr>(dm + j, onm, live, A.M, 2 * NB);
+            deposit.template add<kMovedLo, kDepWindowCorr>(dm + j, onm, live, A.M + 8 * NB, 2 * NB);
+        }
+    }
+    book_events<NB, PREC, THIN>(A, ev, ray, st);
     return ev;
 }
 
@@ -861,163 +925,142 @@ __device__ __forceinline__ StackRec<NB> family_child(const StackRec<NB>& f, int 
     return r;
 }
 
-// Fixed-point deposition, called by all 64 lanes together, into an int64 field `base` with
-// `stride` words per cell (the field J, or a limb of the moved-photon field M). Atomic adds
-// cost per distinct cache line an instruction touches, so the NB bins of a cell are issued
-// by NB adjacent lanes of the same instruction: instruction k, lane j adds bin (64k + j) mod
-// NB of item (64k + j) / NB.
-#ifndef ARC_DEDUP
-#define ARC_DEDUP 1  // 0: every lane's crossing deposited on its own
-#endif
-constexpr int kDepSlots = 128 * kDepWindow;  // hash slots per wave
-constexpr int kDepShift = kDepWindow == 1 ? 32 - 7 : (kDepWindow == 2 ? 32 - 8 : 32 - 9);
-static_assert(kDepWindow == 1 || kDepWindow == 2 || kDepWindow == 4, "window of 1, 2 or 4 segments");
+// Fixed-point deposition, called by all 64 lanes together.
+//
+// Every int64 atomic of the chip is carried out by the memory side of the fabric, never in L2
+// (TCC_EA0_ATOMIC equals TCC_ATOMIC), one request per 64-byte line and instruction whether one or
+// all eight words of the line take part: 1.75e10 requests/s on random lines, 2.4e10 at most. So
+// the field keeps the eight cells of a 2x2x2 tile and one bin in one 64-byte line (field_word),
+// and a wave sums its crossings per tile in LDS before it issues a line. A crossing's sum goes
+// to a table of one bin at a time, indexed by the cell's place inside its 8^3 block: 64 tiles,
+// each tagged with the block it belongs to. A wave's rays are a compact bundle, so its
+// crossings of a window seldom want one table entry for two blocks; where they do, the tiles
+// that lost the entry go in another round (every round serves at least one tile of each wanted
+// entry, so the rounds end). Bins are taken one after the other through the same table, so
+// that it takes 4 KB whatever the number of bins. Integer sums: the field does not depend on
+// any of this.
+constexpr uint32_t kNoBlock = 0xFFFFFFFFu;
 
-// Per-wave LDS space of the deduplicating deposit (item ids and ranks fit in a byte).
-template <int NB>
+// Per-wave LDS space of the deposits. Between windows every sum is zero and every tag kNoBlock.
 struct DepScratch {
-    uint32_t slot_cell[kDepSlots];
-    uint8_t slot_id[kDepSlots];
-    uint8_t slot_rank[kDepSlots];
-    uint32_t cell[64 * kDepWindow];
-    unsigned long long q[64 * kDepWindow][NB];
+    unsigned long long acc[512];  // sums of one bin, by place in the block
+    uint32_t tag[64];             // block whose tile holds the entry
+    uint8_t used[64];             // entries in use, compacted
 };
 
-template <int NB, int LIMB>
-__device__ __forceinline__ void deposit_wave_plain(const Dep<NB>& d, unsigned long long* base, int stride)
+// Called by all 64 lanes of the wave that owns the scratch, before its first window.
+__device__ __forceinline__ void dep_scratch_init(DepScratch* S)
 {
     const int lane = threadIdx.x & 63;
-    long long qd[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) qd[b] = to_fixed<LIMB>(d.v[b]);
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const int s = 64 * k + lane;
-        const int item = s / NB, bin = s - item * NB;
-        const uint32_t cell = (uint32_t)__shfl((int)d.cell, item, 64);
-        long long q = 0;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const long long qb = __shfl(qd[b], item, 64);
-            q = b == bin ? qb : q;
-        }
-        if (cell != kNoCell && q != 0) atomicAdd(base + (size_t)cell * (size_t)stride + (size_t)bin, (unsigned long long)q);
-    }
+    for (int i = lane; i < 512; i += 64) S->acc[i] = 0ull;
+    S->tag[lane] = kNoBlock;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// Crossings of the same cell, by several lanes and over the kDepWindow segments each lane
-// brings, are first summed in LDS, so that each distinct cell costs one set of atomics
-// (integer sums: the result is bitwise the same). Items hash their cell into a per-wave
-// table; items whose cell owns its slot add into the slot's entry, items whose slot was
-// taken by another cell go alone. LDS operations of one wave complete in issue order, and
-// the racy table accesses are volatile so that each read really observes the wave's writes.
-// Items whose integers are all zero are dropped. Returns the number of items issued
-// (wave-uniform).
-template <int NB, int LIMB>
-__device__ __forceinline__ int deposit_wave_dedup(const Dep<NB>* d, DepScratch<NB>* S, unsigned long long* base,
-                                                  int stride)
+// One round of a window: the crossings with `pend` whose tile gets its table entry go into the
+// field and leave `pend`. Returns the lines issued per live bin (wave-uniform).
+template <int NB, int LIMB, int W>
+__device__ __forceinline__ int deposit_round(const Dep<NB>* d, bool (&pend)[W], uint32_t live, DepScratch* S,
+                                             unsigned long long* base, int lines)
 {
-    constexpr int W = kDepWindow;
-    bool v[W];
-    bool anyv = false;
-#pragma unroll
-    for (int w = 0; w < W; ++w) anyv = anyv || d[w].cell != kNoCell;
-    if (!__any(anyv)) return 0;
-    long long q[W][NB];
-    anyv = false;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        bool nz = false;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            q[w][b] = to_fixed<LIMB>(d[w].v[b]);
-            nz = nz || q[w][b] != 0;
-        }
-        v[w] = d[w].cell != kNoCell && nz;
-        anyv = anyv || v[w];
-    }
-    if (!__any(anyv)) return 0;
     // LDS-qualified views: through a generic pointer the accesses would be FLAT instructions,
     // which also wait for the wave's outstanding gathers and atomics
-    volatile kLds uint32_t* slot_cell = (volatile kLds uint32_t*)S->slot_cell;
-    volatile kLds uint8_t* slot_id = (volatile kLds uint8_t*)S->slot_id;
-    volatile kLds uint8_t* slot_rank = (volatile kLds uint8_t*)S->slot_rank;
-    volatile kLds uint32_t* st_cell = (volatile kLds uint32_t*)S->cell;
-    volatile kLds unsigned long long* st_q = (volatile kLds unsigned long long*)&S->q[0][0];
-    kLds unsigned long long* acc_q = (kLds unsigned long long*)&S->q[0][0];
+    volatile kLds uint32_t* tag = (volatile kLds uint32_t*)S->tag;
+    volatile kLds uint8_t* used = (volatile kLds uint8_t*)S->used;
+    kLds unsigned long long* acc = (kLds unsigned long long*)S->acc;
     const int lane = threadIdx.x & 63;
-    const uint64_t lt = __lanemask_lt();
-    bool in[W], lead[W];
-    uint32_t h[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) h[w] = (d[w].cell * 2654435761u) >> kDepShift;
+    // the last crossing that wants an entry names its block; LDS operations of one wave
+    // complete in issue order
 #pragma unroll
     for (int w = 0; w < W; ++w)
-        if (v[w]) slot_cell[h[w]] = d[w].cell;
+        if (pend[w]) tag[(d[w].cell >> 3) & 63u] = d[w].cell >> 9;
+    uint32_t got[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) in[w] = v[w] && slot_cell[h[w]] == d[w].cell;
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-        if (in[w]) slot_id[h[w]] = (uint8_t)(64 * w + lane);
-#pragma unroll
-    for (int w = 0; w < W; ++w) lead[w] = in[w] && slot_id[h[w]] == (uint8_t)(64 * w + lane);
-    int rank[W];
-    int n = 0;
+    for (int w = 0; w < W; ++w) got[w] = tag[(d[w].cell >> 3) & 63u];
+    const bool mine = tag[lane] != kNoBlock;
+    bool in[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const bool emit = lead[w] || (v[w] && !in[w]);
-        const uint64_t em = __ballot(emit);
-        rank[w] = emit ? n + __popcll(em & lt) : -1;
-        n += __popcll(em);
+        in[w] = pend[w] && got[w] == d[w].cell >> 9;
+        pend[w] = pend[w] && !in[w];
     }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(mine);
+    const int n = __popcll(mask);
+    if (mine) used[__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = (uint8_t)lane;
 #pragma unroll
-    for (int w = 0; w < W; ++w)
-        if (lead[w]) slot_rank[h[w]] = (uint8_t)rank[w];
+    for (int b = 0; b < NB; ++b) {
+        if (!(live & (1u << b))) continue;
 #pragma unroll
-    for (int w = 0; w < W; ++w)
-        if (rank[w] >= 0) {
-            st_cell[rank[w]] = d[w].cell;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) st_q[rank[w] * NB + b] = (unsigned long long)q[w][b];
+        for (int w = 0; w < W; ++w) {
+            float v = d[w].v[b];
+            asm volatile("" : "+v"(v));  // the conversion stays inside the live bin's branch
+            if (in[w])
+                __hip_atomic_fetch_add(acc + (d[w].cell & 511u), (unsigned long long)to_fixed<LIMB>(v), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-        if (in[w] && !lead[w]) {
-            const uint32_t r = slot_rank[h[w]];
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                if (q[w][b] != 0) __hip_atomic_fetch_add(acc_q + r * NB + b, (unsigned long long)q[w][b],
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // eight entries per instruction, a line each
+        for (int i0 = 0; i0 < n; i0 += 8) {
+            const int r = i0 + (lane >> 3);
+            if (r < n) {
+                const uint32_t s = used[r], t = tag[s];
+                volatile kLds unsigned long long* e = (volatile kLds unsigned long long*)acc + (s * 8u + (lane & 7));
+                const unsigned long long q = *e;
+                *e = 0ull;
+                if (q != 0)
+                    atomicAdd(base + ((size_t)((t << 6) | s) * (uint32_t)lines + (uint32_t)b) * 8u + (lane & 7), q);
+            }
         }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const int tot = n * NB;
-    for (int s = lane; s < tot; s += 64) {
-        const int item = s / NB, bin = s - item * NB;
-        const uint32_t cell = st_cell[item];
-        const unsigned long long q = st_q[item * NB + bin];
-        if (q != 0) atomicAdd(base + (size_t)cell * (size_t)stride + (size_t)bin, q);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
+    if (mine) tag[lane] = kNoBlock;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     return n;
+}
+
+// W crossings of every lane, their live bins, into the field at `base`, `lines` 64-byte lines per
+// tile (the bins of the field, or of both limbs of the moved-photon field). Returns the lines
+// issued (wave-uniform).
+template <int NB, int LIMB, int W>
+__device__ __forceinline__ int deposit_window(const Dep<NB>* d, const bool (&on)[W], uint32_t live, DepScratch* S,
+                                              unsigned long long* base, int lines)
+{
+    if (live == 0) return 0;
+    bool pend[W];
+    bool any = false;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        pend[w] = on[w];
+        any = any || pend[w];
+    }
+    if (!__builtin_amdgcn_ballot_w64(any)) return 0;
+    int n = deposit_round<NB, LIMB, W>(d, pend, live, S, base, lines);
+    uint32_t left = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) left |= pend[w] ? 1u << w : 0u;
+#pragma unroll 1
+    while (__builtin_amdgcn_ballot_w64(left != 0)) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) pend[w] = (left >> w) & 1u;
+        n += deposit_round<NB, LIMB, W>(d, pend, live, S, base, lines);
+        left = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) left |= pend[w] ? 1u << w : 0u;
+    }
+    return n * __popc(live);
 }
 
 // Wave-wide deposit of the crossings of a pass: add() once per window of kDepWindow
 // segments, by every lane.
 template <int NB>
 struct Depositor {
-    DepScratch<NB>* scratch;
-    uint32_t items = 0;  // deposit items issued by this wave (wave-uniform)
-    // the kDepWindow items d[0 .. kDepWindow) of every lane, as integers of limb LIMB
-    template <int LIMB>
-    __device__ void add(const Dep<NB>* d, unsigned long long* base, int stride)
+    DepScratch* scratch;
+    uint32_t items = 0;  // lines issued by this wave (wave-uniform)
+    // the crossings d[0 .. W) of every lane, as integers of limb LIMB
+    template <int LIMB, int W>
+    __device__ void add(const Dep<NB>* d, const bool (&on)[W], uint32_t live, unsigned long long* base, int lines)
     {
-        if constexpr (ARC_DEDUP == 1) {
-            items += (uint32_t)deposit_wave_dedup<NB, LIMB>(d, scratch, base, stride);
-        } else {
-#pragma unroll
-            for (int w = 0; w < kDepWindow; ++w) deposit_wave_plain<NB, LIMB>(d[w], base, stride);
-        }
+        items += (uint32_t)deposit_window<NB, LIMB, W>(d, on, live, scratch, base, lines);
     }
     __device__ void flush(const TraceArgs& A) const
     {
@@ -1038,22 +1081,18 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 }
 
 template <int NB>
-__device__ __forceinline__ void flush_stats(const TraceArgs& A, const LaneStats& st)
+__device__ __forceinline__ void flush_stats(const TraceArgs& A, const WaveStats& st)
 {
-    const unsigned long long c = wave_sum_u64(st.crossings);
-    const unsigned long long r = wave_sum_u64(st.rays);
-    const unsigned long long s = wave_sum_u64(st.splits);
-    const unsigned long long t = wave_sum_u64(st.terminated);
-    const unsigned long long e = wave_sum_u64(st.escaped);
+    const unsigned long long crossings = wave_sum_u64(st.crossings);
     double esc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) esc[b] = wave_sum_f64(st.esc[b]);
     if ((threadIdx.x & 63) == 0) {
-        if (c) atomicAdd(&A.counters[kCrossings], c);
-        if (r) atomicAdd(&A.counters[kRays], r);
-        if (s) atomicAdd(&A.counters[kSplits], s);
-        if (t) atomicAdd(&A.counters[kTerminated], t);
-        if (e) atomicAdd(&A.counters[kEscapedRays], e);
+        if (crossings) atomicAdd(&A.counters[kCrossings], crossings);
+        if (st.rays) atomicAdd(&A.counters[kRays], st.rays);
+        if (st.splits) atomicAdd(&A.counters[kSplits], st.splits);
+        if (st.terminated) atomicAdd(&A.counters[kTerminated], st.terminated);
+        if (st.escaped) atomicAdd(&A.counters[kEscapedRays], st.escaped);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
             if (esc[b] != 0.0) atomicAdd(&A.esc[b], esc[b]);

@@ -19,12 +19,11 @@ struct OpacityArgs {
     float4* kappa4;
     unsigned long long* J;
     unsigned long long* M;     // moved-photon field of the conserving correction, or null
-    int nbp;
     int* errflag;
 };
 
 struct FinalizeArgs {
-    int nb, nbp;
+    int nb;
     int nx, ny, nz, nbx8, nby8, nbz8;
     uint32_t ncell;
     double gam[kMaxBins][3];   // u_J,b sigma_bS / L^2
@@ -40,7 +39,7 @@ struct FinalizeArgs {
 
 // Section 2.6 fill of the optically thin spheres.
 struct ThinFillArgs {
-    int nb, nbp, nsrc, parts;  // parts: blocks per source
+    int nb, nsrc, parts;       // parts: blocks per source
     int nx, ny, nz, nbx8, nby8;
     const double *pos, *ndot, *r_thin;
     double coef[kMaxBins];     // frac_b / (4 pi u_J,b)
@@ -94,12 +93,12 @@ hipError_t launch_trace_persistent(const TraceArgs& A, int prec, const RayRec* i
                                    int refill, int fam, int stack_cap, hipStream_t s);
 int persistent_max_waves();
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
-hipError_t launch_probe_deposits(unsigned long long* J, int nbp, int nb, uint64_t ncell, uint64_t items,
-                                 uint64_t seed, int cus, hipStream_t s);
+hipError_t launch_probe_deposits(unsigned long long* J, uint64_t nline, uint64_t items, uint64_t seed, int cus,
+                                 hipStream_t s);
 hipError_t launch_probe_gathers(const float4* kappa, uint64_t ncell, uint64_t items, uint64_t seed, float* sink,
                                 int cus, hipStream_t s);
-hipError_t launch_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nbp, int nx, int ny,
-                            int nbx8, int nby8, uint32_t ncell, long long* dst, hipStream_t s);
+hipError_t launch_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nx, int ny, int nbx8,
+                            int nby8, uint32_t ncell, long long* dst, hipStream_t s);
 // cus: compute units of the device (the solver launches resident waves only)
 hipError_t launch_chem(const ChemArgs& a, int cus, hipStream_t s);
 

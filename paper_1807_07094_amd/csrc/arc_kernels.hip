@@ -177,10 +177,10 @@ __global__ __launch_bounds__(256) void k_opacity(OpacityArgs a)
             else
                 a.kappa4[g.base + o] = st[o];
         }
-        const uint32_t words = g.cells * (uint32_t)a.nbp;
-        for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) a.J[(size_t)g.base * a.nbp + w] = 0ull;
+        const uint32_t words = g.cells * (uint32_t)NB;
+        for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) a.J[(size_t)g.base * NB + w] = 0ull;
         if (a.M)
-            for (uint32_t w = threadIdx.x; w < 2u * words; w += blockDim.x) a.M[2ull * g.base * a.nbp + w] = 0ull;
+            for (uint32_t w = threadIdx.x; w < 2u * words; w += blockDim.x) a.M[2ull * g.base * NB + w] = 0ull;
         __syncthreads();
     }
 }
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void k_thin_fill(ThinFillArgs a)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const long long q = llrint(inv * a.coef[b]);
-                if (q != 0) atomicAdd(a.J + (size_t)cell * a.nbp + b, (unsigned long long)q);
+                if (q != 0) atomicAdd(a.J + field_word(cell, NB, b), (unsigned long long)q);
                 absorbed += (double)q * a.uj[b] * (double)k[b];
             }
         }
@@ -418,6 +418,14 @@ hipError_t launch_seed_roots(uint32_t first_src, uint32_t nsrc, int level0, cons
     return hipGetLastError();
 }
 
+// Dynamic LDS of the trace kernels: the index terms of the grid's axes, then the persistent
+// launch's stacks.
+extern __shared__ __align__(16) unsigned char arc_dyn_lds[];
+__host__ __device__ __forceinline__ size_t terms_bytes(const TraceArgs& A)
+{
+    return ((size_t)(A.nx + A.ny + A.nz) * sizeof(uint32_t) + 15u) & ~(size_t)15u;
+}
+
 // -------------------------------------------------------------------------------------
 // Per-level schedule (section 2.1 iii b/c): one ray per lane, traced until it splits,
 // terminates or leaves the grid; splitting lanes write their four children into the
@@ -430,9 +438,12 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
                                                     int fam_out)
 {
     const uint32_t n_in = n_in_dev ? *n_in_dev : n_in_host;
-    __shared__ DepScratch<NB> dscr[4];
+    __shared__ DepScratch dscr[4];
     Depositor<NB> dep{dscr + (threadIdx.x >> 6)};
-    LaneStats st;
+    dep_scratch_init(dep.scratch);
+    const Terms terms = make_terms(A, reinterpret_cast<uint32_t*>(arc_dyn_lds));
+    __syncthreads();
+    WaveStats st;
     st.clear();
     const int lane = threadIdx.x & 63;
     const uint64_t lt = __lanemask_lt();
@@ -445,15 +456,17 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
         if (i < n_in) {
             const RayRec r = in[i];
             record_tree<NB>(A, r.src, r.lp);
-            act = ray_init<NB, THIN>(A, r, ray, st);
+            act = ray_init<NB, THIN>(A, terms, r, ray, st);
         }
+        st.rays += count_lanes(i < n_in);
+        st.escaped += count_lanes(i < n_in && !act);
         // a few crossings per lane per pass; the wave deposits each crossing together
         while (__any(act)) {
             int e;
             if constexpr (CORR)
-                e = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, act, st, dep);
+                e = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, terms, ray, act, st, dep);
             else
-                e = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, act, st, dep);
+                e = trace_pass<NB, PREC, kSegAhead, THIN>(A, terms, ray, act, st, dep);
             if (act && e != kContinue) {
                 ev = e;
                 act = false;
@@ -495,15 +508,15 @@ static hipError_t trace_rays_nb(const TraceArgs& A, int prec, const RayRec* in, 
     const unsigned g = grid_for(n_in, 256, 1u << 16);
     const bool thin = A.r_out != nullptr;
     if (prec == 0 && A.corr && thin)
-        k_trace_rays<NB, 0, true, true><<<g, 256, 0, s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        k_trace_rays<NB, 0, true, true><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
     else if (prec == 0 && A.corr)
-        k_trace_rays<NB, 0, true, false><<<g, 256, 0, s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        k_trace_rays<NB, 0, true, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
     else if (prec == 0 && thin)
-        k_trace_rays<NB, 0, false, true><<<g, 256, 0, s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        k_trace_rays<NB, 0, false, true><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
     else if (prec == 0)
-        k_trace_rays<NB, 0, false, false><<<g, 256, 0, s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        k_trace_rays<NB, 0, false, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
     else
-        k_trace_rays<NB, 1, false, false><<<g, 256, 0, s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        k_trace_rays<NB, 1, false, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
     return hipGetLastError();
 }
 
@@ -531,16 +544,17 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 // root rays when there was none); every new ray of the iteration is started in one place. The
 // stack's top holds the latest splits, so the four children of a ray, and the children of rays
 // that split together, enter together and cross the same cells in the same passes: the wave's
-// deposit merge then sums their crossings of a cell into one atomic item (the int64 atomics in
-// L2 and the VALU issue share the limit of this kernel). The LDS stack is a ring: when it would overflow, its
-// oldest entries move to the top of the spill area, so the pair behaves as one LIFO stack and
+// deposit merge then sums their crossings of a 2x2x2 tile into one 64-byte line per bin. VALU
+// issue bounds the kernel (256^3 x 1024 sources: 29.0 ms, 1.42e11 crossings/s; with a merge per
+// cell, an index computed per step and every bin attenuated to the end 49.1 ms, where the
+// atomics' request rate was as close). The LDS stack is a ring: when it would overflow, its oldest
+// entries move to the top of the spill area, so the pair behaves as one LIFO stack and
 // the wave works depth first. Waves share nothing but the work-queue head, so each wave ends
 // when the queue is drained and its own stacks are empty.
 // -------------------------------------------------------------------------------------
-// The stacks live in dynamic LDS: stack_cap family records per wave, a power of two of at
-// least 64 (a split round of all lanes must fit the ring), chosen at launch (the autotuner's
-// LDS stack depth).
-extern __shared__ __align__(16) unsigned char arc_stack_lds[];
+// The stacks live in dynamic LDS, behind the table of index terms: stack_cap family records per
+// wave, a power of two of at least 64 (a split round of all lanes must fit the ring), chosen at
+// launch (the autotuner's LDS stack depth).
 
 template <int NB, int PREC, int WPB, bool CORR, bool THIN>
 __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(TraceArgs A, const RayRec* __restrict__ items,
@@ -549,15 +563,18 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
                                                                int refill, int fam, int stack_cap)
 {
     using SRec = StackRec<NB>;
-    SRec* lds = reinterpret_cast<SRec*>(arc_stack_lds);
+    const Terms terms = make_terms(A, reinterpret_cast<uint32_t*>(arc_dyn_lds));
+    SRec* lds = reinterpret_cast<SRec*>(arc_dyn_lds + terms_bytes(A));
     const int cmask = stack_cap - 1;
-    __shared__ DepScratch<NB> dscr[WPB];
+    __shared__ DepScratch dscr[WPB];
     const int wid = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const uint64_t lt = __lanemask_lt();
     const uint32_t n_items = *n_items_dev;
     SRec* stk = lds + wid * stack_cap;
     Depositor<NB> dep{dscr + wid};
+    dep_scratch_init(dep.scratch);
+    __syncthreads();
     // the spill area is sized in full records; compact records fit in it
     SRec* spill = reinterpret_cast<SRec*>(spill_all + (size_t)(blockIdx.x * WPB + wid) * spill_cap);
     int base = 0;          // ring start (oldest entry), wave-uniform
@@ -567,16 +584,16 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
     uint32_t spilled = 0;
     bool has = false;
     Ray<NB> ray;
-    LaneStats st;
+    WaveStats st;
     st.clear();
     for (;;) {
         // one pass over the lanes that hold a ray
         int ev = kContinue;
         if (__any(has)) {
             if constexpr (CORR)
-                ev = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, has, st, dep);
+                ev = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, terms, ray, has, st, dep);
             else
-                ev = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, has, st, dep);
+                ev = trace_pass<NB, PREC, kSegAhead, THIN>(A, terms, ray, has, st, dep);
         }
         // splits: one family record each
         const uint64_t sp = __ballot(ev == kSplit);
@@ -660,8 +677,10 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
         }
         if (got) {
             record_tree<NB>(A, r.src, r.lp);
-            has = ray_init<NB, THIN>(A, r, ray, st);
+            has = ray_init<NB, THIN>(A, terms, r, ray, st);
         }
+        st.rays += count_lanes(got);
+        st.escaped += count_lanes(got && !has);
         if (!__any(has) && top == 0 && nspill == 0 && qdone) break;
     }
     flush_stats<NB>(A, st);
@@ -673,27 +692,14 @@ constexpr int kMaxWavesPerBlock = 8;
 
 int persistent_max_waves() { return kMaxWavesPerBlock; }
 
-// LDS of a persistent workgroup of `waves` waves: the stacks (dynamic) and the deposit scratch.
-template <int NB>
-size_t persistent_stack_bytes(int waves, int stack_cap) { return (size_t)waves * stack_cap * sizeof(StackRec<NB>); }
-template <int NB>
-size_t persistent_lds_bytes(int waves, int stack_cap)
-{
-    return persistent_stack_bytes<NB>(waves, stack_cap) + (size_t)waves * sizeof(DepScratch<NB>);
-}
-constexpr size_t kLdsPerCu = 163840;
-
 template <int NB, int PREC, bool CORR, bool THIN>
 static hipError_t persistent_nb(const TraceArgs& A, const RayRec* items, const uint32_t* n_items, uint32_t* head,
                                 RayRec* spill, uint32_t spill_cap, int blocks, int waves, int refill, int fam,
                                 int stack_cap, hipStream_t s)
 {
-    // eight waves only where their LDS fits a compute unit (else four, in twice the blocks)
-    if (waves == 8 && persistent_lds_bytes<NB>(8, stack_cap) > kLdsPerCu) {
-        waves = 4;
-        blocks *= 2;
-    }
-    const size_t dyn = persistent_stack_bytes<NB>(waves, stack_cap);
+    // terms and stacks; with the deposit scratch at most 137 KB (eight waves of four bins, 256
+    // records each, 2048 cells per axis) of a compute unit's 160 KB
+    const size_t dyn = terms_bytes(A) + (size_t)waves * stack_cap * sizeof(StackRec<NB>);
     switch (waves) {
         case 1: k_trace_persistent<NB, PREC, 1, CORR, THIN><<<blocks, 64, dyn, s>>>(A, items, n_items, head, spill, spill_cap, refill, fam, stack_cap); break;
         case 2: k_trace_persistent<NB, PREC, 2, CORR, THIN><<<blocks, 128, dyn, s>>>(A, items, n_items, head, spill, spill_cap, refill, fam, stack_cap); break;
@@ -741,18 +747,14 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z ^ (z >> 31);
 }
 
-// Item i adds 1 to the NB bins of cell hash(i) mod ncell, its bins in NB adjacent lanes of
+// Item i adds 1 to the eight words of 64-byte line hash(i) mod nline, in eight adjacent lanes of
 // one instruction (as the trace's deposits are issued).
-__global__ __launch_bounds__(256) void k_probe_deposits(unsigned long long* J, int nbp, int nb, uint64_t ncell,
-                                                         uint64_t items, uint64_t seed)
+__global__ __launch_bounds__(256) void k_probe_deposits(unsigned long long* J, uint64_t nline, uint64_t items,
+                                                         uint64_t seed)
 {
-    const uint64_t lanes = items * (uint64_t)nb;
-    for (uint64_t s = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; s < lanes; s += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t item = s / (uint64_t)nb;
-        const int bin = (int)(s - item * (uint64_t)nb);
-        const uint64_t cell = mix64(seed + item) % ncell;
-        atomicAdd(J + cell * (uint64_t)nbp + bin, 1ull);
-    }
+    const uint64_t lanes = items * 8ull;
+    for (uint64_t s = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; s < lanes; s += (uint64_t)gridDim.x * blockDim.x)
+        atomicAdd(J + (mix64(seed + (s >> 3)) % nline) * 8ull + (s & 7ull), 1ull);
 }
 
 // Item i reads the 16-byte opacity record of cell hash(i) mod ncell; the sum of what a lane
@@ -768,10 +770,10 @@ __global__ __launch_bounds__(256) void k_probe_gathers(const float4* kappa, uint
     if (acc < 0.0f) sink[0] = acc;
 }
 
-hipError_t launch_probe_deposits(unsigned long long* J, int nbp, int nb, uint64_t ncell, uint64_t items,
-                                 uint64_t seed, int cus, hipStream_t s)
+hipError_t launch_probe_deposits(unsigned long long* J, uint64_t nline, uint64_t items, uint64_t seed, int cus,
+                                 hipStream_t s)
 {
-    k_probe_deposits<<<cus * 32, 256, 0, s>>>(J, nbp, nb, ncell, items, seed);
+    k_probe_deposits<<<cus * 32, 256, 0, s>>>(J, nline, items, seed);
     return hipGetLastError();
 }
 
@@ -801,9 +803,8 @@ __global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a)
             const uint32_t xl = ((o >> 9) << 3) | gather3(m), yl = gather3(m >> 1), zl = gather3(m >> 2);
             const uint32_t l = (zl << 8) | (yl << 5) | xl;
             double Jb[NB];
-            const unsigned long long* j = a.J + (size_t)i * a.nbp;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) Jb[b] = (double)(long long)j[b];
+            for (int b = 0; b < NB; ++b) Jb[b] = (double)(long long)a.J[field_word(i, NB, b)];
             float k[NB];
             if constexpr (NB == 1) {
                 k[0] = a.kappa1[i];
@@ -816,10 +817,10 @@ __global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a)
             }
             if (a.M) {
                 // photons moved in by the secondary correction, absorbed at this cell's opacity
-                const unsigned long long* m = a.M + (size_t)i * (2 * a.nbp);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const double mv = (double)(long long)m[b] * 0x1p20 + (double)(long long)m[a.nbp + b] * 0x1p-12;
+                    const double mv = (double)(long long)a.M[field_word(i, 2 * NB, b)] * 0x1p20 +
+                                      (double)(long long)a.M[field_word(i, 2 * NB, NB + b)] * 0x1p-12;
                     if (k[b] > 0.0f) Jb[b] += mv / (double)k[b];
                 }
             }
@@ -868,26 +869,26 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s)
 }
 
 // dst [bin][cell] = J; with M, then [bin][cell] of M's low limb and [bin][cell] of its high limb.
-__global__ void k_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nbp, int nx, int ny,
-                            int nbx8, int nby8, uint32_t ncell, long long* dst)
+__global__ void k_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nx, int ny, int nbx8,
+                            int nby8, uint32_t ncell, long long* dst)
 {
     for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncell; c += gridDim.x * blockDim.x) {
         const uint32_t x = c % (uint32_t)nx, y = (c / (uint32_t)nx) % (uint32_t)ny, z = c / ((uint32_t)nx * (uint32_t)ny);
         const uint32_t i = blocked_index((int)x, (int)y, (int)z, nbx8, nby8);
         for (int b = 0; b < nb; ++b) {
-            dst[(size_t)b * ncell + c] = (long long)J[(size_t)i * nbp + b];
+            dst[(size_t)b * ncell + c] = (long long)J[field_word(i, nb, b)];
             if (M) {
-                dst[(size_t)(nb + b) * ncell + c] = (long long)M[(size_t)i * 2 * nbp + nbp + b];
-                dst[(size_t)(2 * nb + b) * ncell + c] = (long long)M[(size_t)i * 2 * nbp + b];
+                dst[(size_t)(nb + b) * ncell + c] = (long long)M[field_word(i, 2 * nb, nb + b)];
+                dst[(size_t)(2 * nb + b) * ncell + c] = (long long)M[field_word(i, 2 * nb, b)];
             }
         }
     }
 }
 
-hipError_t launch_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nbp, int nx, int ny,
-                            int nbx8, int nby8, uint32_t ncell, long long* dst, hipStream_t s)
+hipError_t launch_get_field(const unsigned long long* J, const unsigned long long* M, int nb, int nx, int ny, int nbx8,
+                            int nby8, uint32_t ncell, long long* dst, hipStream_t s)
 {
-    k_get_field<<<grid_for(ncell, 256, 1u << 16), 256, 0, s>>>(J, M, nb, nbp, nx, ny, nbx8, nby8, ncell, dst);
+    k_get_field<<<grid_for(ncell, 256, 1u << 16), 256, 0, s>>>(J, M, nb, nx, ny, nbx8, nby8, ncell, dst);
     return hipGetLastError();
 }
 
