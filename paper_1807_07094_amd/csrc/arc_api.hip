@@ -32,12 +32,11 @@ struct arc_ctx {
     size_t M_bytes = 0;
     // source table
     SourceRec* src = nullptr;
-    double* src_pos = nullptr;
-    double* src_ndot = nullptr;
-    uint32_t* src_order = nullptr;
-    double* src_rthin = nullptr;       // optically thin radius per source (section 2.6)
+    double* src_in = nullptr;          // the call's sources as uploaded: SourceUpload
     uint32_t* r_out = nullptr;         // measured R_tau<0.1 per source (FP32 bits)
     int src_cap = 0;
+    double* src_stage = nullptr;       // the same on the host, pinned
+    uint32_t* r_stage = nullptr;       // r_out on the host, pinned
     // HEALPix centres, levels 0..dirs_levels-1
     float4* dirs = nullptr;
     int dirs_levels = 0;
@@ -49,10 +48,8 @@ struct arc_ctx {
     RayRec* spill = nullptr;
     size_t spill_entries = 0;
     // small device scalars
-    unsigned long long* counters = nullptr;  // kNumCounters
-    double* acc = nullptr;                    // [0..3] escaped per bin, [4] absorbed
-    uint32_t* u32 = nullptr;                  // [0] n_out, [1] queue head
-    int* errflag = nullptr;
+    RunBlock* run = nullptr;
+    RunBlock* run_host = nullptr;             // pinned
     unsigned long long* chem_stats = nullptr;  // [0..3] chemistry statistics, [4] work counter
     unsigned long long* reject = nullptr;     // learned step: cells for the plain solver, a bit each
     size_t reject_cap = 0;                    // words
@@ -78,6 +75,13 @@ struct arc_ctx {
         arc_tune_result shape;
     };
     std::vector<Tuned> tuned;
+};
+
+// A call's sources in one upload of n entries: positions, photon rates, thin radii, and the
+// sources by decreasing photon rate (work-queue order).
+struct SourceUpload {
+    size_t pos, ndot, rthin, order, bytes;  // offsets [doubles], size
+    explicit SourceUpload(size_t n) : pos(0), ndot(3 * n), rthin(4 * n), order(5 * n), bytes(44 * n) {}
 };
 
 // Scratch of the allocation-free entry point (arc_rt_timestep_noalloc): a file-scope device
@@ -255,10 +259,8 @@ arc_status arc_create(int32_t device, arc_ctx** out)
         delete c;
         return ARC_E_DEVICE;
     }
-    bool ok = hipMalloc((void**)&c->counters, kNumCounters * sizeof(unsigned long long)) == hipSuccess &&
-              hipMalloc((void**)&c->acc, 8 * sizeof(double)) == hipSuccess &&
-              hipMalloc((void**)&c->u32, 4 * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc((void**)&c->errflag, sizeof(int)) == hipSuccess &&
+    bool ok = hipMalloc((void**)&c->run, sizeof(RunBlock)) == hipSuccess &&
+              hipHostMalloc((void**)&c->run_host, sizeof(RunBlock), hipHostMallocDefault) == hipSuccess &&
               hipMalloc((void**)&c->chem_stats, 5 * sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc((void**)&c->sums, 2 * sizeof(unsigned long long)) == hipSuccess;
     for (int i = 0; i < 6 && ok; ++i) ok = hipEventCreate(&c->ev[i]) == hipSuccess;
@@ -274,11 +276,13 @@ void arc_destroy(arc_ctx* c)
 {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    void* bufs[] = {c->kappa, c->J, c->M, c->src, c->src_pos, c->src_ndot, c->src_order, c->src_rthin, c->r_out,
-                    c->dirs, c->rays[0], c->rays[1], c->spill, c->counters, c->acc, c->u32, c->errflag,
-                    c->chem_stats, c->reject};
+    void* bufs[] = {c->kappa, c->J, c->M, c->src, c->src_in, c->r_out, c->dirs, c->rays[0], c->rays[1], c->spill,
+                    c->run, c->chem_stats, c->reject};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
+    void* pinned[] = {c->src_stage, c->r_stage, c->run_host};
+    for (void* p : pinned)
+        if (p) (void)hipHostFree(p);
     for (int i = 0; i < 6; ++i)
         if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
     for (int i = 0; i < 4; ++i)
@@ -305,7 +309,7 @@ struct TracePlan {
     double uj[kMaxBins];
     double sum_ndot;
     int nsrc;
-    double src_scale[kMaxBins];  // frac_b / (12 u_J,b)
+    BeginArgs ba;
     OpacityArgs oa;
     TraceArgs A;
     FinalizeArgs fa;
@@ -322,8 +326,7 @@ struct TracePlan {
     RayRec* rays0;
     RayRec* rays1;
     RayRec* spill;
-    uint32_t* u32;
-    const uint32_t* order;  // sources by decreasing photon rate (work-queue order)
+    RunBlock* run;
 };
 
 // Validation, fixed-point units, buffers and launch arguments shared by both schedules.
@@ -413,7 +416,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         } else {
             P.uj[k] = need > 0 ? need : 1.0;
         }
-        P.src_scale[k] = b->frac[k] / (12.0 * P.uj[k]);
+        P.ba.scale[k] = b->frac[k] / (12.0 * P.uj[k]);
     }
 
     // Buffers.
@@ -424,23 +427,42 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         if (p->correction == ARC_CORR_CONSERVING)
             HIP_TRY(c, grow(&c->M, &c->M_bytes, nblocked * 2 * nb * sizeof(unsigned long long)));
         if (s->n > c->src_cap) {
-            void* old[] = {c->src, c->src_pos, c->src_ndot, c->src_order, c->src_rthin, c->r_out};
+            void* old[] = {c->src, c->src_in, c->r_out};
+            void* old_pinned[] = {c->src_stage, c->r_stage};
+            c->src = nullptr;
+            c->src_in = c->src_stage = nullptr;
+            c->r_out = c->r_stage = nullptr;
+            c->src_cap = 0;
             for (void* q : old)
                 if (q) HIP_TRY(c, hipFree(q));
-            c->src = nullptr;
-            c->src_pos = c->src_ndot = c->src_rthin = nullptr;
-            c->src_order = c->r_out = nullptr;
-            c->src_cap = 0;
+            for (void* q : old_pinned)
+                if (q) HIP_TRY(c, hipHostFree(q));
+            const SourceUpload up((size_t)s->n);
             HIP_TRY(c, hipMalloc((void**)&c->src, s->n * sizeof(SourceRec)));
-            HIP_TRY(c, hipMalloc((void**)&c->src_pos, s->n * 3 * sizeof(double)));
-            HIP_TRY(c, hipMalloc((void**)&c->src_ndot, s->n * sizeof(double)));
-            HIP_TRY(c, hipMalloc((void**)&c->src_order, s->n * sizeof(uint32_t)));
-            HIP_TRY(c, hipMalloc((void**)&c->src_rthin, s->n * sizeof(double)));
+            HIP_TRY(c, hipMalloc((void**)&c->src_in, up.bytes));
             HIP_TRY(c, hipMalloc((void**)&c->r_out, s->n * sizeof(uint32_t)));
+            HIP_TRY(c, hipHostMalloc((void**)&c->src_stage, up.bytes, hipHostMallocDefault));
+            HIP_TRY(c, hipHostMalloc((void**)&c->r_stage, s->n * sizeof(uint32_t), hipHostMallocDefault));
             c->src_cap = s->n;
         }
     }
     if ((rc = ensure_dirs(c, lmax + 1, st)) != ARC_OK) return rc;
+
+    P.run = c->run;
+    BeginArgs& ba = P.ba;
+    const SourceUpload up((size_t)s->n);
+    ba.run = c->run;
+    ba.nb = nb;
+    ba.nsrc = s->n;
+    ba.level0 = p->level0;
+    if (s->n > 0) {
+        ba.pos = c->src_in + up.pos;
+        ba.ndot = c->src_in + up.ndot;
+        ba.r_thin = thin && s->r_thin ? c->src_in + up.rthin : nullptr;
+        ba.order = reinterpret_cast<const uint32_t*>(c->src_in + up.order);
+    }
+    ba.src = c->src;
+    ba.r_out = thin ? c->r_out : nullptr;
 
     OpacityArgs& oa = P.oa;
     oa.nb = nb;
@@ -463,7 +485,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     oa.kappa4 = nb == 1 ? nullptr : (float4*)c->kappa;
     oa.J = c->J;
     oa.M = p->correction == ARC_CORR_CONSERVING ? c->M : nullptr;
-    oa.errflag = c->errflag;
+    oa.errflag = &c->run->errflag;
 
     TraceArgs& A = P.A;
     A.nx = g->nx;
@@ -483,9 +505,9 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     A.src = c->src;
     A.dirs = c->dirs;
     for (int l = 0; l < kMaxLevels; ++l) A.dir_off[l] = l < c->dirs_levels ? c->dir_off[l] : 0;
-    A.esc = c->acc;
-    A.counters = c->counters;
+    A.slots = c->run->before;
     A.tree = (unsigned long long*)p->tree_out;
+    A.tree_count = &c->run->tree_count;
     A.tree_cap = p->tree_out ? p->tree_cap : 0;
     A.corr = p->correction;
     A.M = oa.M;
@@ -519,7 +541,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     fa.kappa4 = oa.kappa4;
     fa.gamma = out->gamma;
     fa.heat = out->heat;
-    fa.absorbed = c->acc + 4;
+    fa.slots = c->run->before;
 
     if (thin) {
         ThinFillArgs& tf = P.tf;
@@ -535,9 +557,9 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         tf.nz = g->nz;
         tf.nbx8 = nbx8;
         tf.nby8 = nby8;
-        tf.pos = c->src_pos;
-        tf.ndot = c->src_ndot;
-        tf.r_thin = c->src_rthin;
+        tf.pos = ba.pos;
+        tf.ndot = ba.ndot;
+        tf.r_thin = ba.r_thin;
         for (int k = 0; k < nb; ++k) {
             tf.coef[k] = b->frac[k] / (4.0 * M_PI * P.uj[k]);
             tf.uj[k] = P.uj[k];
@@ -545,7 +567,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         tf.J = c->J;
         tf.kappa1 = oa.kappa1;
         tf.kappa4 = oa.kappa4;
-        tf.absorbed_thin = c->acc + 5;
+        tf.slots = c->run->before;
     }
     return ARC_OK;
 }
@@ -622,58 +644,39 @@ arc_status shape_batched(arc_ctx* c, TracePlan& P, int waves, int blocks, int re
     P.rays0 = c->rays[0];
     P.rays1 = c->rays[1];
     P.spill = c->spill;
-    P.u32 = c->u32;
-    P.order = c->src_order;
+    P.ba.n_roots = (uint32_t)n_roots;
+    P.ba.roots = P.nsrc > 0 ? c->rays[0] : nullptr;
     return ARC_OK;
 }
 
-// Stage 0: counters, opacity (section 2.2 cross sections times densities) and the
-// source table.
-hipError_t enqueue_common(arc_ctx* c, const TracePlan& P, hipStream_t st)
+// Stage 0: counters, source table and root rays, opacity (section 2.2 cross sections times
+// densities).
+hipError_t enqueue_common(const TracePlan& P, hipStream_t st)
 {
     hipError_t e;
-    if ((e = launch_zero_u64(c->counters, kNumCounters, st)) != hipSuccess) return e;
-    if ((e = launch_zero_f64(c->acc, 8, st)) != hipSuccess) return e;
-    if ((e = launch_set_u32((uint32_t*)c->errflag, 0u, st)) != hipSuccess) return e;
+    if ((e = launch_begin(P.ba, st)) != hipSuccess) return e;
     if ((e = launch_opacity(P.oa, st)) != hipSuccess) return e;
-    if (P.nsrc > 0 && (e = launch_sources(P.nsrc, c->src_pos, c->src_ndot, P.thin ? c->src_rthin : nullptr,
-                                          P.src_scale, P.nb, c->src, st)) != hipSuccess)
-        return e;
-    if (P.thin) {
-        // no ray measured yet: R_tau<0.1 = +inf
-        if ((e = launch_fill_u32(c->r_out, (uint32_t)P.nsrc, 0x7F800000u, st)) != hipSuccess) return e;
-        if ((e = launch_thin_fill(P.tf, st)) != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return P.thin ? launch_thin_fill(P.tf, st) : hipSuccess;
 }
 
-// Stage 1 (batched): the root rays of every source and the levels traced level by level
-// before the persistent launch.
+// Stage 1 (batched): the levels traced level by level before the persistent launch.
 hipError_t enqueue_levels(const TracePlan& P, hipStream_t st)
 {
-    hipError_t e;
     if (P.nsrc == 0) return hipSuccess;
-    if ((e = launch_seed_roots(0, (uint32_t)P.nsrc, P.A.level0, P.order, P.rays0, st)) != hipSuccess) return e;
-    uint32_t* cnt = P.u32 + 2;  // [2], [3]: ray counts of consecutive levels
-    if ((e = launch_set_u32(cnt, (uint32_t)P.n_roots, st)) != hipSuccess) return e;
     size_t bound = (size_t)P.n_roots;
     int cur = 0;
     RayRec* r[2] = {P.rays0, P.rays1};
     for (int l = P.A.level0; l < P.litem; ++l) {
-        uint32_t* cin = cnt + ((l - P.A.level0) & 1);
-        uint32_t* cout = cnt + ((l - P.A.level0 + 1) & 1);
-        if ((e = launch_set_u32(cout, 0u, st)) != hipSuccess) return e;
         const uint32_t out_cap = (uint32_t)std::min<size_t>(P.cap[1 - cur], 0xFFFFFFF0u);
         // the last level leaves family records: the work items of the persistent launch
         const int fam_out = l + 1 == P.litem ? 1 : 0;
-        if ((e = launch_trace_rays(P.A, P.precision, r[cur], cin, (uint32_t)bound, r[1 - cur], cout, out_cap, fam_out,
-                                   st)) != hipSuccess)
-            return e;
+        const hipError_t e = launch_trace_rays(P.A, P.precision, r[cur], P.run->level_rays + l, (uint32_t)bound,
+                                               r[1 - cur], P.run->level_rays + l + 1, out_cap, fam_out, st);
+        if (e != hipSuccess) return e;
         bound *= 4;
         cur = 1 - cur;
     }
-    if ((e = launch_snapshot_counters(P.A.counters, st)) != hipSuccess) return e;
-    return launch_set_u32(P.u32 + 1, 0u, st);
+    return hipSuccess;
 }
 
 // Stage 2: the persistent launch over the work items of level litem.
@@ -683,8 +686,10 @@ hipError_t enqueue_persistent(const TracePlan& P, hipStream_t st)
     const int cur = (P.litem - P.A.level0) & 1;
     // above the first level the work items are the family records of the level before
     const int fam = P.litem > P.A.level0 ? 1 : 0;
-    return launch_trace_persistent(P.A, P.precision, cur ? P.rays1 : P.rays0, P.u32 + 2 + cur, P.u32 + 1, P.spill,
-                                   P.spill_cap, P.blocks, P.waves, P.refill, fam, P.stack, st);
+    TraceArgs A = P.A;
+    A.slots = P.run->persistent;
+    return launch_trace_persistent(A, P.precision, cur ? P.rays1 : P.rays0, P.run->level_rays + P.litem, &P.run->head,
+                                   P.spill, P.spill_cap, P.blocks, P.waves, P.refill, fam, P.stack, st);
 }
 
 // Stage 3: rates (eq:ion per absorber, section 2.8 heating) and the absorbed ledger.
@@ -695,11 +700,12 @@ hipError_t enqueue_rates(const TracePlan& P, hipStream_t st) { return launch_fin
 arc_status run_plain(arc_ctx* c, const TracePlan& P, hipStream_t st)
 {
     const uint32_t npix0 = 12u << (2 * P.A.level0);
+    uint32_t* n_out = c->run->level_rays + (kMaxLevels - 1);
     for (int si = 0; si < P.nsrc; ++si) {
         size_t n = npix0;
         for (int i = 0; i < 2; ++i)
             if (4 * n > c->rcap[i]) HIP_TRY(c, grow_rays(c, i, 4 * n));
-        HIP_TRY(c, launch_seed_roots((uint32_t)si, 1, P.A.level0, nullptr, c->rays[0], st));
+        HIP_TRY(c, launch_seed_roots((uint32_t)si, P.A.level0, c->rays[0], st));
         int cur = 0;
         while (n > 0) {
             const size_t need = 4 * n;
@@ -719,11 +725,11 @@ arc_status run_plain(arc_ctx* c, const TracePlan& P, hipStream_t st)
                 cur = 0;
                 c->rcap[0] = c->rcap[1] = need;
             }
-            HIP_TRY(c, launch_set_u32(c->u32, 0u, st));
-            HIP_TRY(c, launch_trace_rays(P.A, P.precision, c->rays[cur], nullptr, (uint32_t)n, c->rays[1 - cur], c->u32,
+            HIP_TRY(c, launch_set_u32(n_out, 0u, st));
+            HIP_TRY(c, launch_trace_rays(P.A, P.precision, c->rays[cur], nullptr, (uint32_t)n, c->rays[1 - cur], n_out,
                                          (uint32_t)std::min<size_t>(c->rcap[1 - cur], 0xFFFFFFF0u), 0, st));
             uint32_t nn = 0;
-            HIP_TRY(c, hipMemcpyAsync(&nn, c->u32, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+            HIP_TRY(c, hipMemcpyAsync(&nn, n_out, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
             HIP_TRY(c, hipStreamSynchronize(st));
             n = nn;
             cur = 1 - cur;
@@ -749,7 +755,7 @@ arc_status ensure_graphs(arc_ctx* c, const TracePlan& P)
     for (int i = 0; i < 4; ++i) {
         HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
         hipStream_t cs = c->cap_stream;
-        const hipError_t e = i == 0   ? enqueue_common(c, P, cs)
+        const hipError_t e = i == 0   ? enqueue_common(P, cs)
                              : i == 1 ? enqueue_levels(P, cs)
                              : i == 2 ? enqueue_persistent(P, cs)
                                       : enqueue_rates(P, cs);
@@ -777,25 +783,21 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
                      hipStream_t st, arc_ledger* ledger)
 {
     const bool batched = schedule != ARC_SCHED_PLAIN;
-    std::vector<uint32_t> order;
     if (s->n > 0) {
-        HIP_TRY(c, hipMemcpyAsync(c->src_pos, s->pos, s->n * 3 * sizeof(double), hipMemcpyHostToDevice, st));
-        HIP_TRY(c, hipMemcpyAsync(c->src_ndot, s->ndot, s->n * sizeof(double), hipMemcpyHostToDevice, st));
-        if (P.thin) {
-            if (s->r_thin)
-                HIP_TRY(c, hipMemcpyAsync(c->src_rthin, s->r_thin, s->n * sizeof(double), hipMemcpyHostToDevice, st));
-            else
-                HIP_TRY(c, launch_zero_f64(c->src_rthin, (size_t)s->n, st));
-        }
+        const size_t n = (size_t)s->n;
+        const SourceUpload up(n);
+        std::memcpy(c->src_stage + up.pos, s->pos, 3 * n * sizeof(double));
+        std::memcpy(c->src_stage + up.ndot, s->ndot, n * sizeof(double));
+        if (s->r_thin) std::memcpy(c->src_stage + up.rthin, s->r_thin, n * sizeof(double));
         if (batched) {
             // the work queue starts with the brightest sources, whose rays travel furthest, so
             // that the longest subtrees are not the last ones taken (the field does not depend
             // on the order: integer sums)
-            order.resize(s->n);
-            for (int i = 0; i < s->n; ++i) order[i] = (uint32_t)i;
-            std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b2) { return s->ndot[a] > s->ndot[b2]; });
-            HIP_TRY(c, hipMemcpyAsync(c->src_order, order.data(), s->n * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+            uint32_t* order = reinterpret_cast<uint32_t*>(c->src_stage + up.order);
+            for (size_t i = 0; i < n; ++i) order[i] = (uint32_t)i;
+            std::stable_sort(order, order + n, [&](uint32_t a, uint32_t b2) { return s->ndot[a] > s->ndot[b2]; });
         }
+        HIP_TRY(c, hipMemcpyAsync(c->src_in, c->src_stage, up.bytes, hipMemcpyHostToDevice, st));
     }
     c->timed_kernel = false;
     if (batched && graph) {
@@ -814,7 +816,7 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
         c->timed_kernel = P.nsrc > 0;
     } else {
         HIP_TRY(c, hipEventRecord(c->ev[0], st));
-        HIP_TRY(c, enqueue_common(c, P, st));
+        HIP_TRY(c, enqueue_common(P, st));
         // the first levels of the batched schedule belong to the trace time
         HIP_TRY(c, hipEventRecord(c->ev[1], st));
         if (batched) {
@@ -825,27 +827,35 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
             c->timed_kernel = P.nsrc > 0;
         } else {
             arc_status rc = run_plain(c, P, st);
-            if (rc != ARC_OK) return rc;
+            if (rc != ARC_OK) {
+                (void)hipStreamSynchronize(st);  // the upload has left the pinned buffer
+                return rc;
+            }
         }
         HIP_TRY(c, hipEventRecord(c->ev[2], st));
         HIP_TRY(c, enqueue_rates(P, st));
         HIP_TRY(c, hipEventRecord(c->ev[3], st));
     }
 
-    unsigned long long cnt[kNumCounters];
-    double acc[8];
-    int errflag = 0;
-    std::vector<uint32_t> rbits(P.thin && s->r_thin_out ? (size_t)s->n : 0);
-    HIP_TRY(c, hipMemcpyAsync(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(acc, c->acc, sizeof acc, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(&errflag, c->errflag, sizeof errflag, hipMemcpyDeviceToHost, st));
-    if (!rbits.empty())
-        HIP_TRY(c, hipMemcpyAsync(rbits.data(), c->r_out, rbits.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    const bool want_r = P.thin && s->r_thin_out && s->n > 0;
+    HIP_TRY(c, hipMemcpyAsync(c->run_host, c->run, sizeof(RunBlock), hipMemcpyDeviceToHost, st));
+    if (want_r)
+        HIP_TRY(c, hipMemcpyAsync(c->r_stage, c->r_out, (size_t)s->n * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
-    for (size_t i = 0; i < rbits.size(); ++i) {
+    for (int i = 0; want_r && i < s->n; ++i) {
         float r;
-        std::memcpy(&r, &rbits[i], sizeof r);
+        std::memcpy(&r, &c->r_stage[i], sizeof r);
         s->r_thin_out[i] = (double)r;
+    }
+    const RunBlock& run = *c->run_host;
+    unsigned long long cnt[kNumCounters] = {0}, per[kNumCounters] = {0};
+    double acc[8] = {0};
+    for (int i = 0; i < kCounterSlots; ++i) {
+        for (int k = 0; k < kNumCounters; ++k) {
+            cnt[k] += run.before[i].n[k] + run.persistent[i].n[k];
+            per[k] += run.persistent[i].n[k];
+        }
+        for (int k = 0; k < 8; ++k) acc[k] += run.before[i].photons[k] + run.persistent[i].photons[k];
     }
 
     c->last_nb = P.nb;
@@ -856,16 +866,16 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
     c->last_nby8 = P.nby8;
     c->last_moved = P.A.M != nullptr;
     c->have_field = true;
-    if (errflag) return fail(c, ARC_E_RANGE, "grid values out of range (n_h <= 0, fraction outside [0,1] or non-finite)");
+    if (run.errflag) return fail(c, ARC_E_RANGE, "grid values out of range (n_h <= 0, fraction outside [0,1] or non-finite)");
     if (cnt[kQueueOverflow]) return fail(c, ARC_E_QUEUE, "ray queue capacity exceeded (%llu rays dropped)", cnt[kQueueOverflow]);
     if (ledger) {
         std::memset(ledger, 0, sizeof *ledger);
         ledger->emitted = P.sum_ndot * dt;
         double esc = 0;
-        for (int k = 0; k < P.nb; ++k) esc += acc[k] * P.uj[k];
+        for (int k = 0; k < P.nb; ++k) esc += acc[kPhotonsEscaped + k] * P.uj[k];
         ledger->escaped = esc * dt;
-        ledger->absorbed = acc[4] * dt;
-        ledger->absorbed_thin = acc[5] * dt;
+        ledger->absorbed = acc[kPhotonsAbsorbed] * dt;
+        ledger->absorbed_thin = acc[kPhotonsThin] * dt;
         ledger->crossings = cnt[kCrossings];
         ledger->rays = cnt[kRays];
         ledger->splits = cnt[kSplits];
@@ -874,10 +884,10 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
         ledger->spills = cnt[kSpills];
         ledger->deposits = cnt[kDeposits];
         if (c->timed_kernel) {
-            ledger->kernel_crossings = cnt[kCrossings] - cnt[kCrossingsPre];
-            ledger->kernel_deposits = cnt[kDeposits] - cnt[kDepositsPre];
+            ledger->kernel_crossings = per[kCrossings];
+            ledger->kernel_deposits = per[kDeposits];
         }
-        ledger->tree_count = (int64_t)cnt[kTreeCount];
+        ledger->tree_count = (int64_t)run.tree_count;
         for (int k = 0; k < kMaxBins; ++k) ledger->u_j[k] = k < P.nb ? P.uj[k] : 0.0;
         float ms = 0;
         HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]));
@@ -1121,7 +1131,7 @@ arc_status arc_probe_requests(arc_ctx* c, int64_t items, int64_t cells, uint64_t
         HIP_TRY(c, hipEventRecord(c->ev[0], st));
         HIP_TRY(c, launch_probe_deposits(c->J, nline, (uint64_t)items, seed + rep, c->cus, st));
         HIP_TRY(c, hipEventRecord(c->ev[1], st));
-        HIP_TRY(c, launch_probe_gathers((const float4*)c->kappa, ncell, (uint64_t)items, seed + rep, (float*)c->acc,
+        HIP_TRY(c, launch_probe_gathers((const float4*)c->kappa, ncell, (uint64_t)items, seed + rep, (float*)c->run,
                                         c->cus, st));
         HIP_TRY(c, hipEventRecord(c->ev[2], st));
         HIP_TRY(c, hipEventSynchronize(c->ev[2]));

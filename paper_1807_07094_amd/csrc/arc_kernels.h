@@ -34,7 +34,21 @@ struct FinalizeArgs {
     const float* kappa1;
     const float4* kappa4;
     float *gamma, *heat;       // [3][ncell]
-    double* absorbed;          // sum_c sum_b u_J J kappa
+    CounterSlot* slots;        // photons absorbed: sum_c sum_b u_J J kappa
+};
+
+// Set-up of a call. Root rays (batched) are those of the sources order[0 .. nsrc), each source's
+// contiguous in pixel order; none without `roots`.
+struct BeginArgs {
+    RunBlock* run;
+    int nb, nsrc, level0;
+    uint32_t n_roots;
+    const double *pos, *ndot, *r_thin;  // r_thin: null where no source has a thin sphere
+    double scale[kMaxBins];    // frac_b / (12 u_J,b)
+    SourceRec* src;
+    uint32_t* r_out;           // measured thin radii, or null
+    const uint32_t* order;
+    RayRec* roots;
 };
 
 // Section 2.6 fill of the optically thin spheres.
@@ -47,7 +61,7 @@ struct ThinFillArgs {
     unsigned long long* J;
     const float* kappa1;
     const float4* kappa4;
-    double* absorbed_thin;     // sum of the fill's deposits times u_J kappa
+    CounterSlot* slots;        // photons of the fill: its deposits times u_J kappa
 };
 
 struct ChemArgs {
@@ -66,21 +80,14 @@ struct ChemArgs {
 };
 
 hipError_t launch_zero_u64(unsigned long long* p, size_t n, hipStream_t s);
-hipError_t launch_zero_f64(double* p, size_t n, hipStream_t s);
 hipError_t launch_set_u32(uint32_t* p, uint32_t v, hipStream_t s);
-hipError_t launch_snapshot_counters(unsigned long long* counters, hipStream_t s);
 // out[0] = sum J[i], out[1] = sum J[i] (2i + 1), both mod 2^64; out must be zeroed first.
 hipError_t launch_field_checksum(const unsigned long long* J, size_t n, unsigned long long* out, hipStream_t s);
 hipError_t launch_opacity(const OpacityArgs& a, hipStream_t s);
 hipError_t launch_healpix(int level, float4* out, hipStream_t s);
-hipError_t launch_sources(int n, const double* pos, const double* ndot, const double* r_thin,
-                          const double* frac_over_12uj, int nb, SourceRec* out, hipStream_t s);
+hipError_t launch_begin(const BeginArgs& a, hipStream_t s);
 hipError_t launch_thin_fill(const ThinFillArgs& a, hipStream_t s);
-hipError_t launch_fill_u32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s);
-// Root rays of sources first_src .. first_src + nsrc - 1, or of order[0 .. nsrc) if order
-// is given (source k's rays are contiguous, in pixel order).
-hipError_t launch_seed_roots(uint32_t first_src, uint32_t nsrc, int level0, const uint32_t* order, RayRec* out,
-                             hipStream_t s);
+hipError_t launch_seed_roots(uint32_t src, int level0, RayRec* out, hipStream_t s);
 // n_in_dev (optional) holds the ray count on the device; n_in bounds it and sizes the grid.
 // fam_out: a split ray writes one family record (its own id and depth) instead of its four
 // children, for the persistent launch.

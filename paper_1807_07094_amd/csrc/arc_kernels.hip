@@ -2,8 +2,9 @@
 //
 //   k_opacity          optical depth per cell length for every bin, field zeroing, input checks
 //   k_healpix          FP32 HEALPix pixel centres of one level (computed in FP64)
-//   k_sources          per-source table (lattice position, root-ray photon rate)
-//   k_seed_roots       root rays of a range of sources (or of sources in a given order)
+//   k_begin            cleared counters, per-source table (lattice position, root-ray photon rate),
+//                      root rays of every source in the order of the work queue
+//   k_seed_roots       root rays of one source (the per-level schedule)
 //   k_trace_rays       one ray per lane, rays of one HEALPix level (the per-level schedule)
 //   k_trace_persistent every source in one launch: device work queue, wave-ballot refill,
 //                      per-wave LDS ray stack with a private spill area in memory
@@ -13,6 +14,9 @@
 #include <hip/hip_runtime.h>
 
 #include <math.h>
+#include <stddef.h>
+
+#include <algorithm>
 
 #include "arc_kernels.h"
 
@@ -37,12 +41,6 @@ __global__ void k_zero_u64(unsigned long long* p, size_t n)
 {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0ull;
-}
-
-__global__ void k_zero_f64(double* p, size_t n)
-{
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
 }
 
 hipError_t launch_zero_u64(unsigned long long* p, size_t n, hipStream_t s)
@@ -76,28 +74,9 @@ hipError_t launch_field_checksum(const unsigned long long* J, size_t n, unsigned
 
 __global__ void k_set_u32(uint32_t* p, uint32_t v) { *p = v; }
 
-// Counters of the work done before the persistent launch (its own work is the difference).
-__global__ void k_snapshot_counters(unsigned long long* c)
-{
-    c[kCrossingsPre] = c[kCrossings];
-    c[kDepositsPre] = c[kDeposits];
-}
-
-hipError_t launch_snapshot_counters(unsigned long long* counters, hipStream_t s)
-{
-    k_snapshot_counters<<<1, 1, 0, s>>>(counters);
-    return hipGetLastError();
-}
-
 hipError_t launch_set_u32(uint32_t* p, uint32_t v, hipStream_t s)
 {
     k_set_u32<<<1, 1, 0, s>>>(p, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_f64(double* p, size_t n, hipStream_t s)
-{
-    k_zero_f64<<<grid_for(n, 256), 256, 0, s>>>(p, n);
     return hipGetLastError();
 }
 
@@ -286,31 +265,48 @@ hipError_t launch_healpix(int level, float4* out, hipStream_t s)
 // Source table and root rays (section 2.1 iii a: rays start at radius 0 with zero
 // optical depth; section 2.4: each ray carries an equal share of the source's photons).
 // -------------------------------------------------------------------------------------
-struct ScaleArg {
-    double f[kMaxBins];
-};
-
-__global__ void k_sources(int n, const double* pos, const double* ndot, const double* r_thin, ScaleArg sc, int nb,
-                          SourceRec* out)
+__device__ __forceinline__ RayRec root_ray(uint32_t src, int level0, uint32_t pix)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    SourceRec r;
-    r.x = (float)pos[3 * i];
-    r.y = (float)pos[3 * i + 1];
-    r.z = (float)pos[3 * i + 2];
-    r.r_thin = r_thin ? (float)r_thin[i] : 0.0f;
+    RayRec r;
+    r.src = src;
+    r.lp = ((uint32_t)level0 << kLevelShift) | pix;
+    r.pad0 = r.pad1 = 0;
 #pragma unroll
-    for (int b = 0; b < kMaxBins; ++b) r.scale[b] = b < nb ? (float)(ndot[i] * sc.f[b]) : 0.0f;
-    out[i] = r;
+    for (int b = 0; b < 4; ++b) r.tau[b] = r.taulo[b] = 0.0f;
+    return r;
 }
 
-hipError_t launch_sources(int n, const double* pos, const double* ndot, const double* r_thin,
-                          const double* frac_over_12uj, int nb, SourceRec* out, hipStream_t s)
+// Everything a call needs before its first grid pass, in one launch: the cleared run block, the
+// source table, the unmeasured thin radii (+inf) and, batched, the root rays of every source in
+// the order of the work queue.
+__global__ __launch_bounds__(256) void k_begin(BeginArgs a)
 {
-    ScaleArg sc;
-    for (int b = 0; b < kMaxBins; ++b) sc.f[b] = b < nb ? frac_over_12uj[b] : 0.0;
-    if (n > 0) k_sources<<<grid_for(n, 256), 256, 0, s>>>(n, pos, ndot, r_thin, sc, nb, out);
+    const size_t t0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    uint32_t* words = reinterpret_cast<uint32_t*>(a.run);
+    const size_t seeded = offsetof(RunBlock, level_rays) / 4 + (size_t)a.level0;
+    for (size_t i = t0; i < sizeof(RunBlock) / 4; i += stride) words[i] = i == seeded && a.roots ? a.n_roots : 0u;
+    for (size_t i = t0; i < (size_t)a.nsrc; i += stride) {
+        SourceRec r;
+        r.x = (float)a.pos[3 * i];
+        r.y = (float)a.pos[3 * i + 1];
+        r.z = (float)a.pos[3 * i + 2];
+        r.r_thin = a.r_thin ? (float)a.r_thin[i] : 0.0f;
+#pragma unroll
+        for (int b = 0; b < kMaxBins; ++b) r.scale[b] = b < a.nb ? (float)(a.ndot[i] * a.scale[b]) : 0.0f;
+        a.src[i] = r;
+        if (a.r_out) a.r_out[i] = 0x7F800000u;
+    }
+    if (a.roots) {
+        const uint32_t npix = 12u << (2 * a.level0);
+        for (size_t i = t0; i < (size_t)a.n_roots; i += stride)
+            a.roots[i] = root_ray(a.order[i / npix], a.level0, (uint32_t)(i % npix));
+    }
+}
+
+hipError_t launch_begin(const BeginArgs& a, hipStream_t s)
+{
+    const size_t n = std::max<size_t>(sizeof(RunBlock) / 4, a.roots ? a.n_roots : 0u);
+    k_begin<<<grid_for(n, 256, 8192), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -367,7 +363,7 @@ __global__ __launch_bounds__(256) void k_thin_fill(ThinFillArgs a)
         }
     }
     absorbed = wave_sum_f64(absorbed);
-    if ((threadIdx.x & 63) == 0 && absorbed != 0.0) atomicAdd(a.absorbed_thin, absorbed);
+    if ((threadIdx.x & 63) == 0 && absorbed != 0.0) atomicAdd(&my_slot(a.slots).photons[kPhotonsThin], absorbed);
 }
 
 hipError_t launch_thin_fill(const ThinFillArgs& a, hipStream_t s)
@@ -383,38 +379,17 @@ hipError_t launch_thin_fill(const ThinFillArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-__global__ void k_fill_u32(uint32_t* p, uint32_t n, uint32_t v)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
-}
-
-hipError_t launch_fill_u32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s)
-{
-    if (n > 0) k_fill_u32<<<grid_for(n, 256, 1024), 256, 0, s>>>(p, n, v);
-    return hipGetLastError();
-}
-
-__global__ void k_seed_roots(uint32_t first_src, uint32_t nsrc, int level0, const uint32_t* order, RayRec* out)
+// Root rays of one source (plain schedule).
+__global__ void k_seed_roots(uint32_t src, int level0, RayRec* out)
 {
     const uint32_t npix = 12u << (2 * level0);
-    const size_t n = (size_t)nsrc * npix;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        RayRec r;
-        const uint32_t k = (uint32_t)(i / npix);
-        r.src = order ? order[k] : first_src + k;
-        r.lp = ((uint32_t)level0 << kLevelShift) | (uint32_t)(i % npix);
-        r.pad0 = r.pad1 = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) r.tau[b] = r.taulo[b] = 0.0f;
-        out[i] = r;
-    }
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < npix; i += gridDim.x * blockDim.x)
+        out[i] = root_ray(src, level0, i);
 }
 
-hipError_t launch_seed_roots(uint32_t first_src, uint32_t nsrc, int level0, const uint32_t* order, RayRec* out,
-                             hipStream_t s)
+hipError_t launch_seed_roots(uint32_t src, int level0, RayRec* out, hipStream_t s)
 {
-    const size_t n = (size_t)nsrc * (12u << (2 * level0));
-    k_seed_roots<<<grid_for(n, 256), 256, 0, s>>>(first_src, nsrc, level0, order, out);
+    k_seed_roots<<<grid_for(12u << (2 * level0), 256), 256, 0, s>>>(src, level0, out);
     return hipGetLastError();
 }
 
@@ -491,7 +466,7 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
                         for (int k = 0; k < 4; ++k) out[slot + k] = child_rec<NB>(ray, k);
                     }
                 } else {
-                    atomicAdd(&A.counters[kQueueOverflow], 1ull);
+                    atomicAdd(&my_slot(A.slots).n[kQueueOverflow], 1ull);
                 }
             }
         }
@@ -505,7 +480,8 @@ static hipError_t trace_rays_nb(const TraceArgs& A, int prec, const RayRec* in, 
                                 uint32_t n_in, RayRec* out, uint32_t* n_out, uint32_t out_cap, int fam_out,
                                 hipStream_t s)
 {
-    const unsigned g = grid_for(n_in, 256, 1u << 16);
+    // at most 4096 workgroups: each fills a table of index terms and ends with the waves' counts
+    const unsigned g = grid_for(n_in, 256, 4096);
     const bool thin = A.r_out != nullptr;
     if (prec == 0 && A.corr && thin)
         k_trace_rays<NB, 0, true, true><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
@@ -571,6 +547,11 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
     const int lane = threadIdx.x & 63;
     const uint64_t lt = __lanemask_lt();
     const uint32_t n_items = *n_items_dev;
+    // a wave's first items are its own by its place in the grid, later ones come from the
+    // queue's head (the waves' first atomics on it, all at once, took 25 us)
+    const uint32_t first = fam ? 16u : 64u;
+    const uint32_t shared_from = gridDim.x * (uint32_t)WPB * first;
+    bool started = false;  // wave-uniform
     SRec* stk = lds + wid * stack_cap;
     Depositor<NB> dep{dscr + wid};
     dep_scratch_init(dep.scratch);
@@ -607,7 +588,7 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
                     if (g < spill_cap)
                         spill[g] = stk[(base + i) & cmask];
                     else
-                        atomicAdd(&A.counters[kQueueOverflow], 1ull);
+                        atomicAdd(&my_slot(A.slots).n[kQueueOverflow], 1ull);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 spilled += (uint32_t)m;
@@ -650,9 +631,12 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
             const uint32_t want = fam ? (uint32_t)(rem >> 2) : (uint32_t)rem;
             if (want > 0 && top == 0 && nspill == 0 && !qdone) {
                 const int take = used;
-                uint32_t b0 = 0;
-                if (lane == 0) b0 = atomicAdd(head, want);
-                b0 = __shfl(b0, 0, 64);
+                uint32_t b0 = (blockIdx.x * (uint32_t)WPB + (uint32_t)wid) * first;
+                if (started) {
+                    if (lane == 0) b0 = atomicAdd(head, want);
+                    b0 = shared_from + __shfl(b0, 0, 64);
+                }
+                started = true;
                 if (b0 >= n_items) {
                     qdone = true;
                 } else {
@@ -671,7 +655,7 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
                         if (fam) r = family_child<NB>(r, q & 3);
                         got = true;
                     }
-                    if (b0 + want >= n_items) qdone = true;
+                    if (b0 + want >= n_items || shared_from >= n_items) qdone = true;
                 }
             }
         }
@@ -685,7 +669,7 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
     }
     flush_stats<NB>(A, st);
     dep.flush(A);
-    if (lane == 0 && spilled) atomicAdd(&A.counters[kSpills], (unsigned long long)spilled);
+    if (lane == 0 && spilled) atomicAdd(&my_slot(A.slots).n[kSpills], (unsigned long long)spilled);
 }
 
 constexpr int kMaxWavesPerBlock = 8;
@@ -853,12 +837,13 @@ __global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a)
         __syncthreads();
     }
     absorbed = wave_sum_f64(absorbed);
-    if ((threadIdx.x & 63) == 0 && absorbed != 0.0) atomicAdd(a.absorbed, absorbed);
+    if ((threadIdx.x & 63) == 0 && absorbed != 0.0) atomicAdd(&my_slot(a.slots).photons[kPhotonsAbsorbed], absorbed);
 }
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s)
 {
-    const unsigned g = grid_for((size_t)((a.nbx8 + 3) / 4) * a.nby8 * a.nbz8, 1, 1u << 16);
+    // at most 2048 workgroups (768 are resident): each ends with an atomic per wave
+    const unsigned g = grid_for((size_t)((a.nbx8 + 3) / 4) * a.nby8 * a.nbz8, 1, 2048);
     switch (a.nb) {
         case 1: k_finalize<1><<<g, 256, 0, s>>>(a); break;
         case 2: k_finalize<2><<<g, 256, 0, s>>>(a); break;
