@@ -18,6 +18,8 @@
 
 using namespace arc;
 
+constexpr int kChemWords = kChemSlots * kChemSlotWords + 1;  // statistics and the work counter
+
 struct arc_ctx {
     int device = 0;
     int cus = 0;
@@ -50,7 +52,7 @@ struct arc_ctx {
     // small device scalars
     RunBlock* run = nullptr;
     RunBlock* run_host = nullptr;             // pinned
-    unsigned long long* chem_stats = nullptr;  // [0..3] chemistry statistics, [4] work counter
+    unsigned long long* chem_stats = nullptr;  // chemistry statistics (kChemSlots), then the work counter
     unsigned long long* reject = nullptr;     // learned step: cells for the plain solver, a bit each
     size_t reject_cap = 0;                    // words
     hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -261,7 +263,7 @@ arc_status arc_create(int32_t device, arc_ctx** out)
     }
     bool ok = hipMalloc((void**)&c->run, sizeof(RunBlock)) == hipSuccess &&
               hipHostMalloc((void**)&c->run_host, sizeof(RunBlock), hipHostMallocDefault) == hipSuccess &&
-              hipMalloc((void**)&c->chem_stats, 5 * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc((void**)&c->chem_stats, kChemWords * sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc((void**)&c->sums, 2 * sizeof(unsigned long long)) == hipSuccess;
     for (int i = 0; i < 6 && ok; ++i) ok = hipEventCreate(&c->ev[i]) == hipSuccess;
     if (!ok) {
@@ -1186,7 +1188,7 @@ struct ChemPlan {
 // stage 2 (plain and gated modes): the sub-cycled solver.
 hipError_t chem_stage(arc_ctx* c, const ChemPlan& P, int stage, hipStream_t st)
 {
-    if (stage == 0) return launch_zero_u64(c->chem_stats, 5, st);
+    if (stage == 0) return launch_zero_u64(c->chem_stats, kChemWords, st);
     if (stage == 1) return P.mode != ARC_CHEM_PLAIN ? mlp::launch_infer(P.ia, st) : hipSuccess;
     return P.mode != ARC_CHEM_MLP_ONLY ? launch_chem(P.a, P.cus, st) : hipSuccess;
 }
@@ -1338,6 +1340,7 @@ arc_status arc_chem_step(arc_ctx* c, const arc_grid* g, const arc_rates* r, doub
     ChemArgs& a = P.a;
     a.ncell = (uint32_t)((size_t)g->nx * g->ny * g->nz);
     a.y = g->y_he;
+    a.inv_y = g->y_he > 0 ? 1.0 / g->y_he : 0.0;
     a.n_h = g->n_h;
     a.x_hi = g->x_hi;
     a.x_hei = g->x_hei;
@@ -1354,7 +1357,7 @@ arc_status arc_chem_step(arc_ctx* c, const arc_grid* g, const arc_rates* r, doub
     a.eps = p->eps;
     a.t_floor = p->t_floor;
     a.stats = c->chem_stats;
-    a.chunk_counter = (uint32_t*)(c->chem_stats + 4);
+    a.chunk_counter = (uint32_t*)(c->chem_stats + kChemWords - 1);
     a.mask = nullptr;
     if (p->mode != ARC_CHEM_PLAIN) {
         const size_t words = ((size_t)a.ncell + 63) / 64;
@@ -1400,9 +1403,16 @@ arc_status arc_chem_step(arc_ctx* c, const arc_grid* g, const arc_rates* r, doub
         HIP_TRY(c, chem_stage(c, P, 2, st));
     }
     HIP_TRY(c, hipEventRecord(c->ev[1], st));
-    unsigned long long cs[4];
-    HIP_TRY(c, hipMemcpyAsync(cs, c->chem_stats, sizeof cs, hipMemcpyDeviceToHost, st));
+    unsigned long long raw[kChemSlots * kChemSlotWords], cs[4] = {0, 0, 0, 0};
+    HIP_TRY(c, hipMemcpyAsync(raw, c->chem_stats, sizeof raw, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
+    for (int i = 0; i < kChemSlots; ++i) {
+        const unsigned long long* w = raw + i * kChemSlotWords;
+        cs[0] += w[0];
+        cs[1] += w[1];
+        cs[2] = std::max(cs[2], w[2]);
+        cs[3] += w[3];
+    }
     if (stats) {
         stats->cells = a.ncell;
         stats->sub_total = (int64_t)cs[0];

@@ -85,9 +85,10 @@ __device__ __forceinline__ Coef coefficients(const Lam& l)
 __device__ __forceinline__ Coef coefficients(float T) { return coefficients(lambdas(T)); }
 
 // Cooling per volume [erg cm^-3 s^-1]: recombination, collisional ionisation,
-// collisional excitation, bremsstrahlung. Rate coefficients in FP32, products in FP64.
+// collisional excitation, bremsstrahlung. Rate coefficients in FP32, products and sums in FP64.
+template <bool COLL>
 __device__ __forceinline__ double cooling(float T, const Lam& l, const Coef& k, double ne, double nhi, double nhii,
-                                          double nhei, double nheii, double nheiii, int collisional)
+                                          double nhei, double nheii, double nheiii)
 {
     // recombination cooling: 3.435e-30 T lambda^1.970 / (1 + (lambda / 2.250)^0.376)^3.720; HeIII is
     // hydrogenic (Z^3 times hydrogen at T / Z^2, Z = 2), i.e. the same fit at lambda_HeII times 2 (the fit
@@ -95,20 +96,27 @@ __device__ __forceinline__ double cooling(float T, const Lam& l, const Coef& k, 
     const float rec_hii = 3.435e-30f * fexp2(l.lt + 1.970f * l.lhi - log2_den(l.lhi, kL2_2250, 0.376f, 3.720f));
     const float rec_heii = (1.380649e-16f * 1.26e-14f) * fexp2(l.lt + 0.750f * l.lhei);
     const float rec_heiii = 2.0f * 3.435e-30f * fexp2(l.lt + 1.970f * l.lheii - log2_den(l.lheii, kL2_2250, 0.376f, 3.720f));
-    const double diel_cool = 0.75 * 54.418 * kEV * (double)dielectronic(l);
-    double lam = ne * ((double)rec_hii * nhii + (double)rec_heii * nheii + (double)rec_heiii * nheiii + diel_cool * nheii);
-    if (collisional)
-        lam += ne * (13.598 * kEV * (double)k.k_hi * nhi + 24.587 * kEV * (double)k.k_hei * nhei +
-                     54.418 * kEV * (double)k.k_heii * nheii);
     // collisional excitation, damped by 1 / (1 + (T / 1e5)^(1/2))
-    const float idamp = __builtin_amdgcn_rcpf(1.0f + sqrtf(T * 1e-5f));
-    lam += ne * nhi * (double)(7.5e-19f * fexp2(-0.375f * kLog2e * l.hi) * idamp);
-    lam += ne * nheii * (double)(5.54e-17f * fexp2(-0.397f * l.lt - 0.375f * kLog2e * l.heii) * idamp);
+    const float st = __builtin_amdgcn_sqrtf(T);
+    const float idamp = __builtin_amdgcn_rcpf(1.0f + st * 3.1622776601683794e-3f);
+    const float exc_hi = 7.5e-19f * fexp2(-0.375f * kLog2e * l.hi) * idamp;
+    const float exc_heii = 5.54e-17f * fexp2(-0.397f * l.lt - 0.375f * kLog2e * l.heii) * idamp;
     // bremsstrahlung with the Gaunt factor 1.1 + 0.34 e^(-(5.5 - log10 T)^2 / 3)
     const float lt10 = l.lt * 0.30102999566398120f;
     const float gff = 1.1f + 0.34f * fexp(-(5.5f - lt10) * (5.5f - lt10) * (1.0f / 3.0f));
-    lam += (double)(1.42e-27f * gff * sqrtf(T)) * (nhii + nheii + 4.0 * nheiii) * ne;
-    return lam;
+    double lam = (double)rec_hii * nhii;
+    lam = fma((double)rec_heii, nheii, lam);
+    lam = fma((double)rec_heiii, nheiii, lam);
+    lam = fma(0.75 * 54.418 * kEV * (double)dielectronic(l), nheii, lam);
+    if constexpr (COLL) {
+        lam = fma(13.598 * kEV * (double)k.k_hi, nhi, lam);
+        lam = fma(24.587 * kEV * (double)k.k_hei, nhei, lam);
+        lam = fma(54.418 * kEV * (double)k.k_heii, nheii, lam);
+    }
+    lam = fma((double)exc_hi, nhi, lam);
+    lam = fma((double)exc_heii, nheii, lam);
+    lam = fma((double)(1.42e-27f * gff * st), fma(4.0, nheiii, nhii + nheii), lam);
+    return ne * lam;
 }
 
 }  // namespace chem

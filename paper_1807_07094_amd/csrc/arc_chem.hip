@@ -25,36 +25,37 @@ namespace arc {
 // State of one cell during its sub-cycled update.
 struct ChemCell {
     double nh, nhe, nhi, nhii, nhei, nheii, nheiii, ne, E, t;
-    double ghi, ghei, gheii, hhi, hhei, hheii;
+    float ghi, ghei, gheii, hhi, hhei, hheii;
     float T;
     int n;
-    bool cap;
     uint32_t c;
 };
 
-__device__ __forceinline__ void chem_load(const ChemArgs& a, uint32_t c, ChemCell& s)
+// Loads cell lo + i; lo is wave-uniform, so that the addresses are a scalar base and a 32-bit
+// lane offset.
+__device__ __forceinline__ void chem_load(const ChemArgs& a, uint32_t lo, uint32_t i, ChemCell& s)
 {
-    s.c = c;
-    s.nh = a.n_h[c];
+    s.c = lo + i;
+    s.nh = (a.n_h + lo)[i];
     s.nhe = a.y * s.nh;
-    s.nhi = s.nh * (double)a.x_hi[c];
+    s.nhi = s.nh * (double)(a.x_hi + lo)[i];
     s.nhii = s.nh - s.nhi;
-    s.nhei = s.nhe * (double)a.x_hei[c];
-    s.nheii = s.nhe * (double)a.x_heii[c];
+    s.nhei = s.nhe * (double)(a.x_hei + lo)[i];
+    s.nheii = s.nhe * (double)(a.x_heii + lo)[i];
     s.nheiii = s.nhe - s.nhei - s.nheii;
     if (s.nheiii < 0) s.nheiii = 0;
-    s.T = a.temp[c];
-    s.ne = s.nhii + s.nheii + 2.0 * s.nheiii;
+    s.T = (a.temp + lo)[i];
+    s.ne = fma(2.0, s.nheiii, s.nhii + s.nheii);
     s.E = 1.5 * chem::kKB * (double)s.T * (s.nh + s.nhe + s.ne);
-    s.ghi = a.gamma[c];
-    s.ghei = a.gamma[(size_t)a.ncell + c];
-    s.gheii = a.gamma[2 * (size_t)a.ncell + c];
-    s.hhi = a.heat[c];
-    s.hhei = a.heat[(size_t)a.ncell + c];
-    s.hheii = a.heat[2 * (size_t)a.ncell + c];
+    const size_t n = a.ncell;
+    s.ghi = (a.gamma + lo)[i];
+    s.ghei = (a.gamma + n + lo)[i];
+    s.gheii = (a.gamma + 2 * n + lo)[i];
+    s.hhi = (a.heat + lo)[i];
+    s.hhei = (a.heat + n + lo)[i];
+    s.hheii = (a.heat + 2 * n + lo)[i];
     s.t = 0.0;
     s.n = 0;
-    s.cap = false;
 }
 
 // 1 / b for b > 0 from the hardware reciprocal and two Newton steps (within an ulp or two
@@ -69,60 +70,70 @@ __device__ __forceinline__ double rcp64(double b)
 
 // One sub-step (section 2.7: backward difference for the species, sub-step limited to a
 // fraction eps of the shortest change time). Returns true once the cell has reached dt.
+template <bool RATES, bool THERMAL, bool COLL>
 __device__ __forceinline__ bool chem_substep(const ChemArgs& a, ChemCell& s)
 {
     chem::Coef k{};
-    const chem::Lam l = chem::lambdas(s.T);
-    if (a.rates == 0) {
-        k.a_hii = (float)a.alpha_hii;
-    } else {
+    chem::Lam l{};
+    if constexpr (RATES || THERMAL) l = chem::lambdas(s.T);
+    if constexpr (RATES) {
         k = chem::coefficients(l);
-        if (!a.collisional) k.k_hi = k.k_hei = k.k_heii = 0.0f;
+        if constexpr (!COLL) k.k_hi = k.k_hei = k.k_heii = 0.0f;
+    } else {
+        k.a_hii = (float)a.alpha_hii;
     }
-    const double ndot_hi = (double)k.a_hii * s.ne * s.nhii - (s.ghi + (double)k.k_hi * s.ne) * s.nhi;
+    const double gain_hi = (double)k.a_hii * s.ne, loss_hi = fma((double)k.k_hi, s.ne, (double)s.ghi);
+    const double ndot_hi = fma(gain_hi, s.nhii, -(loss_hi * s.nhi));
     double edot = 0.0;
-    if (!a.isothermal)
-        edot = s.nhi * s.hhi + s.nhei * s.hhei + s.nheii * s.hheii -
-               chem::cooling(s.T, l, k, s.ne, s.nhi, s.nhii, s.nhei, s.nheii, s.nheiii, a.collisional);
+    if constexpr (THERMAL)
+        edot = fma(s.nhi, (double)s.hhi, fma(s.nhei, (double)s.hhei, s.nheii * (double)s.hheii)) -
+               chem::cooling<COLL>(s.T, l, k, s.ne, s.nhi, s.nhii, s.nhei, s.nheii, s.nheiii);
     double h = a.dt - s.t;
     bool last = true;
-    if (s.n >= a.max_sub) {
-        s.cap = true;
-    } else {
-        const double le = edot != 0.0 ? a.eps * s.E * rcp64(fabs(edot)) : INFINITY;
-        const double in = ndot_hi != 0.0 ? rcp64(fabs(ndot_hi)) : 0.0;
-        if (edot != 0.0 && le < h) {
-            h = le;
-            last = false;
+    if (s.n < a.max_sub) {
+        // a limit is divided out only where it binds: most cells take one sub-step
+        if constexpr (THERMAL) {
+            if (a.eps * s.E < h * fabs(edot)) {
+                const double le = a.eps * s.E * rcp64(fabs(edot));
+                if (le < h) {
+                    h = le;
+                    last = false;
+                }
+            }
         }
-        if (s.nhi > 0.0 && ndot_hi != 0.0 && a.eps * s.nhi * in < h) {
-            h = a.eps * s.nhi * in;
-            last = false;
-        }
-        if (s.nhii > 0.0 && ndot_hi != 0.0 && a.eps * s.nhii * in < h) {
-            h = a.eps * s.nhii * in;
-            last = false;
+        const double m = fmin(s.nhi > 0.0 ? s.nhi : INFINITY, s.nhii > 0.0 ? s.nhii : INFINITY);
+        if (a.eps * m < h * fabs(ndot_hi)) {
+            const double ln = a.eps * m * rcp64(fabs(ndot_hi));
+            if (ln < h) {
+                h = ln;
+                last = false;
+            }
         }
     }
-    s.nhi = (s.nhi + (double)k.a_hii * s.ne * s.nhii * h) * rcp64(1.0 + (s.ghi + (double)k.k_hi * s.ne) * h);
+    // three quotients from one reciprocal
+    const double d1 = fma(loss_hi, h, 1.0), d2 = fma(fma((double)k.k_hei, s.ne, (double)s.ghei), h, 1.0),
+                 d3 = fma((double)k.a_heiii * s.ne, h, 1.0);
+    const double p12 = d1 * d2, r = rcp64(p12 * d3), r12 = r * d3;
+    // (the clamps are comparisons, which let a NaN through, not fmin and fmax)
+    s.nhi = fma(gain_hi * s.nhii, h, s.nhi) * (r12 * d2);
     if (s.nhi > s.nh) s.nhi = s.nh;
     s.nhii = s.nh - s.nhi;
-    double nhei_new = (s.nhei + (double)k.a_heii * s.ne * s.nheii * h) * rcp64(1.0 + (s.ghei + (double)k.k_hei * s.ne) * h);
-    double nheiii_new =
-        (s.nheiii + (s.gheii + (double)k.k_heii * s.ne) * s.nheii * h) * rcp64(1.0 + (double)k.a_heiii * s.ne * h);
+    double nhei_new = fma((double)k.a_heii * s.ne * s.nheii, h, s.nhei) * (r12 * d1);
     if (nhei_new > s.nhe) nhei_new = s.nhe;
-    if (nheiii_new > s.nhe - nhei_new) nheiii_new = s.nhe - nhei_new;
+    const double up = fma((double)k.k_heii, s.ne, (double)s.gheii) * s.nheii;
+    s.nheiii = fma(up, h, s.nheiii) * (r * p12);
+    if (s.nheiii > s.nhe - nhei_new) s.nheiii = s.nhe - nhei_new;
     s.nhei = nhei_new;
-    s.nheiii = nheiii_new;
     s.nheii = s.nhe - s.nhei - s.nheiii;
     if (s.nheii < 0.0) s.nheii = 0.0;
-    s.ne = s.nhii + s.nheii + 2.0 * s.nheiii;
-    if (!a.isothermal) {
-        s.E += edot * h;
-        double Td = s.E * rcp64(1.5 * chem::kKB * (s.nh + s.nhe + s.ne));
+    s.ne = fma(2.0, s.nheiii, s.nhii + s.nheii);
+    if constexpr (THERMAL) {
+        s.E = fma(edot, h, s.E);
+        const double heat_cap = 1.5 * chem::kKB * (s.nh + s.nhe + s.ne);
+        double Td = s.E * rcp64(heat_cap);
         if (Td < a.t_floor) {
             Td = a.t_floor;
-            s.E = 1.5 * chem::kKB * Td * (s.nh + s.nhe + s.ne);
+            s.E = Td * heat_cap;
         }
         s.T = (float)Td;
     }
@@ -131,96 +142,130 @@ __device__ __forceinline__ bool chem_substep(const ChemArgs& a, ChemCell& s)
     return !(s.t < a.dt);
 }
 
+template <bool THERMAL>
 __device__ __forceinline__ void chem_store(const ChemArgs& a, const ChemCell& s)
 {
-    a.x_hi[s.c] = (float)(s.nhi / s.nh);
-    if (s.nhe > 0.0) {
-        a.x_hei[s.c] = (float)(s.nhei / s.nhe);
-        a.x_heii[s.c] = (float)(s.nheii / s.nhe);
+    const double inh = rcp64(s.nh);
+    a.x_hi[s.c] = (float)(s.nhi * inh);
+    if (a.y > 0.0) {
+        const double inhe = inh * a.inv_y;
+        a.x_hei[s.c] = (float)(s.nhei * inhe);
+        a.x_heii[s.c] = (float)(s.nheii * inhe);
     }
-    a.temp[s.c] = s.T;
+    if constexpr (THERMAL) a.temp[s.c] = s.T;
 }
 
 // Per-cell chemistry (section 2.7). Cells need from one to many sub-steps, so a wave does
 // not take 64 cells and wait for the slowest: each lane advances its cell one sub-step per
 // iteration and takes the next cell of the wave's chunk when done (refilled once kChemRefill
-// lanes are idle); chunks of kChemChunk cells come from a global counter.
-constexpr uint32_t kChemChunk = 2048;
+// lanes are idle). A wave's first chunk is its own by its place in the grid, later ones come
+// from a global counter. The kernel is instantiated per combination of options, sums with FMAs
+// and divides only where it must: about 400 VALU instructions per sub-step instead of 600, which
+// brings VALU issue to where the 60 bytes per cell are (256^3 cells of a running model, one
+// sub-step in nearly all of them: 575 -> 245 us, of which the bytes take 186 at a copy's rate).
 constexpr int kChemRefill = 16;
 
-__global__ __launch_bounds__(256) void k_chem(ChemArgs a)
+template <bool RATES, bool THERMAL, bool COLL>
+__global__ __launch_bounds__(256) void k_chem(ChemArgs a, uint32_t chunk)
 {
-    unsigned long long sub_total = 0, capped = 0, cells = 0;
-    unsigned int sub_max = 0;
+    unsigned long long sub_total = 0, capped = 0, cells = 0;  // wave-uniform
+    int sub_max = 0;
     const int lane = threadIdx.x & 63;
-    const uint64_t lt = __lanemask_lt();
-    uint32_t lo = 0, hi = 0;  // the wave's remaining chunk [lo, hi), wave-uniform
+    const uint32_t wave = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t own = (uint64_t)wave * chunk, shared_from = (uint64_t)gridDim.x * 4u * chunk;
+    uint32_t lo = (uint32_t)min(own, (uint64_t)a.ncell);  // the wave's remaining chunk [lo, hi), wave-uniform
+    uint32_t hi = (uint32_t)min(own + chunk, (uint64_t)a.ncell);
     bool drained = false;     // wave-uniform
     bool have = false;
     ChemCell s;
     for (;;) {
-        const uint64_t idle = __ballot(!have);
+        const uint64_t idle = __builtin_amdgcn_ballot_w64(!have);
         const int nidle = __popcll(idle);
         if (!drained && (nidle >= kChemRefill || nidle == 64)) {
             // hand the next cells to the idle lanes, in lane order
+            const int place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
             int given = 0;
             while (given < nidle && !drained) {
                 if (lo >= hi) {
                     uint32_t b0 = 0;
-                    if (lane == 0) b0 = atomicAdd(a.chunk_counter, kChemChunk);
-                    b0 = (uint32_t)__shfl((int)b0, 0, 64);
-                    if (b0 >= a.ncell) {
+                    if (shared_from < a.ncell) {
+                        if (lane == 0) b0 = atomicAdd(a.chunk_counter, 1u);
+                        b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+                    }
+                    const uint64_t from = shared_from + (uint64_t)b0 * chunk;
+                    if (from >= a.ncell) {
                         drained = true;
                         break;
                     }
-                    lo = b0;
-                    hi = min(a.ncell, b0 + kChemChunk);
+                    lo = (uint32_t)from;
+                    hi = (uint32_t)min(from + chunk, (uint64_t)a.ncell);
                 }
                 const int take = min(nidle - given, (int)(hi - lo));
-                const int rank = __popcll(idle & lt) - given;
+                const int rank = place - given;
                 if (!have && rank >= 0 && rank < take) {
                     const uint32_t c = lo + (uint32_t)rank;
                     if (!a.mask || ((a.mask[c >> 6] >> (c & 63)) & 1ull)) {
-                        chem_load(a, c, s);
+                        chem_load(a, lo, (uint32_t)rank, s);
                         have = true;
-                        ++cells;
                     }
                 }
                 lo += (uint32_t)take;
                 given += take;
             }
+            cells += __popcll(__builtin_amdgcn_ballot_w64(have) & idle);
         }
-        if (!__any(have)) {
+        const uint64_t busy = __builtin_amdgcn_ballot_w64(have);
+        if (!busy) {
             if (drained) break;
             continue;
         }
-        if (have && chem_substep(a, s)) {
-            chem_store(a, s);
-            sub_total += (unsigned long long)s.n;
-            capped += s.cap ? 1ull : 0ull;
-            sub_max = max(sub_max, (unsigned)s.n);
+        sub_total += __popcll(busy);
+        bool done = false;
+        if (have) done = chem_substep<RATES, THERMAL, COLL>(a, s);
+        if (done) {
+            chem_store<THERMAL>(a, s);
+            sub_max = max(sub_max, s.n);
             have = false;
         }
+        // the sub-step after max_sub others went to the end of the step whatever its limits
+        capped += __popcll(__builtin_amdgcn_ballot_w64(done && s.n > a.max_sub));
     }
-    sub_total = wave_sum_u64(sub_total);
-    capped = wave_sum_u64(capped);
-    cells = wave_sum_u64(cells);
-    for (int off = 32; off > 0; off >>= 1) sub_max = max(sub_max, (unsigned)__shfl_xor((int)sub_max, off, 64));
-    if ((threadIdx.x & 63) == 0) {
-        if (sub_total) atomicAdd(&a.stats[0], sub_total);
-        if (capped) atomicAdd(&a.stats[1], capped);
-        atomicMax(&a.stats[2], (unsigned long long)sub_max);
-        if (cells) atomicAdd(&a.stats[3], cells);
+    for (int off = 32; off > 0; off >>= 1) sub_max = max(sub_max, __shfl_xor(sub_max, off, 64));
+    if (lane == 0) {
+        // atomics on one line go one after the other: kChemSlots copies, summed by the host
+        unsigned long long* st = a.stats + (size_t)(blockIdx.x & (kChemSlots - 1)) * kChemSlotWords;
+        if (sub_total) atomicAdd(&st[0], sub_total);
+        if (capped) atomicAdd(&st[1], capped);
+        if (sub_max) atomicMax(&st[2], (unsigned long long)sub_max);
+        if (cells) atomicAdd(&st[3], cells);
     }
+}
+
+template <bool RATES, bool THERMAL, bool COLL>
+static hipError_t chem_go(const ChemArgs& a, int cus, hipStream_t s)
+{
+    // resident waves only (six per SIMD): every wave loops until the chunks run out
+    const size_t want = ((size_t)a.ncell + 255) / 256;
+    const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>(want, (size_t)std::max(1, cus) * 6));
+    // Two chunks per wave and more on large grids (the second half goes to whoever is free), at
+    // most 2048 cells; on small ones at least the 64 cells of one round, so that all waves work
+    // (64^3 cells in chunks of 2048 kept 128 waves busy, 157 us).
+    const size_t waves = (size_t)blocks * 4;
+    const size_t half = ((size_t)a.ncell / (2 * waves) + 63) / 64 * 64;
+    const uint32_t chunk = (uint32_t)std::min<size_t>(2048, std::max<size_t>(64, half));
+    k_chem<RATES, THERMAL, COLL><<<blocks, 256, 0, s>>>(a, chunk);
+    return hipGetLastError();
 }
 
 hipError_t launch_chem(const ChemArgs& a, int cus, hipStream_t s)
 {
-    // resident waves only: every wave loops until the chunk counter passes ncell
-    const size_t want = ((size_t)a.ncell + 255) / 256;
-    const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>(want, (size_t)std::max(1, cus) * 8));
-    k_chem<<<blocks, 256, 0, s>>>(a);
-    return hipGetLastError();
+    const bool coll = a.collisional != 0;
+    if (a.rates != 0) {
+        if (a.isothermal) return coll ? chem_go<true, false, true>(a, cus, s) : chem_go<true, false, false>(a, cus, s);
+        return coll ? chem_go<true, true, true>(a, cus, s) : chem_go<true, true, false>(a, cus, s);
+    }
+    // fixed alpha_HII: collisional terms are zero
+    return a.isothermal ? chem_go<false, false, false>(a, cus, s) : chem_go<false, true, false>(a, cus, s);
 }
 
 // -------------------------------------------------------------------------------------

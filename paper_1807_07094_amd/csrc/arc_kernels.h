@@ -64,6 +64,7 @@ struct ThinFillArgs {
     CounterSlot* slots;        // photons of the fill: its deposits times u_J kappa
 };
 
+constexpr int kChemSlots = 16, kChemSlotWords = 16;  // a 128-byte line each
 struct ChemArgs {
     uint32_t ncell;
     double y;
@@ -73,7 +74,8 @@ struct ChemArgs {
     double dt;
     int isothermal, rates, collisional, max_sub;
     double alpha_hii, eps, t_floor;
-    unsigned long long* stats;  // [0] sub total, [1] capped, [2] max, [3] cells updated
+    double inv_y;               // 1 / y (0 where y = 0)
+    unsigned long long* stats;  // [kChemSlots][kChemSlotWords]: sub total, capped, max, cells updated
     uint32_t* chunk_counter;    // zero before the launch
     // optional: update only the cells whose bit is set, bit (c mod 64) of word c / 64
     const unsigned long long* mask;
