@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace arc {
@@ -47,6 +48,9 @@ struct Model {
     float gate_err[kGateBins];      // twice the largest held-out error per bin (max of |dx| and |dT|/(10 T))
 };
 
+// the training kernel reads rows of the images 16 bytes at a time
+static_assert(offsetof(Model, w1t) % 16 == 0 && offsetof(Model, w2t) % 16 == 0 && offsetof(Model, w3t) % 16 == 0, "aligned rows");
+
 struct InferArgs {
     const Model* model;
     uint32_t ncell;
@@ -69,11 +73,12 @@ hipError_t launch_infer(const InferArgs& a, hipStream_t s);
 // (x_HI' - x_base, log10 (T'/T)), minibatch rows given by idx.
 struct TrainArgs {
     const Model* model;       // bf16 weights used by the forward pass
+    const float* params;      // FP32 master weights, whose rounding the model holds
     const float* F;
     const float* Y;
     const uint32_t* idx;      // sample order
     uint32_t first, count;    // the minibatch: idx[first .. first + count)
-    float* partial;           // [waves][kNParams] gradient partial sums
+    float* partial;           // [workgroups of 64 samples][kNParams] gradient partial sums
 };
 hipError_t launch_train_grad(const TrainArgs& a, hipStream_t s);
 

@@ -11,10 +11,10 @@
 //                 (each layer's MFMA output is the next layer's operand), gate; accepted
 //                 cells are written, rejected cells are appended to a list for the plain solver
 //   k_predict     the same forward pass without the gate (validation, evaluation)
-//   k_train_grad  quantisation-aware forward and backward of a minibatch (MFMA through LDS),
-//                 one gradient partial per wave (summed in fixed order: deterministic)
-//   k_adam        Adam update of the FP32 master parameters
-//   k_publish     BF16 weight images for the MFMA operands
+//   k_train_grad  quantisation-aware forward and backward of a minibatch (MFMA), one gradient
+//                 partial per 64 samples (summed in fixed order: deterministic)
+//   k_adam        Adam update of the FP32 master parameters and their BF16 images
+//   k_publish     all BF16 weight images for the MFMA operands
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -38,30 +38,6 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// 8 elements (row, k0 .. k0+7) of a bf16 matrix with element strides sr (row) and sk (k).
-__device__ __forceinline__ bf16x8 frag(const __bf16* m, int row, int k0, int sr, int sk)
-{
-    bf16x8 v;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = m[row * sr + (k0 + i) * sk];
-    return v;
-}
-
-// One 16x16 tile of D = A B over depth K (multiple of 32); A(m, k) = A[m sar + k sak],
-// B(k, n) = B[k sbk + n sbn]. Lane l receives D[m0 + 4 (l/16) + r][n0 + l % 16].
-__device__ __forceinline__ f32x4 tile_mm(const __bf16* A, int sar, int sak, const __bf16* B, int sbk, int sbn, int m0,
-                                         int n0, int K)
-{
-    const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        const bf16x8 a = frag(A, m0 + r16, k0 + 8 * q, sar, sak);
-        const bf16x8 b = frag(B, n0 + r16, k0 + 8 * q, sbn, sbk);
-        acc = mfma(a, b, acc);
-    }
-    return acc;
-}
-
 __device__ __forceinline__ float act(float x) { return fmaxf(x, 0.0f); }  // ReLU
 
 // Orders one wave's LDS writes before its later reads by other lanes: LDS operations of
@@ -71,76 +47,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-
-// Forward pass of 64 rows held in LDS: X [64][kK1] -> H (in place, [64][kHid]) -> O [64][2].
-// W1t [kHid][kK1], W2t [kHid][kHid], W3t [kOutP][kHid] and the biases are in LDS.
-// Every lane of the wave must call it. H1 (if given) keeps the first hidden layer.
-__device__ __forceinline__ void forward64(const __bf16* X, __bf16* H, __bf16* H1keep, float* O, const __bf16* w1t,
-                                          const __bf16* w2t, const __bf16* w3t, const float* b1, const float* b2,
-                                          const float* b3)
-{
-    const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
-    // layer 1: [64 x 32] x [32 x 64]
-    for (int t = 0; t < 4; ++t) {
-        f32x4 d[4];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) d[nt] = tile_mm(X, kK1, 1, w1t, 1, kK1, 16 * t, 16 * nt, kK1);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * t + 4 * q + r, col = 16 * nt + r16;
-                const __bf16 h = (__bf16)act(d[nt][r] + b1[col]);
-                H[row * kHid + col] = h;
-                if (H1keep) H1keep[row * kHid + col] = h;
-            }
-    }
-    wave_sync();
-    // layer 2: [64 x 64] x [64 x 64], written back over the rows it reads
-    for (int t = 0; t < 4; ++t) {
-        f32x4 d[4];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) d[nt] = tile_mm(H, kHid, 1, w2t, 1, kHid, 16 * t, 16 * nt, kHid);
-        wave_sync();
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * t + 4 * q + r, col = 16 * nt + r16;
-                H[row * kHid + col] = (__bf16)act(d[nt][r] + b2[col]);
-            }
-        wave_sync();
-    }
-    // layer 3: [64 x 64] x [64 x 16]
-    for (int t = 0; t < 4; ++t) {
-        const f32x4 d = tile_mm(H, kHid, 1, w3t, 1, kHid, 16 * t, 0, kHid);
-        if (r16 < kOut)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) O[(16 * t + 4 * q + r) * kOut + r16] = d[r] + b3[r16];
-    }
-    wave_sync();
-}
-
-// Model weights into LDS (called by the whole block).
-struct SharedModel {
-    __bf16 w1t[kHid * kK1];
-    __bf16 w2t[kHid * kHid];
-    __bf16 w3t[kOutP * kHid];
-    float b1[kHid], b2[kHid], b3[kOut];
-};
-
-__device__ __forceinline__ void load_model(const Model* m, SharedModel& s)
-{
-    for (int i = threadIdx.x; i < kHid * kK1; i += blockDim.x) s.w1t[i] = (&m->w1t[0][0])[i];
-    for (int i = threadIdx.x; i < kHid * kHid; i += blockDim.x) s.w2t[i] = (&m->w2t[0][0])[i];
-    for (int i = threadIdx.x; i < kOutP * kHid; i += blockDim.x) s.w3t[i] = (&m->w3t[0][0])[i];
-    for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
-        s.b1[i] = m->b1[i];
-        s.b2[i] = m->b2[i];
-    }
-    if (threadIdx.x < kOut) s.b3[threadIdx.x] = m->b3[threadIdx.x];
-}
-
 
 // ---------------------------------------------------------------------------------
 // Forward pass with the activations in registers.
@@ -534,137 +440,262 @@ hipError_t launch_features(const float* X, const float* Y, uint32_t m, float y, 
 // Training: gradient of the minibatch loss
 //   L = sum_s (o0 - y0)^2 + (o1 - y1)^2     (standardised targets; divided by the batch
 //                                            size in Adam)
-// through the same BF16 forward as inference. One wave per block, 64 samples per wave.
+// through the same BF16 forward as inference. 64 samples per workgroup of four waves: a wave
+// takes 16 samples through the forward pass and back to both hidden layers without waiting for
+// the others, then, after one barrier, a quarter of the weight gradients, which sum over all 64
+// samples. A minibatch is only a few workgroups, so the step is a chain of latencies: the weights
+// come straight from memory as MFMA operands (all loads issued at the start), every activation
+// is written to LDS in the orders in which it is read (16 bytes a lane, rows padded against bank
+// conflicts), and the ReLU masks stay in registers. Batch of 1024: 44 us with one wave per 64
+// samples, weights staged in LDS and operands gathered element by element, 9 us so.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_train_grad(TrainArgs a)
+constexpr int kRow = 72;  // padded row of 64 BF16 values in LDS (144 bytes)
+
+__device__ __forceinline__ bf16x8 zero8()
 {
-    __shared__ SharedModel sm;
-    __shared__ __bf16 w3pad[32 * kHid];  // W3t with zero rows to depth 32
-    __shared__ __bf16 X[64 * kK1];
-    __shared__ __bf16 H[64 * kHid];      // second hidden layer after the forward pass
-    __shared__ __bf16 H1[64 * kHid];
-    __shared__ __bf16 D2[64 * kHid];     // dL/dz2
-    __shared__ __bf16 D1[64 * kHid];     // dL/dz1
-    __shared__ __bf16 DO[64 * 32];       // dL/do, zero-padded to depth 32
-    __shared__ float O[64 * kOut];
-    load_model(a.model, sm);
-    for (int i = threadIdx.x; i < 32 * kHid; i += blockDim.x) w3pad[i] = i < kOutP * kHid ? sm.w3t[i] : (__bf16)0.0f;
-    __syncthreads();
-    const int lane = threadIdx.x, r16 = lane & 15, q = lane >> 4;
-    const uint32_t s_local = blockIdx.x * 64u + (uint32_t)lane;
-    const bool valid = s_local < a.count;
-    float y0 = 0.0f, y1 = 0.0f;
-    {
-        const uint32_t i = valid ? a.idx[a.first + s_local] : 0u;
+    bf16x8 v;
 #pragma unroll
-        for (int k = 0; k < kK1; ++k) X[lane * kK1 + k] = (__bf16)(k < kIn && valid ? a.F[(size_t)i * kIn + k] : 0.0f);
-        if (valid) {
-            y0 = a.Y[(size_t)i * 2];
-            y1 = a.Y[(size_t)i * 2 + 1];
+    for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.0f;
+    return v;
+}
+__device__ __forceinline__ bf16x8 from_f32(const float* p)
+{
+    bf16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = (__bf16)p[i];
+    return v;
+}
+__device__ __forceinline__ bf16x8 row8(const __bf16* m, int row, int k) { return *(const bf16x8*)(m + row * kRow + k); }
+
+__global__ __launch_bounds__(256) void k_train_grad(TrainArgs a)
+{
+    // [sample][unit]: operands of the next layer; [unit][sample]: operands of the weight gradients
+    __shared__ __align__(16) __bf16 H1[64 * kRow], H2[64 * kRow];       // H2's rows become D2's
+    __shared__ __align__(16) __bf16 H1t[64 * kRow], H2t[64 * kRow], D1t[64 * kRow], D2t[64 * kRow];
+    __shared__ __align__(16) __bf16 Xt[kIn * kRow], DOt[kOut * kRow], DO[64 * kOut];
+    const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4, t = threadIdx.x >> 6;
+    const Model* M = a.model;
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const f32x4 none = {0.0f, 0.0f, 0.0f, 0.0f};
+    // operands: lane (r16, q) supplies row or column r16, depth 8 q .. 8 q + 7 of a k-step
+    const uint32_t s0 = blockIdx.x * 64u + 16u * (uint32_t)t;  // the wave's first sample
+    bf16x8 x = zero8();
+    if (q == 0) {
+        const uint32_t sl = s0 + (uint32_t)r16;
+        if (sl < a.count) x = from_f32(a.F + (size_t)a.idx[a.first + sl] * kIn);
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) Xt[k * kRow + 16 * t + r16] = x[k];
+    }
+    float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (r16 < kOut)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t sl = s0 + 4u * (uint32_t)q + (uint32_t)r;
+            if (sl < a.count) y[r] = a.Y[(size_t)a.idx[a.first + sl] * 2 + r16];
+        }
+    bf16x8 w1[4], w2[4][2], w3[2], w2b[4][2], w3b[4];
+    float b1[4], b2[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const int n = 16 * nt + r16;
+        w1[nt] = *(const bf16x8*)&M->w1t[n][8 * q];
+        b1[nt] = M->b1[n];
+        b2[nt] = M->b2[n];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            w2[nt][k] = *(const bf16x8*)&M->w2t[n][32 * k + 8 * q];
+            // the same rounding of the master weights, in the order of the way back
+            w2b[nt][k] = from_f32(a.params + kW2 + n * kHid + 32 * k + 8 * q);
+        }
+        w3b[nt] = zero8();
+        if (q == 0) {
+            w3b[nt][0] = (__bf16)a.params[kW3 + n * kOut];
+            w3b[nt][1] = (__bf16)a.params[kW3 + n * kOut + 1];
         }
     }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) w3[k] = *(const bf16x8*)&M->w3t[r16][32 * k + 8 * q];
+    const float b3 = r16 < kOut ? M->b3[r16] : 0.0f;
+
+    // a tile's element r of a lane is (sample 16 t + 4 q + r, unit 16 nt + r16)
+    uint32_t pos1 = 0, pos2 = 0;  // which hidden values are positive, bit 4 nt + r
+    auto put = [&](__bf16* rows, __bf16* cols, int nt, const bf16x4& v) {
+        if (rows)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) rows[(16 * t + 4 * q + r) * kRow + 16 * nt + r16] = v[r];
+        *(bf16x4*)(cols + (16 * nt + r16) * kRow + 16 * t + 4 * q) = v;
+    };
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const f32x4 d = mfma(x, w1[nt], none);
+        bf16x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = (__bf16)act(d[r] + b1[nt]);
+            pos1 |= (float)v[r] > 0.0f ? 1u << (4 * nt + r) : 0u;
+        }
+        put(H1, H1t, nt, v);
+    }
     wave_sync();
-    forward64(X, H, H1, O, sm.w1t, sm.w2t, sm.w3t, sm.b1, sm.b2, sm.b3);
-    // output gradient
     {
-        const float g0 = valid ? 2.0f * (O[lane * kOut] - y0) : 0.0f;
-        const float g1 = valid ? 2.0f * (O[lane * kOut + 1] - y1) : 0.0f;
-#pragma unroll
-        for (int k = 0; k < 32; ++k) DO[lane * 32 + k] = (__bf16)(k == 0 ? g0 : (k == 1 ? g1 : 0.0f));
-    }
-    wave_sync();
-    float* P = a.partial + (size_t)blockIdx.x * kNParams;
-    // dW3[k][n] = sum_s H2[s][k] dO[s][n]   (M = 64 k, N = 16 n, K = 64 s)
-    for (int t = 0; t < 4; ++t) {
-        const f32x4 d = tile_mm(H, 1, kHid, DO, 32, 1, 16 * t, 0, 64);
-        if (r16 < kOut)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) P[kW3 + (16 * t + 4 * q + r) * kOut + r16] = d[r];
-    }
-    // dz2 = (dO W3^T) * [H2 > 0]               (M = 64 s, N = 64 k, K = 32 n)
-    for (int t = 0; t < 4; ++t)
+        const bf16x8 h0 = row8(H1, 16 * t + r16, 8 * q), h1 = row8(H1, 16 * t + r16, 32 + 8 * q);
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
-            const f32x4 d = tile_mm(DO, 32, 1, w3pad, kHid, 1, 16 * t, 16 * nt, 32);
+            const f32x4 d = mfma(h1, w2[nt][1], mfma(h0, w2[nt][0], none));
+            bf16x4 v;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = 16 * t + 4 * q + r, col = 16 * nt + r16;
-                const float h = (float)H[row * kHid + col];
-                D2[row * kHid + col] = (__bf16)(h > 0.0f ? d[r] : 0.0f);
+                v[r] = (__bf16)act(d[r] + b2[nt]);
+                pos2 |= (float)v[r] > 0.0f ? 1u << (4 * nt + r) : 0u;
             }
+            put(H2, H2t, nt, v);
         }
+    }
     wave_sync();
-    // dW2[k][n] = sum_s H1[s][k] dz2[s][n]     (M = 64, N = 64, K = 64)
-    for (int t = 0; t < 4; ++t)
+    {
+        const bf16x8 h0 = row8(H2, 16 * t + r16, 8 * q), h1 = row8(H2, 16 * t + r16, 32 + 8 * q);
+        const f32x4 d = mfma(h1, w3[1], mfma(h0, w3[0], none));
+        // output gradient
+        if (r16 < kOut) {
+            bf16x4 g;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int sl = 16 * t + 4 * q + r;
+                g[r] = (__bf16)(blockIdx.x * 64u + (uint32_t)sl < a.count ? 2.0f * ((d[r] + b3) - y[r]) : 0.0f);
+                DO[sl * kOut + r16] = g[r];
+            }
+            *(bf16x4*)(DOt + r16 * kRow + 16 * t + 4 * q) = g;
+        }
+    }
+    wave_sync();
+    // dz2 = (dO W3^T) * [H2 > 0]
+    {
+        bf16x8 g = zero8();
+        if (q == 0) {
+            g[0] = DO[(16 * t + r16) * kOut];
+            g[1] = DO[(16 * t + r16) * kOut + 1];
+        }
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
-            const f32x4 d = tile_mm(H1, 1, kHid, D2, kHid, 1, 16 * t, 16 * nt, 64);
+            const f32x4 d = mfma(g, w3b[nt], none);
+            bf16x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (__bf16)((pos2 >> (4 * nt + r)) & 1u ? d[r] : 0.0f);
+            put(H2, D2t, nt, v);
+        }
+    }
+    wave_sync();
+    // dz1 = (dz2 W2^T) * [H1 > 0]
+    {
+        const bf16x8 h0 = row8(H2, 16 * t + r16, 8 * q), h1 = row8(H2, 16 * t + r16, 32 + 8 * q);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const f32x4 d = mfma(h1, w2b[nt][1], mfma(h0, w2b[nt][0], none));
+            bf16x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (__bf16)((pos1 >> (4 * nt + r)) & 1u ? d[r] : 0.0f);
+            put(nullptr, D1t, nt, v);
+        }
+    }
+    __syncthreads();
+    // weight gradients over the 64 samples, rows 16 t .. 16 t + 15 of each matrix
+    float* P = a.partial + (size_t)blockIdx.x * kNParams;
+    {
+        // dW2[k][n] = sum_s H1[s][k] dz2[s][n]
+        const bf16x8 h0 = row8(H1t, 16 * t + r16, 8 * q), h1 = row8(H1t, 16 * t + r16, 32 + 8 * q);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const f32x4 d = mfma(h1, row8(D2t, 16 * nt + r16, 32 + 8 * q), mfma(h0, row8(D2t, 16 * nt + r16, 8 * q), none));
 #pragma unroll
             for (int r = 0; r < 4; ++r) P[kW2 + (16 * t + 4 * q + r) * kHid + 16 * nt + r16] = d[r];
         }
-    // dz1 = (dz2 W2^T) * [H1 > 0]              (M = 64 s, N = 64 k, K = 64 n)
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const f32x4 d = tile_mm(D2, kHid, 1, sm.w2t, kHid, 1, 16 * t, 16 * nt, 64);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * t + 4 * q + r, col = 16 * nt + r16;
-                const float h = (float)H1[row * kHid + col];
-                D1[row * kHid + col] = (__bf16)(h > 0.0f ? d[r] : 0.0f);
-            }
-        }
-    wave_sync();
-    // dW1[k][n] = sum_s X[s][k] dz1[s][n]      (M = 16 k (5 used), N = 64, K = 64)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const f32x4 d = tile_mm(X, 1, kK1, D1, kHid, 1, 0, 16 * nt, 64);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int k = 4 * q + r;
-            if (k < kIn) P[kW1 + k * kHid + 16 * nt + r16] = d[r];
-        }
     }
-    // bias gradients: column sums
     {
-        float s1 = 0.0f, s2 = 0.0f;
-        for (int s = 0; s < 64; ++s) {
-            s1 += (float)D1[s * kHid + lane];
-            s2 += (float)D2[s * kHid + lane];
+        // dW3[k][n] = sum_s H2[s][k] dO[s][n]
+        const bool on = r16 < kOut;
+        const bf16x8 g0 = on ? row8(DOt, r16, 8 * q) : zero8(), g1 = on ? row8(DOt, r16, 32 + 8 * q) : zero8();
+        const f32x4 d = mfma(row8(H2t, 16 * t + r16, 32 + 8 * q), g1, mfma(row8(H2t, 16 * t + r16, 8 * q), g0, none));
+        if (on)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) P[kW3 + (16 * t + 4 * q + r) * kOut + r16] = d[r];
+    }
+    {
+        // dW1[k][n] = sum_s X[s][k] dz1[s][n], columns 16 t .. 16 t + 15
+        const bool on = r16 < kIn;
+        const bf16x8 x0 = on ? row8(Xt, r16, 8 * q) : zero8(), x1 = on ? row8(Xt, r16, 32 + 8 * q) : zero8();
+        const f32x4 d = mfma(x1, row8(D1t, 16 * t + r16, 32 + 8 * q), mfma(x0, row8(D1t, 16 * t + r16, 8 * q), none));
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * q + r < kIn) P[kW1 + (4 * q + r) * kHid + 16 * t + r16] = d[r];
+    }
+    // bias gradients: sums over the samples, in their order
+    if (t < 2 || (t == 2 && lane < kOut)) {
+        const __bf16* m = t == 0 ? D1t : (t == 1 ? D2t : DOt);
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 64; k += 8) {
+            const bf16x8 v = row8(m, lane, k);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum += (float)v[i];
         }
-        P[kB1 + lane] = s1;
-        P[kB2 + lane] = s2;
-        if (lane < kOut) {
-            float s3 = 0.0f;
-            for (int s = 0; s < 64; ++s) s3 += (float)DO[s * 32 + lane];
-            P[kB3 + lane] = s3;
-        }
+        P[(t == 0 ? kB1 : (t == 1 ? kB2 : kB3)) + lane] = sum;
     }
 }
 
 hipError_t launch_train_grad(const TrainArgs& a, hipStream_t s)
 {
-    const unsigned waves = (a.count + 63) / 64;
-    k_train_grad<<<waves, 64, 0, s>>>(a);
+    k_train_grad<<<(a.count + 63) / 64, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
-__global__ void k_adam(AdamArgs a)
+// BF16 image or bias of parameter p in the model.
+__device__ __forceinline__ void publish_param(Model* M, int p, float v)
+{
+    if (p < kB1) {
+        M->w1t[p % kHid][p / kHid] = (__bf16)v;
+    } else if (p < kW2) {
+        M->b1[p - kB1] = v;
+    } else if (p < kB2) {
+        M->w2t[(p - kW2) % kHid][(p - kW2) / kHid] = (__bf16)v;
+    } else if (p < kW3) {
+        M->b2[p - kB2] = v;
+    } else if (p < kB3) {
+        M->w3t[(p - kW3) % kOut][(p - kW3) / kOut] = (__bf16)v;
+    } else {
+        M->b3[p - kB3] = v;
+    }
+}
+
+// Sums the partial gradients in their order, updates, and publishes the parameter's image (a
+// launch of its own before). 64 threads a workgroup: 77 of them share the latencies.
+__global__ __launch_bounds__(64) void k_adam(AdamArgs a)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= kNParams) return;
+    const float m0 = a.m[p], v0 = a.v[p], w0 = a.params[p];
     float g = 0.0f;
-    for (int w = 0; w < a.nwaves; ++w) g += a.partial[(size_t)w * kNParams + p];
+    int w = 0;
+    for (; w + 8 <= a.nwaves; w += 8) {
+        float part[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) part[i] = a.partial[(size_t)(w + i) * kNParams + p];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) g += part[i];
+    }
+    for (; w < a.nwaves; ++w) g += a.partial[(size_t)w * kNParams + p];
     g *= a.inv_batch;
-    const float m = a.beta1 * a.m[p] + (1.0f - a.beta1) * g;
-    const float v = a.beta2 * a.v[p] + (1.0f - a.beta2) * g * g;
+    const float m = a.beta1 * m0 + (1.0f - a.beta1) * g;
+    const float v = a.beta2 * v0 + (1.0f - a.beta2) * g * g;
     a.m[p] = m;
     a.v[p] = v;
     const float mh = m / (1.0f - powf(a.beta1, (float)a.step));
     const float vh = v / (1.0f - powf(a.beta2, (float)a.step));
-    a.params[p] -= a.lr * mh / (sqrtf(vh) + a.eps);
+    const float wn = w0 - a.lr * mh / (sqrtf(vh) + a.eps);
+    a.params[p] = wn;
+    publish_param(a.model, p, wn);
 }
 
+// Every image from the master parameters, the padding's zeros among them (before training).
 __global__ void k_publish(const float* P, Model* M)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHid * kHid; i += gridDim.x * blockDim.x) {
@@ -688,10 +719,8 @@ __global__ void k_publish(const float* P, Model* M)
 
 hipError_t launch_adam(const AdamArgs& a, hipStream_t s)
 {
-    k_adam<<<(kNParams + 255) / 256, 256, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_publish(a.params, a.model, s);
+    k_adam<<<(kNParams + 63) / 64, 64, 0, s>>>(a);
+    return hipGetLastError();
 }
 
 hipError_t launch_publish(const float* params, Model* model, hipStream_t s)

@@ -221,7 +221,7 @@ arc_status arc_mlp_train(arc_ctx* ctx, arc_mlp* mlp, const float* X, const float
         TRY(hipStreamSynchronize(st));  // train is reshuffled next epoch
         for (size_t first = 0; first < n_train; first += batch) {
             const uint32_t count = (uint32_t)std::min<size_t>(batch, n_train - first);
-            TrainArgs ta{mlp->model, F, Yt, idx, (uint32_t)first, count, partial};
+            TrainArgs ta{mlp->model, mlp->params, F, Yt, idx, (uint32_t)first, count, partial};
             TRY(launch_train_grad(ta, st));
             AdamArgs aa{};
             aa.params = mlp->params;
