@@ -288,11 +288,11 @@ __device__ __forceinline__ void record_tree(const TraceArgs& A, uint32_t src, ui
 // optically thin approximation (THIN, section 2.6) a ray starts no closer than its source's
 // thin radius; a ray whose split radius does not lie beyond that start splits at once (it is
 // returned active with thi >= tend and crosses nothing).
-// Returns false (and books the escape's photons; the caller counts it) when the start point lies
-// outside the grid.
+// Returns false (and books the escape's photons; the caller counts it and, with THIN, books the
+// bound `reach`) when the start point lies outside the grid.
 template <int NB, bool THIN, class Rec>
 __device__ __forceinline__ bool ray_init(const TraceArgs& A, const Terms& terms, const Rec& r, Ray<NB>& ray,
-                                         WaveStats& st)
+                                         WaveStats& st, float& reach)
 {
     ray.src = r.src;
     ray.lp = r.lp;
@@ -346,7 +346,7 @@ __device__ __forceinline__ bool ray_init(const TraceArgs& A, const Terms& terms,
         }
         // a ray that starts outside the grid while still thin bounds the thin radius by its start
         if constexpr (THIN)
-            if (ts < kTauThin) atomicMin(A.r_out + ray.src, __float_as_uint(t0));
+            if (ts < kTauThin) reach = t0;
     }
     return inside;
 }
@@ -550,14 +550,29 @@ __device__ __forceinline__ int geom_next(const TraceArgs& A, const Terms& terms,
 
 // Section 2.6: the least path length at which the ray's depth in the softest bin reaches
 // kTauThin, within this segment (ts: depth at its start, dts: its increment, ks: its
-// opacity), bounds the source's thin radius (one atomic per ray at most).
-template <int NB>
-__device__ __forceinline__ void thin_reach(const TraceArgs& A, const Ray<NB>& ray, const Seg& sg, float ts, float dts,
-                                           float ks)
+// opacity), bounds the source's thin radius.
+__device__ __forceinline__ void thin_reach(const Seg& sg, float ts, float dts, float ks, float& reach)
 {
-    if (ts < kTauThin && ts + dts >= kTauThin) {
-        const float rc = (sg.t1 - sg.ds) + (kTauThin - ts) / ks;
-        atomicMin(A.r_out + ray.src, __float_as_uint(rc));
+    if (ts < kTauThin && ts + dts >= kTauThin) reach = (sg.t1 - sg.ds) + (kTauThin - ts) / ks;
+}
+
+// Bounds of the wave's lanes (+inf: none) on their sources' thin radii. Called by all 64 lanes.
+// Atomics on one word go one after the other, and every ray of a source has one: the lanes of a
+// source (mostly all of them) are reduced first, and a bound that the word already holds is
+// dropped (a stale read of it is only larger). 128^3 x 32 sources: the levels before the
+// persistent launch 870 us with an atomic per ray.
+__device__ __forceinline__ void thin_bounds(const TraceArgs& A, uint32_t src, float reach)
+{
+    uint64_t left;
+    while ((left = __builtin_amdgcn_ballot_w64(reach < INFINITY)) != 0) {
+        const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)src, __builtin_ctzll(left));
+        float m = src == s ? reach : INFINITY;
+        for (int off = 32; off > 0; off >>= 1) m = fminf(m, __shfl_xor(m, off, 64));
+        if ((threadIdx.x & 63) == 0) {
+            const uint32_t bits = __float_as_uint(m);
+            if (bits < __hip_atomic_load(A.r_out + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(A.r_out + s, bits);
+        }
+        if (src == s) reach = INFINITY;
     }
 }
 
@@ -591,7 +606,7 @@ __device__ __forceinline__ uint32_t live_bins(const Ray<NB>& ray, bool active, c
 // the ray terminates here.
 template <int NB, int PREC, bool THIN>
 __device__ __forceinline__ bool attenuate_seg(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
-                                              uint32_t live, float v[NB], float (&T)[NB])
+                                              uint32_t live, float v[NB], float (&T)[NB], float& reach)
 {
     float ts = 0.0f, dts = 0.0f, ks = 1.0f;
     float dtau[NB], taup[NB];
@@ -640,7 +655,7 @@ __device__ __forceinline__ bool attenuate_seg(const TraceArgs& A, Ray<NB>& ray, 
         // termination: absorb what is left in this cell, field += remaining photons / opacity
         if (term) v[b] = __builtin_fmaf(ray.w[b] * Tn, rk, v[b]);
     }
-    if constexpr (THIN) thin_reach<NB>(A, ray, sg, ts, dts, ks);
+    if constexpr (THIN) thin_reach(sg, ts, dts, ks, reach);
     return term;
 }
 
@@ -655,7 +670,7 @@ __device__ __forceinline__ void ray_transmission(const Ray<NB>& ray, float (&T)[
 // A lane's event of the pass into the wave's counts; the photons an escaping lane carried out of
 // the grid go into the FP64 ledger.
 template <int NB, int PREC, bool THIN>
-__device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ray<NB>& ray, WaveStats& st)
+__device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ray<NB>& ray, float reach, WaveStats& st)
 {
     st.splits += count_lanes(ev == kSplit);
     st.terminated += count_lanes(ev == kTerminate);
@@ -671,9 +686,10 @@ __device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ra
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (b == A.ksoft) tsp = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
-            if (tsp < kTauThin) atomicMin(A.r_out + ray.src, __float_as_uint(ray.thi));
+            if (tsp < kTauThin) reach = ray.thi;
         }
     }
+    if constexpr (THIN) thin_bounds(A, ray.src, reach);
 }
 
 // Limbs of the moved-photon field: mv = hi 2^20 + lo 2^-12 (units of u_J,b). A crossing's lo
@@ -713,10 +729,10 @@ constexpr float kMovedRatioJ = 16.0f;
 template <int NB, int PREC, bool THIN>
 __device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
                                                  const float kapn[NB], uint32_t live, Dep<NB>& dep, Dep<NB>& dj,
-                                                 Dep<NB>& dm, bool& use_j, bool& use_m, float (&T)[NB])
+                                                 Dep<NB>& dm, bool& use_j, bool& use_m, float (&T)[NB], float& reach)
 {
     float v[NB];
-    const bool term = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, live, v, T);
+    const bool term = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, live, v, T, reach);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (!(live & (1u << b))) continue;
@@ -797,10 +813,11 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
     // issued before an unknown number of atomics would wait for all of them)
     static_assert(K % kDepWindow == 0, "whole windows per pass");
     Dep<NB> dep[K];
+    float reach = INFINITY;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         dep[j].cell = sg[j].cell;
-        if (j < nseg && attenuate_seg<NB, PREC, THIN>(A, ray, sg[j], kap[j], live, dep[j].v, T)) {
+        if (j < nseg && attenuate_seg<NB, PREC, THIN>(A, ray, sg[j], kap[j], live, dep[j].v, T, reach)) {
             nseg = j + 1;
             ev = kTerminate;
         }
@@ -813,7 +830,7 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
         for (int w = 0; w < kDepWindow; ++w) on[w] = j0 + w < nseg;
         deposit.template add<kWhole, kDepWindow>(dep + j0, on, live, A.J, NB);
     }
-    book_events<NB, PREC, THIN>(A, ev, ray, st);
+    book_events<NB, PREC, THIN>(A, ev, ray, reach, st);
     return ev;
 }
 
@@ -859,13 +876,14 @@ __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& 
     const uint32_t live = live_bins<NB>(ray, active, T, kLiveMinCorr);
     Dep<NB> dep[K], dj[K], dm[K];
     bool use_j[K], use_m[K];
+    float reach = INFINITY;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         use_j[j] = use_m[j] = false;
         dep[j].cell = sg[j].cell;
         dj[j].cell = dm[j].cell = sg[j].nb != kNoCell ? sg[j].nb : 0u;
         if (j < nseg && deposit_seg_corr<NB, PREC, THIN>(A, ray, sg[j], kap[j], kapn[j], live, dep[j], dj[j], dm[j],
-                                                         use_j[j], use_m[j], T)) {
+                                                         use_j[j], use_m[j], T, reach)) {
             nseg = j + 1;
             ev = kTerminate;
         }
@@ -887,7 +905,7 @@ __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& 
             deposit.template add<kMovedLo, kDepWindowCorr>(dm + j, onm, live, A.M + 8 * NB, 2 * NB);
         }
     }
-    book_events<NB, PREC, THIN>(A, ev, ray, st);
+    book_events<NB, PREC, THIN>(A, ev, ray, reach, st);
     return ev;
 }
 

@@ -428,11 +428,13 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
         int ev = kEscape;
         Ray<NB> ray;
         bool act = false;
+        float reach = INFINITY;
         if (i < n_in) {
             const RayRec r = in[i];
             record_tree<NB>(A, r.src, r.lp);
-            act = ray_init<NB, THIN>(A, terms, r, ray, st);
+            act = ray_init<NB, THIN>(A, terms, r, ray, st, reach);
         }
+        if constexpr (THIN) thin_bounds(A, ray.src, reach);
         st.rays += count_lanes(i < n_in);
         st.escaped += count_lanes(i < n_in && !act);
         // a few crossings per lane per pass; the wave deposits each crossing together
@@ -659,10 +661,12 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
                 }
             }
         }
+        float reach = INFINITY;
         if (got) {
             record_tree<NB>(A, r.src, r.lp);
-            has = ray_init<NB, THIN>(A, terms, r, ray, st);
+            has = ray_init<NB, THIN>(A, terms, r, ray, st, reach);
         }
+        if constexpr (THIN) thin_bounds(A, ray.src, reach);
         st.rays += count_lanes(got);
         st.escaped += count_lanes(got && !has);
         if (!__any(has) && top == 0 && nspill == 0 && qdone) break;
