@@ -581,13 +581,17 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
 // from 1.4e8 to 4e5). Lowered while the larger ray buffer would exceed item_bytes.
 constexpr int kDefaultItemDepth = 5;
 
-// Default refill threshold of the persistent launch: a wave refills once 48 of its lanes are
-// idle, so that many rays, mostly children of the same splits, start together and their merged
-// deposits make fewer atomics (1024^3 x 16384 sources from the generated state, merge windows
-// of two segments: refill at 32, 48 and 64 idle lanes, 0.283, 0.273 and 0.261 deposit items per
-// crossing, 744, 718 and 712 ms; windows of four: 48 and 64, 686 and 696 ms, the wider merge
-// costing more issue per crossing than the last atomics it saves).
-constexpr int kDefaultRefill = 48;
+// Default refill threshold of the persistent launch: a wave refills once 40 of its lanes are
+// idle, so that many rays, mostly children of the same splits, start together and share the
+// tiles of their deposits (256^3 x 1024 sources: refill at 32, 40, 48 and 64 idle lanes 24.9,
+// 24.3, 24.3 and 25.6 ms; 128^3 x 16 sources, where idle lanes cost more, 40 beats 48 by 2%).
+constexpr int kDefaultRefill = 40;
+
+// Default grid of the persistent launch: the waves that are resident at once. Their first work
+// items are theirs by their place in the grid, so a wave that has to wait for another's end would
+// start its items late (128^3 x 16 sources, three waves per SIMD: 768 workgroups of four waves
+// 0.53 ms, 1024 0.63 ms).
+int default_waves_per_cu(int nb) { return 4 * persistent_waves_per_simd(nb); }
 
 // Default depth of each wave's LDS stack: 64 split rays (2 KB), a full split round of the
 // wave; deeper stacks spill less but hold fewer waves per compute unit.
@@ -932,7 +936,7 @@ arc_status arc_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const 
     hipStream_t st = (hipStream_t)p->stream;
     if (p->schedule == ARC_SCHED_BATCHED) {
         const int waves = p->tune_waves > 0 ? p->tune_waves : 4;
-        const int blocks = p->tune_blocks > 0 ? p->tune_blocks : std::max(1, c->cus * (16 / std::max(1, waves)));
+        const int blocks = p->tune_blocks > 0 ? p->tune_blocks : std::max(1, c->cus * default_waves_per_cu(P.nb) / std::max(1, waves));
         const int refill = p->tune_refill > 0 ? p->tune_refill : kDefaultRefill;
         const int stack = p->tune_stack > 0 ? p->tune_stack : kDefaultStack;
         if ((rc = shape_batched(c, P, waves, blocks, refill, p->tune_item_level, stack)) != ARC_OK)
@@ -1027,7 +1031,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
     };
     arc_tune_result best{};
     best.waves = 4;
-    best.waves_per_cu = 16;
+    best.waves_per_cu = default_waves_per_cu(P.nb);
     best.refill = kDefaultRefill;
     best.stack = kDefaultStack;
     best.item_delta = kDefaultItemDepth;
@@ -1066,7 +1070,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
         }
     // (3) refill threshold
     const arc_tune_result base3 = best;
-    for (int rf : {16, 32, 56, 64}) {
+    for (int rf : {16, 32, 48, 56, 64}) {
         if (rf == base3.refill) continue;
         arc_tune_result t = base3;
         t.refill = rf;

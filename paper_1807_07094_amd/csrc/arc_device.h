@@ -139,17 +139,15 @@ struct TraceArgs {
 constexpr float kTauThin = 0.1f;  // optical depth that bounds the optically thin sphere
 
 // The blocked cell index is the sum of one term per axis. Every workgroup that traces keeps the
-// terms of the three axes in LDS (nx + ny + nz words, axis after axis), and a ray carries the
-// addresses of its cell's three entries: a step moves one address, and the index costs three LDS
-// reads and an add (computing a term takes ten VALU instructions, which bound the trace).
+// terms of the three axes in LDS, axis after axis, each between two entries that stand for
+// "outside the grid" (nx + ny + nz + 6 words), and a ray carries the addresses of its cell's three
+// entries: a step moves one address, and the index costs three LDS reads and an add (computing
+// a term takes ten VALU instructions, which bound the trace).
 typedef const volatile kLds char* TermAddr;
+constexpr uint32_t kOutside = 0x80000000u;  // indices are below 2^31
 
 struct Terms {
     TermAddr base[3];      // entry of coordinate 0 along each axis
-    __device__ __forceinline__ bool inside(int i, TermAddr p, int n) const
-    {
-        return (uint32_t)(p - base[i]) < 4u * (uint32_t)n;
-    }
 };
 
 __device__ __forceinline__ uint32_t term_at(TermAddr p) { return *(const volatile kLds uint32_t*)p; }
@@ -172,16 +170,23 @@ struct Ray {
     uint32_t src, lp;
 };
 
-// Counts of a wave (wave-uniform, from ballots) and, per lane, crossings and photons lost.
+// Counts of a wave (wave-uniform, from ballots), its lanes' crossings, and the photons they
+// carried out of the grid, in LDS (the registers are worth more: they bound the occupancy).
 struct WaveStats {
     unsigned long long rays, splits, terminated, escaped;
     uint32_t crossings;    // per lane
-    double esc[kMaxBins];  // per lane
-    __device__ void clear()
+    kLds double* esc;      // [kMaxBins]
+    __device__ void clear(kLds double* lds)
     {
         rays = splits = terminated = escaped = 0;
         crossings = 0;
-        for (int b = 0; b < kMaxBins; ++b) esc[b] = 0.0;
+        esc = lds;
+        if ((threadIdx.x & 63) < kMaxBins) esc[threadIdx.x & 63] = 0.0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __device__ __forceinline__ void lose(int b, double photons)
+    {
+        __hip_atomic_fetch_add(esc + b, photons, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
 };
 
@@ -245,16 +250,20 @@ __device__ __forceinline__ uint32_t axis_term(const TraceArgs& A, int i, int v)
     return blk9 * (((uint32_t)A.nbx8 * (uint32_t)A.nby8) & 0x1FFFFu) + m;
 }
 
-// Fills the workgroup's table of index terms (nx + ny + nz words at `table`); all threads of the
-// workgroup call it, and a barrier follows before the first use.
+// Fills the workgroup's table of index terms (nx + ny + nz + 6 words at `table`); all threads of
+// the workgroup call it, and a barrier follows before the first use.
 __device__ __forceinline__ Terms make_terms(const TraceArgs& A, uint32_t* table)
 {
-    for (int k = threadIdx.x; k < A.nx + A.ny + A.nz; k += blockDim.x)
-        table[k] = k < A.nx ? axis_term(A, 0, k) : (k < A.nx + A.ny ? axis_term(A, 1, k - A.nx) : axis_term(A, 2, k - A.nx - A.ny));
     Terms t;
-    t.base[0] = (TermAddr)table;
-    t.base[1] = t.base[0] + 4 * A.nx;
-    t.base[2] = t.base[1] + 4 * A.ny;
+    const int n[3] = {A.nx, A.ny, A.nz};
+    int from = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        for (int k = (int)threadIdx.x - 1; k <= n[i]; k += (int)blockDim.x)
+            table[from + 1 + k] = k < 0 || k == n[i] ? kOutside : axis_term(A, i, k);
+        t.base[i] = (TermAddr)(table + from + 1);
+        from += n[i] + 2;
+    }
     return t;
 }
 
@@ -341,7 +350,7 @@ __device__ __forceinline__ bool ray_init(const TraceArgs& A, const Terms& terms,
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const float tb = ray.tau[b] + ray.taulo[b];
-            st.esc[b] += (double)ray.w[b] * (double)transmission(tb);
+            st.lose(b, (double)ray.w[b] * (double)transmission(tb));
             if (b == A.ksoft) ts = tb;
         }
         // a ray that starts outside the grid while still thin bounds the thin radius by its start
@@ -388,8 +397,7 @@ constexpr double kFaceTie = 1e-9;
 // FP64 from the exact boundary numerators; faces within kFaceTie count as tied, and ties go
 // to the lower axis, then the lower face.
 template <int NB>
-__device__ __forceinline__ void geom_correction(const TraceArgs& A, const Terms& terms, const Ray<NB>& ray, float nhi,
-                                                float nlo, Seg& sg)
+__device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB>& ray, float nhi, float nlo, Seg& sg)
 {
     sg.nb = kNoCell;
     sg.fc = 1.0f;
@@ -419,20 +427,12 @@ __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Terms&
     float fc = 0.5f + (float)dmin * __builtin_amdgcn_rcpf((float)lpix);
     if (A.corr == 3) fc *= fc;
     if (A.corr == 2) {
-        // the neighbour's per-axis term replaces the cell's along `axis` (static indices only:
-        // a runtime index into the ray's arrays would move them to scratch memory)
-        bool inside = true;
-        TermAddr oc = ray.o[0], on = ray.o[0];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            if (i == axis) {
-                oc = ray.o[i];
-                on = oc + 4 * side;
-                inside = terms.inside(i, on, i == 0 ? A.nx : (i == 1 ? A.ny : A.nz));
-            }
-        }
-        if (!inside) return;  // no neighbour inside: the cell keeps everything
-        sg.nb = sg.cell - term_at(oc) + term_at(on);
+        // the neighbour's per-axis term replaces the cell's along `axis`
+        const TermAddr o0 = ray.o[0], o1 = ray.o[1], o2 = ray.o[2];
+        const TermAddr oc = axis == 0 ? o0 : (axis == 1 ? o1 : o2);
+        const uint32_t there = term_at(oc + 4 * side);
+        if (there & kOutside) return;  // no neighbour inside: the cell keeps everything
+        sg.nb = sg.cell - term_at(oc) + there;
     }
     sg.fc = fc;
 }
@@ -447,8 +447,9 @@ __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Terms&
 // says whether any comparison is that close. The split radius and the grid's walls are looked
 // at only within 2e-6 of the nearer of them (tlim): a boundary met before that is neither, so
 // an ordinary step is about thirty instructions (a bundle's lanes reach their ends together).
+// `term` receives the cell's index terms, whose sum the caller forms later (they come from LDS).
 template <int NB, int PREC, bool CORR = false>
-__device__ __forceinline__ int geom_next(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, Seg& sg)
+__device__ __forceinline__ int geom_next(const TraceArgs& A, Ray<NB>& ray, Seg& sg, uint32_t (&term)[3])
 {
     constexpr float kNear = 1.000001f;
     // values of their own: a select between members of the ray is turned into an indexed access
@@ -495,41 +496,46 @@ __device__ __forceinline__ int geom_next(const TraceArgs& A, const Terms& terms,
             at_end = ray.tend <= tw;
         }
     }
-    sg.cell = term_at(ray.o[0]) + term_at(ray.o[1]) + term_at(ray.o[2]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) term[i] = term_at(ray.o[i]);
+    if constexpr (CORR) sg.cell = term[0] + term[1] + term[2];
     // next path length as a double-float: the low part from the lowest crossed axis. With the
     // correction the position must not move before its distances are taken.
     float nhi = tw, nlo = 0.0f;
-    if constexpr (PREC == 0) {
-        if (m2) nlo = __builtin_fmaf(-tw, e2, a2) * ray.ie[2];
-        if (m1) nlo = __builtin_fmaf(-tw, e1, a1) * ray.ie[1];
-        if (m0) nlo = __builtin_fmaf(-tw, e0, a0) * ray.ie[0];
-    }
+    auto low = [&](int i) { return __builtin_fmaf(-tw, ray.e[i], ray.a[i]) * ray.ie[i]; };
     if constexpr (CORR) {
-        const float chi = at_end ? ray.tend : nhi, clo = at_end ? 0.0f : nlo;
-        geom_correction(A, terms, ray, chi, clo, sg);
+        if (m2) nlo = low(2);
+        if (m1) nlo = low(1);
+        if (m0) nlo = low(0);
+        geom_correction(A, ray, at_end ? ray.tend : nhi, at_end ? 0.0f : nlo, sg);
     }
+    // one axis after the other under its own lanes (branches, not selects: half the instructions)
     if (m2) {
         asm volatile("");
+        if constexpr (PREC == 0 && !CORR) nlo = low(2);
         ray.a[2] += 1.0f;
         ray.o[2] += ray.step[2];
     }
     if (m1) {
         asm volatile("");
+        if constexpr (PREC == 0 && !CORR) nlo = low(1);
         ray.a[1] += 1.0f;
         ray.o[1] += ray.step[1];
     }
     if (m0) {
         asm volatile("");
+        if constexpr (PREC == 0 && !CORR) nlo = low(0);
         ray.a[0] += 1.0f;
         ray.o[0] += ray.step[0];
     }
     int ev = kContinue;
     if (lim) {
+        asm volatile("");
         if (at_end) {
             nhi = ray.tend;
             nlo = 0.0f;
             ev = kSplit;
-        } else if (!(terms.inside(0, ray.o[0], A.nx) && terms.inside(1, ray.o[1], A.ny) && terms.inside(2, ray.o[2], A.nz))) {
+        } else if ((term_at(ray.o[0]) | term_at(ray.o[1]) | term_at(ray.o[2])) & kOutside) {
             ev = kEscape;
         }
     }
@@ -595,6 +601,20 @@ __device__ __forceinline__ uint32_t live_bins(const Ray<NB>& ray, bool active, c
     return live;
 }
 
+// The hardware's maximum and minimum, without the canonicalisation that fmaxf and fminf add.
+__device__ __forceinline__ float max_raw(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float min_raw(float a, float b)
+{
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // Photons of one segment (section 2.4, eq:ion per bin): the amount v_b = S ds g(dtau) for the
 // cell in field units, attenuation (compensated tau), then the termination test (a
 // terminating crossing adds the rest of the photons, S / kappa, to v_b) and, with THIN, the
@@ -622,9 +642,9 @@ __device__ __forceinline__ bool attenuate_seg(const TraceArgs& A, Ray<NB>& ray, 
         }
         if constexpr (PREC == 0) {
             // the sum's rounding error, exact from the larger of the two terms
-            const float s = ray.tau[b] + dtau[b];
-            ray.taulo[b] += fminf(ray.tau[b], dtau[b]) - (s - fmaxf(ray.tau[b], dtau[b]));
-            ray.tau[b] = s;
+            const float hi = max_raw(ray.tau[b], dtau[b]), lo = min_raw(ray.tau[b], dtau[b]);
+            ray.tau[b] = hi + lo;
+            ray.taulo[b] += lo - (ray.tau[b] - hi);
         } else {
             ray.tau[b] += dtau[b];
         }
@@ -652,8 +672,15 @@ __device__ __forceinline__ bool attenuate_seg(const TraceArgs& A, Ray<NB>& ray, 
         const float lost = (ray.w[b] * (T[b] - Tn)) * rk;
         v[b] = x < 0.25f ? series : lost;
         T[b] = Tn;
-        // termination: absorb what is left in this cell, field += remaining photons / opacity
-        if (term) v[b] = __builtin_fmaf(ray.w[b] * Tn, rk, v[b]);
+    }
+    if (term) {
+        asm volatile("");
+        // absorb what is left in this cell: field += remaining photons / opacity
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (!(live & (1u << b))) continue;
+            v[b] = __builtin_fmaf(ray.w[b] * T[b], __builtin_amdgcn_rcpf(kap[b]), v[b]);
+        }
     }
     if constexpr (THIN) thin_reach(sg, ts, dts, ks, reach);
     return term;
@@ -679,7 +706,7 @@ __device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ra
         float T[NB];
         ray_transmission<NB, PREC>(ray, T);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) st.esc[b] += (double)(ray.w[b] * T[b]);
+        for (int b = 0; b < NB; ++b) st.lose(b, (double)(ray.w[b] * T[b]));
         // a ray that leaves the grid while still thin bounds the thin radius by its exit
         if constexpr (THIN) {
             float tsp = 0.0f;
@@ -760,27 +787,27 @@ __device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ra
 }
 
 // Segments whose geometry is computed ahead of their deposits (opacity loads in flight per
-// lane), and segments of each lane whose deposits the wave merges together. VALU issue bounds the
-// trace (90% at 256^3 x 1024 sources: 3.9 wave-instructions per crossing, 46 of 64 lanes active),
-// so both are flat over a wide range there (persistent launch, ms; lines per crossing): twelve
-// ahead with windows of 4, 6 and 12: 29.9, 29.0 and 29.6; 0.116, 0.103 and 0.090; eight ahead
-// with windows of 4 and 8: 30.2 and 29.3. Wider windows make fewer lines, but more of their
-// tiles want the same table entry. With the geometric correction two opacities per segment leave
-// room for four.
-constexpr int kSegAhead = 12;
-constexpr int kDepWindow = 6;
+// lane), all deposited in one merge window. The trace is a long mix of VALU, scalar, LDS and
+// branch instructions per wave, so what counts beside their number is how many waves a SIMD has
+// to fill the gaps: eight ahead fit the 128 registers of four waves. 256^3 x 1024 sources,
+// persistent launch: three waves and twelve ahead 28.9 ms; four waves and eight ahead with
+// windows of eight 24.3 (0.096 field lines per crossing), of four 24.9 (0.115); six ahead 25.0,
+// five 25.9; five waves and four ahead spill registers, 35. The extra state of thin spheres leaves
+// room for six, the two opacities per segment of the geometric correction for four.
+constexpr int kSegAhead = 8;
+constexpr int kSegAheadThin = 6;
 constexpr int kSegAheadCorr = 4;
-constexpr int kDepWindowCorr = 4;
+template <bool THIN>
+constexpr int seg_ahead() { return THIN ? kSegAheadThin : kSegAhead; }
 
 // Up to K crossings of one lane per pass: the geometry of K segments is computed first
 // and their opacities are loaded together (K loads in flight per lane), then the
-// segments are deposited in order; `deposit.add` is called once per kDepWindow segments by
-// the whole wave. With THIN, a lane whose ray starts at or beyond its split radius (inside
+// segments are deposited in order, the wave's together. With THIN, a lane whose ray starts at or beyond its split radius (inside
 // the source's thin sphere) splits at once, without a crossing.
 // Returns the lane's final event of the pass (kContinue if the ray goes on).
 template <int NB, int PREC, int K, bool THIN, class Depositor>
-__device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, bool active,
-                                          WaveStats& st, Depositor& deposit)
+__device__ __forceinline__ int trace_pass(const TraceArgs& A, Ray<NB>& ray, bool active, WaveStats& st,
+                                          Depositor& deposit)
 {
     Seg sg[K];
     int nseg = 0;  // segments of the lane (a count, not K lane masks: those spill)
@@ -792,17 +819,24 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
             ev = kSplit;
         }
     }
+    // the index terms of a segment are summed one segment later, when they have come from LDS; a
+    // lane without the segment keeps older ones (or zero): a valid cell to read
+    uint32_t term[2][3] = {{0u, 0u, 0u}, {0u, 0u, 0u}};
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        sg[j].cell = 0u;
-        if (go) {
-            ev = geom_next<NB, PREC>(A, terms, ray, sg[j]);
-            nseg = j + 1;
-            go = ev == kContinue;
+    for (int j = 0; j <= K; ++j) {
+        if (j < K) {
+            if (go) {
+                ev = geom_next<NB, PREC>(A, ray, sg[j], term[j & 1]);
+                nseg = j + 1;
+                go = ev == kContinue;
+            }
+        }
+        if (j > 0) {
+            const uint32_t(&t)[3] = term[(j - 1) & 1];
+            sg[j - 1].cell = t[0] + t[1] + t[2];
         }
     }
-    // the gathers are issued unconditionally (cell 0 for a lane without the segment), so that
-    // no branch separates them and each deposit waits for its own gather only
+    // the gathers are issued unconditionally, so that no branch separates them and each deposit waits for its own gather only
     float kap[K][NB];
 #pragma unroll
     for (int j = 0; j < K; ++j) kappa_at<NB>(A, sg[j].cell, kap[j]);
@@ -811,7 +845,6 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
     const uint32_t live = live_bins<NB>(ray, active, T, kLiveMin);
     // every gather is consumed before the pass issues its first atomic (a wait for a gather
     // issued before an unknown number of atomics would wait for all of them)
-    static_assert(K % kDepWindow == 0, "whole windows per pass");
     Dep<NB> dep[K];
     float reach = INFINITY;
 #pragma unroll
@@ -823,13 +856,10 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
         }
     }
     st.crossings += (uint32_t)nseg;
+    bool on[K];
 #pragma unroll
-    for (int j0 = 0; j0 < K; j0 += kDepWindow) {
-        bool on[kDepWindow];
-#pragma unroll
-        for (int w = 0; w < kDepWindow; ++w) on[w] = j0 + w < nseg;
-        deposit.template add<kWhole, kDepWindow>(dep + j0, on, live, A.J, NB);
-    }
+    for (int j = 0; j < K; ++j) on[j] = j < nseg;
+    deposit.template add<kWhole, K>(dep, on, live, A.J, NB);
     book_events<NB, PREC, THIN>(A, ev, ray, reach, st);
     return ev;
 }
@@ -838,10 +868,9 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, const Terms& terms
 // opacities loaded with the cells'. The crossings' cells form windows, as without the
 // correction; in mode 2 their neighbours' high limbs, then their low limbs, form two more.
 template <int NB, int PREC, int K, bool THIN, class Depositor>
-__device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& terms, Ray<NB>& ray, bool active,
-                                               WaveStats& st, Depositor& deposit)
+__device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, Ray<NB>& ray, bool active, WaveStats& st,
+                                               Depositor& deposit)
 {
-    static_assert(K % kDepWindowCorr == 0, "whole windows per pass");
     Seg sg[K];
     int nseg = 0;  // segments of the lane (a count, not K lane masks: those spill)
     bool go = active;
@@ -857,7 +886,8 @@ __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& 
         sg[j].cell = 0u;
         sg[j].nb = kNoCell;
         if (go) {
-            ev = geom_next<NB, PREC, true>(A, terms, ray, sg[j]);
+            uint32_t term[3];
+            ev = geom_next<NB, PREC, true>(A, ray, sg[j], term);
             nseg = j + 1;
             go = ev == kContinue;
         }
@@ -889,21 +919,14 @@ __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, const Terms& 
         }
     }
     st.crossings += (uint32_t)nseg;
+    bool on[K];
 #pragma unroll
-    for (int j = 0; j < K; j += kDepWindowCorr) {
-        bool on[kDepWindowCorr], onj[kDepWindowCorr], onm[kDepWindowCorr];
-#pragma unroll
-        for (int w = 0; w < kDepWindowCorr; ++w) {
-            on[w] = j + w < nseg;
-            onj[w] = use_j[j + w];
-            onm[w] = use_m[j + w];
-        }
-        deposit.template add<kWhole, kDepWindowCorr>(dep + j, on, live, A.J, NB);
-        if (A.corr == 2) {
-            deposit.template add<kWhole, kDepWindowCorr>(dj + j, onj, live, A.J, NB);
-            deposit.template add<kMovedHi, kDepWindowCorr>(dm + j, onm, live, A.M, 2 * NB);
-            deposit.template add<kMovedLo, kDepWindowCorr>(dm + j, onm, live, A.M + 8 * NB, 2 * NB);
-        }
+    for (int j = 0; j < K; ++j) on[j] = j < nseg;
+    deposit.template add<kWhole, K>(dep, on, live, A.J, NB);
+    if (A.corr == 2) {
+        deposit.template add<kWhole, K>(dj, use_j, live, A.J, NB);
+        deposit.template add<kMovedHi, K>(dm, use_m, live, A.M, 2 * NB);
+        deposit.template add<kMovedLo, K>(dm, use_m, live, A.M + 8 * NB, 2 * NB);
     }
     book_events<NB, PREC, THIN>(A, ev, ray, reach, st);
     return ev;
@@ -990,6 +1013,7 @@ struct DepScratch {
     unsigned long long acc[512];  // sums of one bin, by place in the block
     uint32_t tag[64];             // block whose tile holds the entry
     uint8_t used[64];             // entries in use, compacted
+    double esc[kMaxBins];         // photons the wave's lanes carried out of the grid (WaveStats)
 };
 
 // Called by all 64 lanes of the wave that owns the scratch, before its first window.
@@ -1094,8 +1118,7 @@ __device__ __forceinline__ int deposit_window(const Dep<NB>* d, const bool (&on)
     return n * __popc(live);
 }
 
-// Wave-wide deposit of the crossings of a pass: add() once per window of kDepWindow
-// segments, by every lane.
+// Wave-wide deposit of the crossings of a pass: add() by every lane.
 template <int NB>
 struct Depositor {
     DepScratch* scratch;
@@ -1128,9 +1151,7 @@ template <int NB>
 __device__ __forceinline__ void flush_stats(const TraceArgs& A, const WaveStats& st)
 {
     const unsigned long long crossings = wave_sum_u64(st.crossings);
-    double esc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) esc[b] = wave_sum_f64(st.esc[b]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if ((threadIdx.x & 63) == 0) {
         CounterSlot& c = my_slot(A.slots);
         if (crossings) atomicAdd(&c.n[kCrossings], crossings);
@@ -1140,7 +1161,7 @@ __device__ __forceinline__ void flush_stats(const TraceArgs& A, const WaveStats&
         if (st.escaped) atomicAdd(&c.n[kEscapedRays], st.escaped);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-            if (esc[b] != 0.0) atomicAdd(&c.photons[kPhotonsEscaped + b], esc[b]);
+            if (st.esc[b] != 0.0) atomicAdd(&c.photons[kPhotonsEscaped + b], st.esc[b]);
     }
 }
 

@@ -100,7 +100,8 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 hipError_t launch_trace_persistent(const TraceArgs& A, int prec, const RayRec* items, const uint32_t* n_items,
                                    uint32_t* head, RayRec* spill, uint32_t spill_cap, int blocks, int waves,
                                    int refill, int fam, int stack_cap, hipStream_t s);
-int persistent_max_waves();
+// Waves per SIMD that the persistent kernel's registers allow (a compute unit has four SIMDs).
+constexpr int persistent_waves_per_simd(int nb) { return nb <= 3 ? 4 : 3; }
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
 hipError_t launch_probe_deposits(unsigned long long* J, uint64_t nline, uint64_t items, uint64_t seed, int cus,
                                  hipStream_t s);

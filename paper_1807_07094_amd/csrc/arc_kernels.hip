@@ -398,7 +398,7 @@ hipError_t launch_seed_roots(uint32_t src, int level0, RayRec* out, hipStream_t 
 extern __shared__ __align__(16) unsigned char arc_dyn_lds[];
 __host__ __device__ __forceinline__ size_t terms_bytes(const TraceArgs& A)
 {
-    return ((size_t)(A.nx + A.ny + A.nz) * sizeof(uint32_t) + 15u) & ~(size_t)15u;
+    return ((size_t)(A.nx + A.ny + A.nz + 6) * sizeof(uint32_t) + 15u) & ~(size_t)15u;
 }
 
 // -------------------------------------------------------------------------------------
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
     const Terms terms = make_terms(A, reinterpret_cast<uint32_t*>(arc_dyn_lds));
     __syncthreads();
     WaveStats st;
-    st.clear();
+    st.clear((kLds double*)dep.scratch->esc);
     const int lane = threadIdx.x & 63;
     const uint64_t lt = __lanemask_lt();
     const uint32_t stride = gridDim.x * blockDim.x;
@@ -441,9 +441,9 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
         while (__any(act)) {
             int e;
             if constexpr (CORR)
-                e = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, terms, ray, act, st, dep);
+                e = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, act, st, dep);
             else
-                e = trace_pass<NB, PREC, kSegAhead, THIN>(A, terms, ray, act, st, dep);
+                e = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, act, st, dep);
             if (act && e != kContinue) {
                 ev = e;
                 act = false;
@@ -522,10 +522,11 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 // root rays when there was none); every new ray of the iteration is started in one place. The
 // stack's top holds the latest splits, so the four children of a ray, and the children of rays
 // that split together, enter together and cross the same cells in the same passes: the wave's
-// deposit merge then sums their crossings of a 2x2x2 tile into one 64-byte line per bin. VALU
-// issue bounds the kernel (256^3 x 1024 sources: 29.0 ms, 1.42e11 crossings/s; with a merge per
-// cell, an index computed per step and every bin attenuated to the end 49.1 ms, where the
-// atomics' request rate was as close). The LDS stack is a ring: when it would overflow, its oldest
+// deposit merge then sums their crossings of a 2x2x2 tile into one 64-byte line per bin. Issue
+// bounds the kernel: 3.7 VALU wave-instructions per crossing (42 lanes active in the mean), 1.4
+// scalar ones, 0.5 branches, four waves per SIMD filling each other's gaps (256^3 x 1024 sources:
+// 24.3 ms, 1.70e11 crossings/s; with a merge per cell, an index computed per step, every bin
+// attenuated to the end and three waves per SIMD 49.1 ms). The LDS stack is a ring: when it would overflow, its oldest
 // entries move to the top of the spill area, so the pair behaves as one LIFO stack and
 // the wave works depth first. Waves share nothing but the work-queue head, so each wave ends
 // when the queue is drained and its own stacks are empty.
@@ -535,7 +536,7 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 // launch (the autotuner's LDS stack depth).
 
 template <int NB, int PREC, int WPB, bool CORR, bool THIN>
-__global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(TraceArgs A, const RayRec* __restrict__ items,
+__global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_trace_persistent(TraceArgs A, const RayRec* __restrict__ items,
                                                                const uint32_t* n_items_dev, uint32_t* head,
                                                                RayRec* __restrict__ spill_all, uint32_t spill_cap,
                                                                int refill, int fam, int stack_cap)
@@ -568,15 +569,15 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
     bool has = false;
     Ray<NB> ray;
     WaveStats st;
-    st.clear();
+    st.clear((kLds double*)dep.scratch->esc);
     for (;;) {
         // one pass over the lanes that hold a ray
         int ev = kContinue;
         if (__any(has)) {
             if constexpr (CORR)
-                ev = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, terms, ray, has, st, dep);
+                ev = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, has, st, dep);
             else
-                ev = trace_pass<NB, PREC, kSegAhead, THIN>(A, terms, ray, has, st, dep);
+                ev = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, has, st, dep);
         }
         // splits: one family record each
         const uint64_t sp = __ballot(ev == kSplit);
@@ -675,10 +676,6 @@ __global__ __launch_bounds__(WPB * 64, NB <= 3 ? 3 : 2) void k_trace_persistent(
     dep.flush(A);
     if (lane == 0 && spilled) atomicAdd(&my_slot(A.slots).n[kSpills], (unsigned long long)spilled);
 }
-
-constexpr int kMaxWavesPerBlock = 8;
-
-int persistent_max_waves() { return kMaxWavesPerBlock; }
 
 template <int NB, int PREC, bool CORR, bool THIN>
 static hipError_t persistent_nb(const TraceArgs& A, const RayRec* items, const uint32_t* n_items, uint32_t* head,
