@@ -18,8 +18,6 @@
 
 using namespace arc;
 
-constexpr int kChemWords = kChemSlots * kChemSlotWords + 1;  // statistics and the work counter
-
 struct arc_ctx {
     int device = 0;
     int cus = 0;
@@ -34,10 +32,10 @@ struct arc_ctx {
     size_t M_bytes = 0;
     // source table
     SourceRec* src = nullptr;
-    double* src_in = nullptr;          // the call's sources as uploaded: SourceUpload
+    double* src_fill = nullptr;        // [5] per source: the thin fill's copy
     uint32_t* r_out = nullptr;         // measured R_tau<0.1 per source (FP32 bits)
     int src_cap = 0;
-    double* src_stage = nullptr;       // the same on the host, pinned
+    double* src_stage = nullptr;       // the call's sources, pinned: SourceUpload
     uint32_t* r_stage = nullptr;       // r_out on the host, pinned
     // HEALPix centres, levels 0..dirs_levels-1
     float4* dirs = nullptr;
@@ -51,24 +49,32 @@ struct arc_ctx {
     size_t spill_entries = 0;
     // small device scalars
     RunBlock* run = nullptr;
-    RunBlock* run_host = nullptr;             // pinned
-    unsigned long long* chem_stats = nullptr;  // chemistry statistics (kChemSlots), then the work counter
+    // a call leaves these two as it wants to find them (zero; +inf), unless it failed on the way
+    ChemBlock* chem_run = nullptr;
+    unsigned long long* limits = nullptr;     // the time step's two minima
+    bool chem_clean = false, limits_clean = false;
+    struct Host {                             // pinned: written by the last kernel of a call
+        RunResult run;
+        ChemResult chem;
+        double limits[2];
+    };
+    Host* host = nullptr;
+    double clock_khz = 1e5;                   // of the device's stamps
     unsigned long long* reject = nullptr;     // learned step: cells for the plain solver, a bit each
     size_t reject_cap = 0;                    // words
-    hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    bool timed_kernel = false;  // ev[4], ev[5] bracket the dominant trace kernel
+    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};  // request probes
     // last trace
     int last_nb = 0, last_nx = 0, last_ny = 0, last_nbx8 = 0, last_nby8 = 0;
     size_t last_ncell = 0;
     bool last_moved = false;  // the last trace filled M
     bool have_field = false;
-    // replayed launches of the batched schedule: [0] set-up, [1] the first levels, [2] the
-    // persistent trace, [3] the rates; valid while the launch arguments equal graph_key
+    // the replayed launches of the batched schedule; valid while the launch arguments equal
+    // graph_key
     hipStream_t cap_stream = nullptr;
-    hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
+    hipGraphExec_t gexec = nullptr;
     std::vector<unsigned char> graph_key;
-    // the chemistry step's stages (statistics, network, solver), same scheme
-    hipGraphExec_t cexec[3] = {nullptr, nullptr, nullptr};
+    // the chemistry step's, same scheme
+    hipGraphExec_t cexec = nullptr;
     std::vector<unsigned char> chem_key;
     unsigned long long* sums = nullptr;  // field checksums of the autotuner
     unsigned long long* static_scratch = nullptr;  // this device's copy of `scratch`
@@ -79,8 +85,8 @@ struct arc_ctx {
     std::vector<Tuned> tuned;
 };
 
-// A call's sources in one upload of n entries: positions, photon rates, thin radii, and the
-// sources by decreasing photon rate (work-queue order).
+// A call's sources, n entries in pinned memory that the first kernel reads: positions, photon
+// rates, thin radii, and the sources by decreasing photon rate (work-queue order).
 struct SourceUpload {
     size_t pos, ndot, rthin, order, bytes;  // offsets [doubles], size
     explicit SourceUpload(size_t n) : pos(0), ndot(3 * n), rthin(4 * n), order(5 * n), bytes(44 * n) {}
@@ -262,14 +268,17 @@ arc_status arc_create(int32_t device, arc_ctx** out)
         return ARC_E_DEVICE;
     }
     bool ok = hipMalloc((void**)&c->run, sizeof(RunBlock)) == hipSuccess &&
-              hipHostMalloc((void**)&c->run_host, sizeof(RunBlock), hipHostMallocDefault) == hipSuccess &&
-              hipMalloc((void**)&c->chem_stats, kChemWords * sizeof(unsigned long long)) == hipSuccess &&
+              hipHostMalloc((void**)&c->host, sizeof(arc_ctx::Host), hipHostMallocDefault) == hipSuccess &&
+              hipMalloc((void**)&c->limits, 2 * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc((void**)&c->chem_run, sizeof(ChemBlock)) == hipSuccess &&
               hipMalloc((void**)&c->sums, 2 * sizeof(unsigned long long)) == hipSuccess;
-    for (int i = 0; i < 6 && ok; ++i) ok = hipEventCreate(&c->ev[i]) == hipSuccess;
+    for (int i = 0; i < 3 && ok; ++i) ok = hipEventCreate(&c->ev[i]) == hipSuccess;
     if (!ok) {
         arc_destroy(c);
         return ARC_E_NOMEM;
     }
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
     *out = c;
     return ARC_OK;
 }
@@ -278,19 +287,17 @@ void arc_destroy(arc_ctx* c)
 {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    void* bufs[] = {c->kappa, c->J, c->M, c->src, c->src_in, c->r_out, c->dirs, c->rays[0], c->rays[1], c->spill,
-                    c->run, c->chem_stats, c->reject};
+    void* bufs[] = {c->kappa, c->J, c->M, c->src, c->src_fill, c->r_out, c->dirs, c->rays[0], c->rays[1], c->spill,
+                    c->run, c->chem_run, c->limits, c->reject};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
-    void* pinned[] = {c->src_stage, c->r_stage, c->run_host};
+    void* pinned[] = {c->src_stage, c->r_stage, c->host};
     for (void* p : pinned)
         if (p) (void)hipHostFree(p);
-    for (int i = 0; i < 6; ++i)
-        if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
-    for (int i = 0; i < 4; ++i)
-        if (c->gexec[i]) (void)hipGraphExecDestroy(c->gexec[i]);
     for (int i = 0; i < 3; ++i)
-        if (c->cexec[i]) (void)hipGraphExecDestroy(c->cexec[i]);
+        if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
+    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
+    if (c->cexec) (void)hipGraphExecDestroy(c->cexec);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->sums) (void)hipFree(c->sums);
     delete c;
@@ -329,6 +336,8 @@ struct TracePlan {
     RayRec* rays1;
     RayRec* spill;
     RunBlock* run;
+    RunResult* result;
+    uint32_t* r_host;   // pinned: where the measured thin radii go, or null
 };
 
 // Validation, fixed-point units, buffers and launch arguments shared by both schedules.
@@ -429,10 +438,10 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         if (p->correction == ARC_CORR_CONSERVING)
             HIP_TRY(c, grow(&c->M, &c->M_bytes, nblocked * 2 * nb * sizeof(unsigned long long)));
         if (s->n > c->src_cap) {
-            void* old[] = {c->src, c->src_in, c->r_out};
+            void* old[] = {c->src, c->src_fill, c->r_out};
             void* old_pinned[] = {c->src_stage, c->r_stage};
             c->src = nullptr;
-            c->src_in = c->src_stage = nullptr;
+            c->src_fill = c->src_stage = nullptr;
             c->r_out = c->r_stage = nullptr;
             c->src_cap = 0;
             for (void* q : old)
@@ -441,7 +450,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
                 if (q) HIP_TRY(c, hipHostFree(q));
             const SourceUpload up((size_t)s->n);
             HIP_TRY(c, hipMalloc((void**)&c->src, s->n * sizeof(SourceRec)));
-            HIP_TRY(c, hipMalloc((void**)&c->src_in, up.bytes));
+            HIP_TRY(c, hipMalloc((void**)&c->src_fill, s->n * 5 * sizeof(double)));
             HIP_TRY(c, hipMalloc((void**)&c->r_out, s->n * sizeof(uint32_t)));
             HIP_TRY(c, hipHostMalloc((void**)&c->src_stage, up.bytes, hipHostMallocDefault));
             HIP_TRY(c, hipHostMalloc((void**)&c->r_stage, s->n * sizeof(uint32_t), hipHostMallocDefault));
@@ -451,6 +460,8 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     if ((rc = ensure_dirs(c, lmax + 1, st)) != ARC_OK) return rc;
 
     P.run = c->run;
+    P.result = &c->host->run;
+    P.r_host = thin && s->r_thin_out && s->n > 0 ? c->r_stage : nullptr;
     BeginArgs& ba = P.ba;
     const SourceUpload up((size_t)s->n);
     ba.run = c->run;
@@ -458,10 +469,11 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     ba.nsrc = s->n;
     ba.level0 = p->level0;
     if (s->n > 0) {
-        ba.pos = c->src_in + up.pos;
-        ba.ndot = c->src_in + up.ndot;
-        ba.r_thin = thin && s->r_thin ? c->src_in + up.rthin : nullptr;
-        ba.order = reinterpret_cast<const uint32_t*>(c->src_in + up.order);
+        ba.pos = c->src_stage + up.pos;
+        ba.ndot = c->src_stage + up.ndot;
+        ba.r_thin = thin && s->r_thin ? c->src_stage + up.rthin : nullptr;
+        ba.fill = thin ? c->src_fill : nullptr;
+        ba.order = reinterpret_cast<const uint32_t*>(c->src_stage + up.order);
     }
     ba.src = c->src;
     ba.r_out = thin ? c->r_out : nullptr;
@@ -544,6 +556,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     fa.gamma = out->gamma;
     fa.heat = out->heat;
     fa.slots = c->run->before;
+    fa.stamp = &c->run->stamp[kStampRates];
 
     if (thin) {
         ThinFillArgs& tf = P.tf;
@@ -559,9 +572,7 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
         tf.nz = g->nz;
         tf.nbx8 = nbx8;
         tf.nby8 = nby8;
-        tf.pos = ba.pos;
-        tf.ndot = ba.ndot;
-        tf.r_thin = ba.r_thin;
+        tf.src = ba.fill;
         for (int k = 0; k < nb; ++k) {
             tf.coef[k] = b->frac[k] / (4.0 * M_PI * P.uj[k]);
             tf.uj[k] = P.uj[k];
@@ -676,8 +687,10 @@ hipError_t enqueue_levels(const TracePlan& P, hipStream_t st)
         const uint32_t out_cap = (uint32_t)std::min<size_t>(P.cap[1 - cur], 0xFFFFFFF0u);
         // the last level leaves family records: the work items of the persistent launch
         const int fam_out = l + 1 == P.litem ? 1 : 0;
-        const hipError_t e = launch_trace_rays(P.A, P.precision, r[cur], P.run->level_rays + l, (uint32_t)bound,
-                                               r[1 - cur], P.run->level_rays + l + 1, out_cap, fam_out, st);
+        TraceArgs A = P.A;
+        A.stamp = l == P.A.level0 ? &P.run->stamp[kStampTrace] : nullptr;
+        const hipError_t e = launch_trace_rays(A, P.precision, r[cur], &P.run->level_rays[l].n, (uint32_t)bound,
+                                               r[1 - cur], &P.run->level_rays[l + 1].n, out_cap, fam_out, st);
         if (e != hipSuccess) return e;
         bound *= 4;
         cur = 1 - cur;
@@ -694,19 +707,36 @@ hipError_t enqueue_persistent(const TracePlan& P, hipStream_t st)
     const int fam = P.litem > P.A.level0 ? 1 : 0;
     TraceArgs A = P.A;
     A.slots = P.run->persistent;
-    return launch_trace_persistent(A, P.precision, cur ? P.rays1 : P.rays0, P.run->level_rays + P.litem, &P.run->head,
+    A.stamp = &P.run->stamp[kStampPersistent];
+    return launch_trace_persistent(A, P.precision, cur ? P.rays1 : P.rays0, &P.run->level_rays[P.litem].n, &P.run->head.n,
                                    P.spill, P.spill_cap, P.blocks, P.waves, P.refill, fam, P.stack, st);
 }
 
-// Stage 3: rates (eq:ion per absorber, section 2.8 heating) and the absorbed ledger.
-hipError_t enqueue_rates(const TracePlan& P, hipStream_t st) { return launch_finalize(P.fa, st); }
+// Stage 3: rates (eq:ion per absorber, section 2.8 heating) and the absorbed ledger; then the
+// call's counters to the host.
+hipError_t enqueue_rates(const TracePlan& P, hipStream_t st)
+{
+    const hipError_t e = launch_finalize(P.fa, st);
+    return e != hipSuccess ? e : launch_end(P.run, P.result, P.A.r_out, P.r_host, P.nsrc, st);
+}
+
+// The whole batched call.
+hipError_t enqueue_batched(const TracePlan& P, hipStream_t st)
+{
+    hipError_t e;
+    if ((e = enqueue_common(P, st)) != hipSuccess) return e;
+    if ((e = enqueue_levels(P, st)) != hipSuccess) return e;
+    if ((e = enqueue_persistent(P, st)) != hipSuccess) return e;
+    return enqueue_rates(P, st);
+}
 
 // Section 2.1 iii: one source at a time, one HEALPix level per launch; the host reads
 // back the number of children before launching the next level.
 arc_status run_plain(arc_ctx* c, const TracePlan& P, hipStream_t st)
 {
     const uint32_t npix0 = 12u << (2 * P.A.level0);
-    uint32_t* n_out = c->run->level_rays + (kMaxLevels - 1);
+    uint32_t* n_out = &c->run->level_rays[kMaxLevels - 1].n;
+    bool first = true;
     for (int si = 0; si < P.nsrc; ++si) {
         size_t n = npix0;
         for (int i = 0; i < 2; ++i)
@@ -732,7 +762,10 @@ arc_status run_plain(arc_ctx* c, const TracePlan& P, hipStream_t st)
                 c->rcap[0] = c->rcap[1] = need;
             }
             HIP_TRY(c, launch_set_u32(n_out, 0u, st));
-            HIP_TRY(c, launch_trace_rays(P.A, P.precision, c->rays[cur], nullptr, (uint32_t)n, c->rays[1 - cur], n_out,
+            TraceArgs A = P.A;
+            A.stamp = first ? &c->run->stamp[kStampTrace] : nullptr;
+            first = false;
+            HIP_TRY(c, launch_trace_rays(A, P.precision, c->rays[cur], nullptr, (uint32_t)n, c->rays[1 - cur], n_out,
                                          (uint32_t)std::min<size_t>(c->rcap[1 - cur], 0xFFFFFFF0u), 0, st));
             uint32_t nn = 0;
             HIP_TRY(c, hipMemcpyAsync(&nn, n_out, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -744,47 +777,40 @@ arc_status run_plain(arc_ctx* c, const TracePlan& P, hipStream_t st)
     return ARC_OK;
 }
 
-// Records the four stages of the batched schedule as graphs (on the context's own
-// capture stream) unless the recorded ones were made with the same arguments.
-arc_status ensure_graphs(arc_ctx* c, const TracePlan& P)
+// Records what `enqueue` launches as a graph (on the context's own capture stream) into *exec,
+// unless the recorded one was made with the same `size` bytes at `args`.
+template <class F>
+arc_status ensure_graph(arc_ctx* c, hipGraphExec_t* exec, std::vector<unsigned char>& key, const void* args, size_t size,
+                        const char* what, F enqueue)
 {
-    const unsigned char* key = reinterpret_cast<const unsigned char*>(&P);
-    if (c->gexec[0] && c->graph_key.size() == sizeof P && std::memcmp(c->graph_key.data(), key, sizeof P) == 0)
-        return ARC_OK;
-    for (int i = 0; i < 4; ++i)
-        if (c->gexec[i]) {
-            HIP_TRY(c, hipGraphExecDestroy(c->gexec[i]));
-            c->gexec[i] = nullptr;
-        }
-    c->graph_key.clear();
-    if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    for (int i = 0; i < 4; ++i) {
-        HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-        hipStream_t cs = c->cap_stream;
-        const hipError_t e = i == 0   ? enqueue_common(P, cs)
-                             : i == 1 ? enqueue_levels(P, cs)
-                             : i == 2 ? enqueue_persistent(P, cs)
-                                      : enqueue_rates(P, cs);
-        hipGraph_t graph = nullptr;
-        const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &graph);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return fail(c, ARC_E_DEVICE, "graph capture of stage %d: %s", i,
-                        hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        const hipError_t e3 = hipGraphInstantiate(&c->gexec[i], graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        if (e3 != hipSuccess) {
-            c->gexec[i] = nullptr;
-            return fail(c, ARC_E_DEVICE, "graph instantiation of stage %d: %s", i, hipGetErrorString(e3));
-        }
+    const unsigned char* bytes = static_cast<const unsigned char*>(args);
+    if (*exec && key.size() == size && std::memcmp(key.data(), bytes, size) == 0) return ARC_OK;
+    if (*exec) {
+        HIP_TRY(c, hipGraphExecDestroy(*exec));
+        *exec = nullptr;
     }
-    c->graph_key.assign(key, key + sizeof P);
+    key.clear();
+    if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+    HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
+    const hipError_t e = enqueue(c->cap_stream);
+    hipGraph_t graph = nullptr;
+    const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &graph);
+    if (e != hipSuccess || e2 != hipSuccess) {
+        if (graph) (void)hipGraphDestroy(graph);
+        return fail(c, ARC_E_DEVICE, "graph capture of %s: %s", what, hipGetErrorString(e != hipSuccess ? e : e2));
+    }
+    const hipError_t e3 = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    if (e3 != hipSuccess) {
+        *exec = nullptr;
+        return fail(c, ARC_E_DEVICE, "graph instantiation of %s: %s", what, hipGetErrorString(e3));
+    }
+    key.assign(bytes, bytes + size);
     return ARC_OK;
 }
 
-// One whole trace with a planned shape: uploads, the stages (eagerly or as graphs),
-// event timing, and the read-back of counters, ledger and error flags.
+// One whole trace with a planned shape: the sources into pinned memory, the stages (eagerly or
+// as a graph), and the counters, ledger and error flags that the last kernel leaves there.
 arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, double dt, int schedule, bool graph,
                      hipStream_t st, arc_ledger* ledger)
 {
@@ -803,66 +829,33 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
             for (size_t i = 0; i < n; ++i) order[i] = (uint32_t)i;
             std::stable_sort(order, order + n, [&](uint32_t a, uint32_t b2) { return s->ndot[a] > s->ndot[b2]; });
         }
-        HIP_TRY(c, hipMemcpyAsync(c->src_in, c->src_stage, up.bytes, hipMemcpyHostToDevice, st));
     }
-    c->timed_kernel = false;
     if (batched && graph) {
-        arc_status rc = ensure_graphs(c, P);
+        arc_status rc = ensure_graph(c, &c->gexec, c->graph_key, &P, sizeof P, "the trace",
+                                     [&](hipStream_t cs) { return enqueue_batched(P, cs); });
         if (rc != ARC_OK) return rc;
-        HIP_TRY(c, hipEventRecord(c->ev[0], st));
-        HIP_TRY(c, hipGraphLaunch(c->gexec[0], st));
-        HIP_TRY(c, hipEventRecord(c->ev[1], st));
-        HIP_TRY(c, hipGraphLaunch(c->gexec[1], st));
-        HIP_TRY(c, hipEventRecord(c->ev[4], st));
-        HIP_TRY(c, hipGraphLaunch(c->gexec[2], st));
-        HIP_TRY(c, hipEventRecord(c->ev[5], st));
-        HIP_TRY(c, hipEventRecord(c->ev[2], st));
-        HIP_TRY(c, hipGraphLaunch(c->gexec[3], st));
-        HIP_TRY(c, hipEventRecord(c->ev[3], st));
-        c->timed_kernel = P.nsrc > 0;
+        HIP_TRY(c, hipGraphLaunch(c->gexec, st));
+    } else if (batched) {
+        HIP_TRY(c, enqueue_batched(P, st));
     } else {
-        HIP_TRY(c, hipEventRecord(c->ev[0], st));
         HIP_TRY(c, enqueue_common(P, st));
-        // the first levels of the batched schedule belong to the trace time
-        HIP_TRY(c, hipEventRecord(c->ev[1], st));
-        if (batched) {
-            HIP_TRY(c, enqueue_levels(P, st));
-            HIP_TRY(c, hipEventRecord(c->ev[4], st));
-            HIP_TRY(c, enqueue_persistent(P, st));
-            HIP_TRY(c, hipEventRecord(c->ev[5], st));
-            c->timed_kernel = P.nsrc > 0;
-        } else {
-            arc_status rc = run_plain(c, P, st);
-            if (rc != ARC_OK) {
-                (void)hipStreamSynchronize(st);  // the upload has left the pinned buffer
-                return rc;
-            }
+        arc_status rc = run_plain(c, P, st);
+        if (rc != ARC_OK) {
+            (void)hipStreamSynchronize(st);  // nothing reads the pinned buffers any more
+            return rc;
         }
-        HIP_TRY(c, hipEventRecord(c->ev[2], st));
         HIP_TRY(c, enqueue_rates(P, st));
-        HIP_TRY(c, hipEventRecord(c->ev[3], st));
     }
-
-    const bool want_r = P.thin && s->r_thin_out && s->n > 0;
-    HIP_TRY(c, hipMemcpyAsync(c->run_host, c->run, sizeof(RunBlock), hipMemcpyDeviceToHost, st));
-    if (want_r)
-        HIP_TRY(c, hipMemcpyAsync(c->r_stage, c->r_out, (size_t)s->n * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
-    for (int i = 0; want_r && i < s->n; ++i) {
+    for (int i = 0; P.r_host && i < s->n; ++i) {
         float r;
         std::memcpy(&r, &c->r_stage[i], sizeof r);
         s->r_thin_out[i] = (double)r;
     }
-    const RunBlock& run = *c->run_host;
-    unsigned long long cnt[kNumCounters] = {0}, per[kNumCounters] = {0};
-    double acc[8] = {0};
-    for (int i = 0; i < kCounterSlots; ++i) {
-        for (int k = 0; k < kNumCounters; ++k) {
-            cnt[k] += run.before[i].n[k] + run.persistent[i].n[k];
-            per[k] += run.persistent[i].n[k];
-        }
-        for (int k = 0; k < 8; ++k) acc[k] += run.before[i].photons[k] + run.persistent[i].photons[k];
-    }
+    const RunResult& run = c->host->run;
+    const unsigned long long *cnt = run.n, *per = run.persistent;
+    const double* acc = run.photons;
+    auto ms_between = [&](int a, int b2) { return (double)(run.stamp[b2] - run.stamp[a]) / c->clock_khz; };
 
     c->last_nb = P.nb;
     c->last_ncell = P.ncell;
@@ -889,21 +882,15 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
         ledger->escaped_rays = cnt[kEscapedRays];
         ledger->spills = cnt[kSpills];
         ledger->deposits = cnt[kDeposits];
-        if (c->timed_kernel) {
-            ledger->kernel_crossings = per[kCrossings];
-            ledger->kernel_deposits = per[kDeposits];
-        }
         ledger->tree_count = (int64_t)run.tree_count;
         for (int k = 0; k < kMaxBins; ++k) ledger->u_j[k] = k < P.nb ? P.uj[k] : 0.0;
-        float ms = 0;
-        HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]));
-        ledger->ms_trace = ms;
-        HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[0], c->ev[3]));
-        ledger->ms_total = ms;
-        ledger->ms_kernel = 0;
-        if (c->timed_kernel) {
-            HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[4], c->ev[5]));
-            ledger->ms_kernel = ms;
+        const bool levels = !batched || P.litem > P.A.level0;
+        if (P.nsrc > 0) ledger->ms_trace = ms_between(levels ? kStampTrace : kStampPersistent, kStampRates);
+        ledger->ms_total = ms_between(kStampBegin, kStampEnd);
+        if (batched && P.nsrc > 0) {
+            ledger->kernel_crossings = per[kCrossings];
+            ledger->kernel_deposits = per[kDeposits];
+            ledger->ms_kernel = ms_between(kStampPersistent, kStampRates);
         }
     }
     return ARC_OK;
@@ -1184,50 +1171,19 @@ namespace {
 struct ChemPlan {
     ChemArgs a;
     mlp::InferArgs ia;
+    ChemResult* result;
     int mode;
     int cus;
 };
 
-// Stage 0: statistics and the work counter; stage 1 (learned modes): network and gate;
-// stage 2 (plain and gated modes): the sub-cycled solver.
-hipError_t chem_stage(arc_ctx* c, const ChemPlan& P, int stage, hipStream_t st)
+// The network and its gate (learned modes), the sub-cycled solver (plain and gated modes), and
+// the statistics to the host.
+hipError_t enqueue_chem(const ChemPlan& P, hipStream_t st)
 {
-    if (stage == 0) return launch_zero_u64(c->chem_stats, kChemWords, st);
-    if (stage == 1) return P.mode != ARC_CHEM_PLAIN ? mlp::launch_infer(P.ia, st) : hipSuccess;
-    return P.mode != ARC_CHEM_MLP_ONLY ? launch_chem(P.a, P.cus, st) : hipSuccess;
-}
-
-arc_status ensure_chem_graphs(arc_ctx* c, const ChemPlan& P)
-{
-    const unsigned char* key = reinterpret_cast<const unsigned char*>(&P);
-    if (c->cexec[0] && c->chem_key.size() == sizeof P && std::memcmp(c->chem_key.data(), key, sizeof P) == 0)
-        return ARC_OK;
-    for (int i = 0; i < 3; ++i)
-        if (c->cexec[i]) {
-            HIP_TRY(c, hipGraphExecDestroy(c->cexec[i]));
-            c->cexec[i] = nullptr;
-        }
-    c->chem_key.clear();
-    if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    for (int i = 0; i < 3; ++i) {
-        HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-        const hipError_t e = chem_stage(c, P, i, c->cap_stream);
-        hipGraph_t graph = nullptr;
-        const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &graph);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return fail(c, ARC_E_DEVICE, "graph capture of chemistry stage %d: %s", i,
-                        hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        const hipError_t e3 = hipGraphInstantiate(&c->cexec[i], graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        if (e3 != hipSuccess) {
-            c->cexec[i] = nullptr;
-            return fail(c, ARC_E_DEVICE, "graph instantiation of chemistry stage %d: %s", i, hipGetErrorString(e3));
-        }
-    }
-    c->chem_key.assign(key, key + sizeof P);
-    return ARC_OK;
+    hipError_t e = hipSuccess;
+    if (P.mode != ARC_CHEM_PLAIN && (e = mlp::launch_infer(P.ia, st)) != hipSuccess) return e;
+    if (P.mode != ARC_CHEM_MLP_ONLY && (e = launch_chem(P.a, P.cus, st)) != hipSuccess) return e;
+    return launch_chem_end(P.a.run, P.result, st);
 }
 
 }  // namespace
@@ -1278,17 +1234,18 @@ arc_status arc_rt_timestep(arc_ctx* c, const arc_grid* g, const arc_rates* r, co
     c->err.clear();
     if (!dt_n || !dt_i) return fail(c, ARC_E_ARG, "null outputs");
     TimestepArgs a;
-    arc_status rc = plan_timestep(c, g, r, b, p, eps, c->sums, a);
+    arc_status rc = plan_timestep(c, g, r, b, p, eps, c->limits, a);
     if (rc != ARC_OK) return rc;
     hipStream_t st = (hipStream_t)p->stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    HIP_TRY(c, launch_timestep_reset(c->sums, st));
+    if (!c->limits_clean) HIP_TRY(c, launch_timestep_reset(c->limits, st));
+    c->limits_clean = false;
     HIP_TRY(c, launch_timestep(a, c->cus, st));
-    unsigned long long h[2];
-    HIP_TRY(c, hipMemcpyAsync(h, c->sums, sizeof h, hipMemcpyDeviceToHost, st));
+    HIP_TRY(c, launch_timestep_end(c->limits, c->host->limits, st));
     HIP_TRY(c, hipStreamSynchronize(st));
-    std::memcpy(dt_n, &h[0], sizeof(double));
-    std::memcpy(dt_i, &h[1], sizeof(double));
+    c->limits_clean = true;
+    *dt_n = c->host->limits[0];
+    *dt_i = c->host->limits[1];
     return ARC_OK;
 }
 
@@ -1360,8 +1317,8 @@ arc_status arc_chem_step(arc_ctx* c, const arc_grid* g, const arc_rates* r, doub
     a.alpha_hii = p->alpha_hii;
     a.eps = p->eps;
     a.t_floor = p->t_floor;
-    a.stats = c->chem_stats;
-    a.chunk_counter = (uint32_t*)(c->chem_stats + kChemWords - 1);
+    a.run = c->chem_run;
+    P.result = &c->host->chem;
     a.mask = nullptr;
     if (p->mode != ARC_CHEM_PLAIN) {
         const size_t words = ((size_t)a.ncell + 63) / 64;
@@ -1390,47 +1347,32 @@ arc_status arc_chem_step(arc_ctx* c, const arc_grid* g, const arc_rates* r, doub
         ia.t_floor = (float)p->t_floor;
         ia.reject = c->reject;
         ia.collisional = p->rates == 1 ? p->collisional : 0;
+        ia.stamp = &c->chem_run->stamp[0];
         if (p->mode == ARC_CHEM_MLP_GATED) a.mask = c->reject;
     }
+    if (!c->chem_clean) HIP_TRY(c, launch_zero_u64((unsigned long long*)c->chem_run, sizeof(ChemBlock) / 8, st));
+    c->chem_clean = false;
     if (p->graph) {
-        if ((rc = ensure_chem_graphs(c, P)) != ARC_OK) return rc;
-        HIP_TRY(c, hipGraphLaunch(c->cexec[0], st));
-        HIP_TRY(c, hipEventRecord(c->ev[0], st));
-        HIP_TRY(c, hipGraphLaunch(c->cexec[1], st));
-        HIP_TRY(c, hipEventRecord(c->ev[2], st));
-        HIP_TRY(c, hipGraphLaunch(c->cexec[2], st));
+        if ((rc = ensure_graph(c, &c->cexec, c->chem_key, &P, sizeof P, "the chemistry step",
+                               [&](hipStream_t cs) { return enqueue_chem(P, cs); })) != ARC_OK)
+            return rc;
+        HIP_TRY(c, hipGraphLaunch(c->cexec, st));
     } else {
-        HIP_TRY(c, chem_stage(c, P, 0, st));
-        HIP_TRY(c, hipEventRecord(c->ev[0], st));
-        HIP_TRY(c, chem_stage(c, P, 1, st));
-        HIP_TRY(c, hipEventRecord(c->ev[2], st));
-        HIP_TRY(c, chem_stage(c, P, 2, st));
+        HIP_TRY(c, enqueue_chem(P, st));
     }
-    HIP_TRY(c, hipEventRecord(c->ev[1], st));
-    unsigned long long raw[kChemSlots * kChemSlotWords], cs[4] = {0, 0, 0, 0};
-    HIP_TRY(c, hipMemcpyAsync(raw, c->chem_stats, sizeof raw, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
-    for (int i = 0; i < kChemSlots; ++i) {
-        const unsigned long long* w = raw + i * kChemSlotWords;
-        cs[0] += w[0];
-        cs[1] += w[1];
-        cs[2] = std::max(cs[2], w[2]);
-        cs[3] += w[3];
-    }
+    c->chem_clean = true;
     if (stats) {
+        const ChemResult& r2 = c->host->chem;
+        const bool solver = p->mode != ARC_CHEM_MLP_ONLY, network = p->mode != ARC_CHEM_PLAIN;
+        auto ms_between = [&](int i, int j) { return (double)(r2.stamp[j] - r2.stamp[i]) / c->clock_khz; };
         stats->cells = a.ncell;
-        stats->sub_total = (int64_t)cs[0];
-        stats->capped = (int64_t)cs[1];
-        stats->sub_max = (int32_t)cs[2];
-        float ms = 0;
-        HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[0], c->ev[1]));
-        stats->ms = ms;
-        stats->fallback = p->mode == ARC_CHEM_MLP_GATED ? (int64_t)cs[3] : 0;
-        stats->ms_mlp = 0;
-        if (p->mode != ARC_CHEM_PLAIN) {
-            HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[0], c->ev[2]));
-            stats->ms_mlp = ms;
-        }
+        stats->sub_total = (int64_t)r2.sub_total;
+        stats->capped = (int64_t)r2.capped;
+        stats->sub_max = (int32_t)r2.sub_max;
+        stats->ms = ms_between(network ? 0 : 1, 2);
+        stats->fallback = p->mode == ARC_CHEM_MLP_GATED ? (int64_t)r2.cells : 0;
+        stats->ms_mlp = network ? ms_between(0, solver ? 1 : 2) : 0.0;
     }
     return ARC_OK;
 }

@@ -170,6 +170,7 @@ __global__ __launch_bounds__(256) void k_chem(ChemArgs a, uint32_t chunk)
 {
     unsigned long long sub_total = 0, capped = 0, cells = 0;  // wave-uniform
     int sub_max = 0;
+    stamp_start(&a.run->stamp[1]);
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t own = (uint64_t)wave * chunk, shared_from = (uint64_t)gridDim.x * 4u * chunk;
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(256) void k_chem(ChemArgs a, uint32_t chunk)
                 if (lo >= hi) {
                     uint32_t b0 = 0;
                     if (shared_from < a.ncell) {
-                        if (lane == 0) b0 = atomicAdd(a.chunk_counter, 1u);
+                        if (lane == 0) b0 = atomicAdd(&a.run->chunk, 1u);
                         b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
                     }
                     const uint64_t from = shared_from + (uint64_t)b0 * chunk;
@@ -232,13 +233,46 @@ __global__ __launch_bounds__(256) void k_chem(ChemArgs a, uint32_t chunk)
     }
     for (int off = 32; off > 0; off >>= 1) sub_max = max(sub_max, __shfl_xor(sub_max, off, 64));
     if (lane == 0) {
-        // atomics on one line go one after the other: kChemSlots copies, summed by the host
-        unsigned long long* st = a.stats + (size_t)(blockIdx.x & (kChemSlots - 1)) * kChemSlotWords;
-        if (sub_total) atomicAdd(&st[0], sub_total);
-        if (capped) atomicAdd(&st[1], capped);
-        if (sub_max) atomicMax(&st[2], (unsigned long long)sub_max);
-        if (cells) atomicAdd(&st[3], cells);
+        // atomics on one line go one after the other: kChemSlots copies
+        ChemSlot& st = a.run->slot[blockIdx.x & (kChemSlots - 1)];
+        if (sub_total) atomicAdd(&st.sub_total, sub_total);
+        if (capped) atomicAdd(&st.capped, capped);
+        if (sub_max) atomicMax(&st.sub_max, (unsigned long long)sub_max);
+        if (cells) atomicAdd(&st.cells, cells);
     }
+}
+
+// The step's last launch: statistics and stamps to the host's pinned memory, and the block
+// cleared for the next step (a launch before it and a copy after it cost 20 us each in gaps).
+__global__ __launch_bounds__(64) void k_chem_end(ChemBlock* run, ChemResult* out)
+{
+    const int t = threadIdx.x;
+    if (t == 0) {
+        out->stamp[2] = wall_clock64();
+        ChemResult r = {0, 0, 0, 0, {0, 0, 0}};
+        for (int i = 0; i < kChemSlots; ++i) {
+            r.sub_total += run->slot[i].sub_total;
+            r.capped += run->slot[i].capped;
+            r.sub_max = max(r.sub_max, run->slot[i].sub_max);
+            r.cells += run->slot[i].cells;
+        }
+        out->sub_total = r.sub_total;
+        out->capped = r.capped;
+        out->sub_max = r.sub_max;
+        out->cells = r.cells;
+        out->stamp[0] = run->stamp[0];
+        out->stamp[1] = run->stamp[1];
+        run->chunk = 0u;
+        __threadfence_system();
+    }
+    __syncthreads();
+    if (t < kChemSlots) run->slot[t].sub_total = run->slot[t].capped = run->slot[t].sub_max = run->slot[t].cells = 0ull;
+}
+
+hipError_t launch_chem_end(ChemBlock* run, ChemResult* out, hipStream_t s)
+{
+    k_chem_end<<<1, 64, 0, s>>>(run, out);
+    return hipGetLastError();
 }
 
 template <bool RATES, bool THERMAL, bool COLL>
@@ -365,6 +399,21 @@ __global__ void k_timestep_publish(const unsigned long long* bits, double* out)
 hipError_t launch_timestep_publish(const unsigned long long* bits, double* out, hipStream_t s)
 {
     k_timestep_publish<<<1, 64, 0, s>>>(bits, out);
+    return hipGetLastError();
+}
+
+__global__ void k_timestep_end(unsigned long long* bits, double* out)
+{
+    if (threadIdx.x < 2) {
+        out[threadIdx.x] = __longlong_as_double((long long)bits[threadIdx.x]);
+        bits[threadIdx.x] = 0x7FF0000000000000ull;  // +inf
+        __threadfence_system();
+    }
+}
+
+hipError_t launch_timestep_end(unsigned long long* bits, double* out, hipStream_t s)
+{
+    k_timestep_end<<<1, 64, 0, s>>>(bits, out);
     return hipGetLastError();
 }
 

@@ -62,8 +62,8 @@ enum Counter : int {
 enum Photons : int { kPhotonsEscaped = 0, kPhotonsAbsorbed = kMaxBins, kPhotonsThin };  // escaped: one per bin
 
 // Sums that every wave adds to at its end. Atomics on one line are carried out one after the
-// other, about 6 ns each, so a workgroup adds to one of kCounterSlots copies and the host sums
-// them (256^3 x 1024 sources with one copy: the levels before the persistent launch took 10.3
+// other, about 6 ns each, so a workgroup adds to one of kCounterSlots copies and the last kernel
+// sums them (256^3 x 1024 sources with one copy: the levels before the persistent launch took 10.3
 // ms, of which 8 were this, and the rates 0.43 ms instead of 0.22).
 constexpr int kCounterSlots = 64;
 struct __align__(256) CounterSlot {
@@ -72,15 +72,42 @@ struct __align__(256) CounterSlot {
     unsigned long long pad[8];
 };
 
-// The device's side of one call, in one block: cleared by its first kernel, read back at its end.
+// A counter with a line of its own: a level's kernel reads how many rays it has while it counts
+// the next level's, and such reads and atomics on one line wait for each other.
+struct __align__(128) LineCount {
+    uint32_t n, pad[31];
+};
+
+// When the stages of a call began (device clock): its first kernel, the trace, the persistent
+// launch, the rates, and the end of the last grid pass. Kernels stamp their start: an event
+// between two launches leaves the device idle for 6 to 18 us.
+enum Stamp : int { kStampBegin = 0, kStampTrace, kStampPersistent, kStampRates, kStampEnd, kNumStamps };
+
+// The device's side of one call, in one block, cleared by its first kernel (but for the stamps).
 struct RunBlock {
     CounterSlot before[kCounterSlots];      // everything but the persistent launch
     CounterSlot persistent[kCounterSlots];
-    uint32_t level_rays[kMaxLevels];        // rays (or families) waiting at each level
-    uint32_t head;                          // work queue: items taken after the waves' first
+    LineCount level_rays[kMaxLevels];       // rays (or families) waiting at each level
+    LineCount head;                         // work queue: items taken after the waves' first
     int32_t errflag;                        // grid values out of range
     unsigned long long tree_count;
+    unsigned long long stamp[kNumStamps];
 };
+
+// What the host reads of it, written to pinned memory by the call's last kernel.
+struct RunResult {
+    unsigned long long n[kNumCounters], persistent[kNumCounters];
+    double photons[8];
+    unsigned long long stamp[kNumStamps];
+    unsigned long long tree_count;
+    int32_t errflag;
+};
+
+// The kernel's start into *stamp (if given), by its first workgroup.
+__device__ __forceinline__ void stamp_start(unsigned long long* stamp)
+{
+    if (stamp && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *stamp = wall_clock64();
+}
 
 // Per-source constants (section 2.1 keeps the source position on chip; here it is a
 // 32-byte record read through L2 once per ray).
@@ -122,6 +149,7 @@ struct TraceArgs {
     const float4* dirs;        // HEALPix centres of every level, concatenated
     long long dir_off[kMaxLevels];
     CounterSlot* slots;        // [kCounterSlots]
+    unsigned long long* stamp; // where the launch notes its start, or null
     unsigned long long* tree;  // optional record of every ray traced
     unsigned long long* tree_count;
     long long tree_cap;
@@ -1009,11 +1037,14 @@ __device__ __forceinline__ StackRec<NB> family_child(const StackRec<NB>& f, int 
 constexpr uint32_t kNoBlock = 0xFFFFFFFFu;
 
 // Per-wave LDS space of the deposits. Between windows every sum is zero and every tag kNoBlock.
-struct DepScratch {
+struct __align__(16) DepScratch {
     unsigned long long acc[512];  // sums of one bin, by place in the block
     uint32_t tag[64];             // block whose tile holds the entry
     uint8_t used[64];             // entries in use, compacted
     double esc[kMaxBins];         // photons the wave's lanes carried out of the grid (WaveStats)
+    // When the wave began: noted in memory only at its end, since a store ahead of the trace turns
+    // its uniform loads into vector loads (256^3 x 1024 sources: 29.3 ms instead of 28.1).
+    unsigned long long began;
 };
 
 // Called by all 64 lanes of the wave that owns the scratch, before its first window.
@@ -1022,6 +1053,7 @@ __device__ __forceinline__ void dep_scratch_init(DepScratch* S)
     const int lane = threadIdx.x & 63;
     for (int i = lane; i < 512; i += 64) S->acc[i] = 0ull;
     S->tag[lane] = kNoBlock;
+    if (lane == 0) S->began = wall_clock64();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
@@ -1131,7 +1163,9 @@ struct Depositor {
     }
     __device__ void flush(const TraceArgs& A) const
     {
-        if ((threadIdx.x & 63) == 0 && items) atomicAdd(&my_slot(A.slots).n[kDeposits], (unsigned long long)items);
+        if ((threadIdx.x & 63) != 0) return;
+        if (items) atomicAdd(&my_slot(A.slots).n[kDeposits], (unsigned long long)items);
+        if (A.stamp && blockIdx.x == 0) *A.stamp = scratch->began;
     }
 };
 

@@ -35,6 +35,7 @@ struct FinalizeArgs {
     const float4* kappa4;
     float *gamma, *heat;       // [3][ncell]
     CounterSlot* slots;        // photons absorbed: sum_c sum_b u_J J kappa
+    unsigned long long* stamp;
 };
 
 // Set-up of a call. Root rays (batched) are those of the sources order[0 .. nsrc), each source's
@@ -43,11 +44,12 @@ struct BeginArgs {
     RunBlock* run;
     int nb, nsrc, level0;
     uint32_t n_roots;
-    const double *pos, *ndot, *r_thin;  // r_thin: null where no source has a thin sphere
+    const double *pos, *ndot, *r_thin;  // pinned; r_thin: null where no source has a thin sphere
+    double* fill;              // [nsrc][5] for the thin fill (position, rate, radius), or null
     double scale[kMaxBins];    // frac_b / (12 u_J,b)
     SourceRec* src;
     uint32_t* r_out;           // measured thin radii, or null
-    const uint32_t* order;
+    const uint32_t* order;     // pinned
     RayRec* roots;
 };
 
@@ -55,7 +57,7 @@ struct BeginArgs {
 struct ThinFillArgs {
     int nb, nsrc, parts;       // parts: blocks per source
     int nx, ny, nz, nbx8, nby8;
-    const double *pos, *ndot, *r_thin;
+    const double* src;         // [nsrc][5]: position, photon rate, thin radius
     double coef[kMaxBins];     // frac_b / (4 pi u_J,b)
     double uj[kMaxBins];
     unsigned long long* J;
@@ -64,7 +66,23 @@ struct ThinFillArgs {
     CounterSlot* slots;        // photons of the fill: its deposits times u_J kappa
 };
 
-constexpr int kChemSlots = 16, kChemSlotWords = 16;  // a 128-byte line each
+// The device's side of one chemistry step: statistics in copies (a 128-byte line each), the next
+// chunk of cells, when the stages began. Zero before the step: its last kernel clears what it
+// has handed to the host.
+constexpr int kChemSlots = 16;
+struct __align__(128) ChemSlot {
+    unsigned long long sub_total, capped, sub_max, cells;
+};
+struct ChemBlock {
+    ChemSlot slot[kChemSlots];
+    unsigned long long stamp[2];  // network, solver
+    uint32_t chunk;
+};
+struct ChemResult {
+    unsigned long long sub_total, capped, sub_max, cells, stamp[3];  // stamps: network, solver, end
+};
+hipError_t launch_chem_end(ChemBlock* run, ChemResult* out, hipStream_t s);
+
 struct ChemArgs {
     uint32_t ncell;
     double y;
@@ -75,8 +93,7 @@ struct ChemArgs {
     int isothermal, rates, collisional, max_sub;
     double alpha_hii, eps, t_floor;
     double inv_y;               // 1 / y (0 where y = 0)
-    unsigned long long* stats;  // [kChemSlots][kChemSlotWords]: sub total, capped, max, cells updated
-    uint32_t* chunk_counter;    // zero before the launch
+    ChemBlock* run;
     // optional: update only the cells whose bit is set, bit (c mod 64) of word c / 64
     const unsigned long long* mask;
 };
@@ -88,6 +105,9 @@ hipError_t launch_field_checksum(const unsigned long long* J, size_t n, unsigned
 hipError_t launch_opacity(const OpacityArgs& a, hipStream_t s);
 hipError_t launch_healpix(int level, float4* out, hipStream_t s);
 hipError_t launch_begin(const BeginArgs& a, hipStream_t s);
+// r_host (pinned, optional): receives r_out[0 .. nsrc).
+hipError_t launch_end(const RunBlock* run, RunResult* out, const uint32_t* r_out, uint32_t* r_host, int nsrc,
+                      hipStream_t s);
 hipError_t launch_thin_fill(const ThinFillArgs& a, hipStream_t s);
 hipError_t launch_seed_roots(uint32_t src, int level0, RayRec* out, hipStream_t s);
 // n_in_dev (optional) holds the ray count on the device; n_in bounds it and sizes the grid.
@@ -126,5 +146,7 @@ struct TimestepArgs {
 hipError_t launch_timestep_reset(unsigned long long* out, hipStream_t s);
 hipError_t launch_timestep(const TimestepArgs& a, int cus, hipStream_t s);
 hipError_t launch_timestep_publish(const unsigned long long* bits, double* out, hipStream_t s);
+// The same into pinned host memory, then bits back to +inf for the next call.
+hipError_t launch_timestep_end(unsigned long long* bits, double* out, hipStream_t s);
 
 }  // namespace arc

@@ -10,6 +10,7 @@
 //                      per-wave LDS ray stack with a private spill area in memory
 //   k_thin_fill        optically thin approximation: point-source field inside each thin radius
 //   k_finalize         fixed-point field -> photoionisation and photoheating rates
+//   k_end              counters, stamps and radii to the host
 //   k_get_field        field copy in [bin][cell] order
 #include <hip/hip_runtime.h>
 
@@ -278,13 +279,15 @@ __device__ __forceinline__ RayRec root_ray(uint32_t src, int level0, uint32_t pi
 
 // Everything a call needs before its first grid pass, in one launch: the cleared run block, the
 // source table, the unmeasured thin radii (+inf) and, batched, the root rays of every source in
-// the order of the work queue.
+// the order of the work queue. The sources are read from the host's pinned memory: a copy
+// ahead of the kernel costs 3 us and a gap of 10.
 __global__ __launch_bounds__(256) void k_begin(BeginArgs a)
 {
+    stamp_start(&a.run->stamp[kStampBegin]);
     const size_t t0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
     uint32_t* words = reinterpret_cast<uint32_t*>(a.run);
-    const size_t seeded = offsetof(RunBlock, level_rays) / 4 + (size_t)a.level0;
-    for (size_t i = t0; i < sizeof(RunBlock) / 4; i += stride) words[i] = i == seeded && a.roots ? a.n_roots : 0u;
+    const size_t seeded = (offsetof(RunBlock, level_rays) + (size_t)a.level0 * sizeof(LineCount)) / 4;
+    for (size_t i = t0; i < offsetof(RunBlock, stamp) / 4; i += stride) words[i] = i == seeded && a.roots ? a.n_roots : 0u;
     for (size_t i = t0; i < (size_t)a.nsrc; i += stride) {
         SourceRec r;
         r.x = (float)a.pos[3 * i];
@@ -295,6 +298,15 @@ __global__ __launch_bounds__(256) void k_begin(BeginArgs a)
         for (int b = 0; b < kMaxBins; ++b) r.scale[b] = b < a.nb ? (float)(a.ndot[i] * a.scale[b]) : 0.0f;
         a.src[i] = r;
         if (a.r_out) a.r_out[i] = 0x7F800000u;
+        if (a.fill) {
+            // the thin fill's copy on the device
+            double* f = a.fill + 5 * i;
+            f[0] = a.pos[3 * i];
+            f[1] = a.pos[3 * i + 1];
+            f[2] = a.pos[3 * i + 2];
+            f[3] = a.ndot[i];
+            f[4] = a.r_thin ? a.r_thin[i] : 0.0;
+        }
     }
     if (a.roots) {
         const uint32_t npix = 12u << (2 * a.level0);
@@ -310,6 +322,59 @@ hipError_t launch_begin(const BeginArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// The call's last launch: sums the counters' copies (in a fixed order) into the host's pinned
+// memory, with the stamps and the measured thin radii. One workgroup.
+__global__ __launch_bounds__(256) void k_end(const RunBlock* run, RunResult* out, const uint32_t* r_out,
+                                             uint32_t* r_host, int nsrc)
+{
+    __shared__ double part[256];
+    const int t = threadIdx.x;
+    if (t == 0) {
+        out->stamp[kStampEnd] = wall_clock64();
+        out->errflag = run->errflag;
+        out->tree_count = run->tree_count;
+    }
+    if (t < kNumStamps && t != kStampEnd) out->stamp[t] = run->stamp[t];
+    // one counter per 16 threads: each sums a part of the copies, then the first sums the parts
+    const int k = t >> 4, i = t & 15;
+    __shared__ unsigned long long before[256], persistent[256];
+    unsigned long long vb = 0, vp = 0;
+    for (int j = i; j < kCounterSlots; j += 16) {
+        vb += run->before[j].n[k];
+        vp += run->persistent[j].n[k];
+    }
+    before[t] = vb;
+    persistent[t] = vp;
+    __syncthreads();
+    if (i == 0 && k < kNumCounters) {
+        for (int j = 1; j < 16; ++j) {
+            vb += before[t + j];
+            vp += persistent[t + j];
+        }
+        out->persistent[k] = vp;
+        out->n[k] = vb + vp;
+    }
+    double d = 0.0;
+    if (k < 8)
+        for (int j = i; j < kCounterSlots; j += 16) d += run->before[j].photons[k] + run->persistent[j].photons[k];
+    part[t] = d;
+    __syncthreads();
+    if (i == 0 && k < 8) {
+        for (int j = 1; j < 16; ++j) d += part[t + j];
+        out->photons[k] = d;
+    }
+    if (r_host)
+        for (int j = t; j < nsrc; j += 256) r_host[j] = r_out[j];
+    __threadfence_system();
+}
+
+hipError_t launch_end(const RunBlock* run, RunResult* out, const uint32_t* r_out, uint32_t* r_host, int nsrc,
+                      hipStream_t s)
+{
+    k_end<<<1, 256, 0, s>>>(run, out, r_out, r_host, nsrc);
+    return hipGetLastError();
+}
+
 // -------------------------------------------------------------------------------------
 // Optically thin approximation (section 2.6): every cell whose centre lies within a source's
 // thin radius R receives that source's point-source field S_b / (4 pi r^2), r the centre's
@@ -321,9 +386,10 @@ __global__ __launch_bounds__(256) void k_thin_fill(ThinFillArgs a)
 {
     const int i = blockIdx.x;
     double absorbed = 0.0;
-    const double R = (double)(float)a.r_thin[i];
+    const double* src = a.src + 5 * i;
+    const double R = (double)(float)src[4];
     if (R > 0.0) {
-        const double xs[3] = {a.pos[3 * i], a.pos[3 * i + 1], a.pos[3 * i + 2]};
+        const double xs[3] = {src[0], src[1], src[2]};
         const int n[3] = {a.nx, a.ny, a.nz};
         int lo[3], ext[3];
 #pragma unroll
@@ -332,7 +398,7 @@ __global__ __launch_bounds__(256) void k_thin_fill(ThinFillArgs a)
             const int hi = min(n[d] - 1, (int)ceil(xs[d] + R));
             ext[d] = max(0, hi - lo[d] + 1);
         }
-        const double ndot = a.ndot[i];
+        const double ndot = src[3];
         const size_t total = (size_t)ext[0] * ext[1] * ext[2];
         const size_t stride = (size_t)gridDim.y * blockDim.x;
         for (size_t l = (size_t)blockIdx.y * blockDim.x + threadIdx.x; l < total; l += stride) {
@@ -779,6 +845,7 @@ __global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a)
     // per region: contiguous reads of the field and opacity, rates into LDS in linear
     // order, then whole x-rows of the six rate arrays
     __shared__ float out[6][kRegionCells];
+    stamp_start(a.stamp);
     double absorbed = 0.0;
     const uint32_t nreg = (((uint32_t)a.nbx8 + 3u) / 4u) * (uint32_t)a.nby8 * (uint32_t)a.nbz8;
     for (uint32_t r = blockIdx.x; r < nreg; r += gridDim.x) {

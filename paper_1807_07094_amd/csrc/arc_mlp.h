@@ -65,6 +65,7 @@ struct InferArgs {
     float t_floor;
     unsigned long long* reject;     // per 64-cell tile, bit set = the plain solver updates the cell
     int collisional;
+    unsigned long long* stamp;      // when the kernel began
 };
 
 hipError_t launch_infer(const InferArgs& a, hipStream_t s);

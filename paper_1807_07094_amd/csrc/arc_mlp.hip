@@ -256,6 +256,7 @@ __device__ __forceinline__ void standardise(const Model* M, const Scales& z, boo
 __global__ __launch_bounds__(256) void k_infer(InferArgs a)
 {
     const Model* M = a.model;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.stamp = wall_clock64();
     __shared__ LdsWeights w;
     // the gate's verdict per bin (enough samples, small held-out error) as one bit each, so that
     // a cell's gate test reads LDS instead of two scattered loads from the model's tables
