@@ -122,6 +122,10 @@ hipError_t launch_trace_persistent(const TraceArgs& A, int prec, const RayRec* i
                                    int refill, int fam, int stack_cap, hipStream_t s);
 // Waves per SIMD that the persistent kernel's registers allow (a compute unit has four SIMDs).
 constexpr int persistent_waves_per_simd(int nb) { return nb <= 3 ? 4 : 3; }
+// The same for a level's kernel: the fourth wave is worth its spills but with the correction
+// (256^3 x 1024 sources: levels 2.08 ms with three, 1.84 with four; corrected 192^3 x 128: 0.60
+// and 0.73).
+constexpr int level_waves_per_simd(int nb, bool corr) { return corr ? 3 : persistent_waves_per_simd(nb); }
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
 hipError_t launch_probe_deposits(unsigned long long* J, uint64_t nline, uint64_t items, uint64_t seed, int cus,
                                  hipStream_t s);

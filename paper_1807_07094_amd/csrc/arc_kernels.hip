@@ -470,15 +470,20 @@ __host__ __device__ __forceinline__ size_t terms_bytes(const TraceArgs& A)
 // -------------------------------------------------------------------------------------
 // Per-level schedule (section 2.1 iii b/c): one ray per lane, traced until it splits,
 // terminates or leaves the grid; splitting lanes write their four children into the
-// next level's array, one slot reservation per wave.
+// next level's array, one slot reservation per workgroup: the counter's line takes one atomic
+// in 4 to 9 ns, which bounded the launches of 10^5 rays and more (203x100x37 x 200 sources: all
+// levels 136 us with one per wave, 106 now; 256^3 x 1024: 3.3 ms, 1.84 now). The waves of a
+// workgroup end together for it; their rays are neighbours.
 // -------------------------------------------------------------------------------------
 template <int NB, int PREC, bool CORR, bool THIN>
-__global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* __restrict__ in,
+__global__ __launch_bounds__(256, level_waves_per_simd(NB, CORR)) void k_trace_rays(TraceArgs A, const RayRec* __restrict__ in,
                                                     const uint32_t* n_in_dev, uint32_t n_in_host,
                                                     RayRec* __restrict__ out, uint32_t* n_out, uint32_t out_cap,
                                                     int fam_out)
 {
     const uint32_t n_in = n_in_dev ? *n_in_dev : n_in_host;
+    // the grid is sized for the most rays there could be; the first workgroup notes the start
+    if (blockIdx.x && blockIdx.x * blockDim.x >= n_in) return;
     __shared__ DepScratch dscr[4];
     Depositor<NB> dep{dscr + (threadIdx.x >> 6)};
     dep_scratch_init(dep.scratch);
@@ -486,7 +491,9 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
     __syncthreads();
     WaveStats st;
     st.clear((kLds double*)dep.scratch->esc);
+    __shared__ uint32_t wave_out[4], block_out;
     const int lane = threadIdx.x & 63;
+    const int wid = threadIdx.x >> 6;
     const uint64_t lt = __lanemask_lt();
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t base = blockIdx.x * blockDim.x; base < n_in; base += stride) {
@@ -518,12 +525,17 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
         // a split ray leaves its four children, or (fam_out: the persistent launch's work
         // items) one family record from which they are derived
         const uint64_t m = __ballot(ev == kSplit);
+        const uint32_t per = fam_out ? 1u : 4u;
+        if (lane == 0) wave_out[wid] = per * (uint32_t)__popcll(m);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t n = wave_out[0] + wave_out[1] + wave_out[2] + wave_out[3];
+            block_out = n ? atomicAdd(n_out, n) : 0u;
+        }
+        __syncthreads();
         if (m) {
-            const uint32_t per = fam_out ? 1u : 4u;
-            const int leader = __ffsll((unsigned long long)m) - 1;
-            uint32_t wbase = 0;
-            if (lane == leader) wbase = atomicAdd(n_out, per * (uint32_t)__popcll(m));
-            wbase = __shfl(wbase, leader, 64);
+            uint32_t wbase = block_out;
+            for (int w = 0; w < wid; ++w) wbase += wave_out[w];
             if (ev == kSplit) {
                 const uint32_t slot = wbase + per * (uint32_t)__popcll(m & lt);
                 if (slot + per <= out_cap) {
@@ -538,6 +550,7 @@ __global__ __launch_bounds__(256) void k_trace_rays(TraceArgs A, const RayRec* _
                 }
             }
         }
+        __syncthreads();
     }
     flush_stats<NB>(A, st);
     dep.flush(A);
@@ -608,6 +621,16 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
                                                                int refill, int fam, int stack_cap)
 {
     using SRec = StackRec<NB>;
+    const uint32_t n_items = *n_items_dev;
+    // A wave's first items are its own by its place in the grid, since the waves' first atomics on
+    // the queue's head, all at once, take longer; later ones come from the queue's head. Few items
+    // are spread over all the waves, which fill their lanes with the rays that split: 1 source in
+    // 64^3 0.20 ms instead of 0.31 with 16 families to each wave, 28x32x24 x 3 0.155 instead of
+    // 0.195; with half the items at first and the rest from the head 0.35 and 0.24.
+    const uint32_t waves = gridDim.x * (uint32_t)WPB, most = fam ? 16u : 64u;
+    const uint32_t first = min(most, max(1u, (n_items + waves - 1u) / waves));
+    if (blockIdx.x && blockIdx.x * (uint32_t)WPB * first >= n_items) return;
+    const uint32_t shared_from = waves * first;
     const Terms terms = make_terms(A, reinterpret_cast<uint32_t*>(arc_dyn_lds));
     SRec* lds = reinterpret_cast<SRec*>(arc_dyn_lds + terms_bytes(A));
     const int cmask = stack_cap - 1;
@@ -615,11 +638,6 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
     const int wid = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const uint64_t lt = __lanemask_lt();
-    const uint32_t n_items = *n_items_dev;
-    // a wave's first items are its own by its place in the grid, later ones come from the
-    // queue's head (the waves' first atomics on it, all at once, took 25 us)
-    const uint32_t first = fam ? 16u : 64u;
-    const uint32_t shared_from = gridDim.x * (uint32_t)WPB * first;
     bool started = false;  // wave-uniform
     SRec* stk = lds + wid * stack_cap;
     Depositor<NB> dep{dscr + wid};
@@ -697,7 +715,7 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
             }
             // work items: single rays, or (fam) family records taken whole, four lanes each
             const int rem = nidle - used;
-            const uint32_t want = fam ? (uint32_t)(rem >> 2) : (uint32_t)rem;
+            const uint32_t room = fam ? (uint32_t)(rem >> 2) : (uint32_t)rem, want = started ? room : min(room, first);
             if (want > 0 && top == 0 && nspill == 0 && !qdone) {
                 const int take = used;
                 uint32_t b0 = (blockIdx.x * (uint32_t)WPB + (uint32_t)wid) * first;
