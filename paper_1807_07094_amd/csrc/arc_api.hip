@@ -1188,7 +1188,7 @@ struct ChemPlan {
 hipError_t enqueue_chem(const ChemPlan& P, hipStream_t st)
 {
     hipError_t e = hipSuccess;
-    if (P.mode != ARC_CHEM_PLAIN && (e = mlp::launch_infer(P.ia, st)) != hipSuccess) return e;
+    if (P.mode != ARC_CHEM_PLAIN && (e = mlp::launch_infer(P.ia, P.cus, st)) != hipSuccess) return e;
     if (P.mode != ARC_CHEM_MLP_ONLY && (e = launch_chem(P.a, P.cus, st)) != hipSuccess) return e;
     return launch_chem_end(P.a.run, P.result, st);
 }

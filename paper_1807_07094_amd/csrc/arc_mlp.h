@@ -48,7 +48,8 @@ struct Model {
     float gate_err[kGateBins];      // twice the largest held-out error per bin (max of |dx| and |dT|/(10 T))
 };
 
-// the training kernel reads rows of the images 16 bytes at a time
+// the training kernel reads rows of the images, and inference the gate's tables, 16 bytes at a time
+static_assert(offsetof(Model, gate_count) % 16 == 0 && offsetof(Model, gate_err) % 16 == 0, "aligned tables");
 static_assert(offsetof(Model, w1t) % 16 == 0 && offsetof(Model, w2t) % 16 == 0 && offsetof(Model, w3t) % 16 == 0, "aligned rows");
 
 struct InferArgs {
@@ -68,7 +69,9 @@ struct InferArgs {
     unsigned long long* stamp;      // when the kernel began
 };
 
-hipError_t launch_infer(const InferArgs& a, hipStream_t s);
+constexpr int kInferWavesPerSimd = 5;
+// cus: compute units of the device (resident workgroups only)
+hipError_t launch_infer(const InferArgs& a, int cus, hipStream_t s);
 
 // Training on standardised features F [m][kIn] and standardised targets Y [m][2]
 // (x_HI' - x_base, log10 (T'/T)), minibatch rows given by idx.

@@ -7,9 +7,9 @@
 // exponentially towards photoionisation equilibrium with the rates of the start of the step.
 // Helium is not an output: the gate accepts a cell only when its helium is close to steady.
 //
-//   k_infer       per cell: features, forward pass with the activations kept in registers
-//                 (each layer's MFMA output is the next layer's operand), gate; accepted
-//                 cells are written, rejected cells are appended to a list for the plain solver
+//   k_infer       per cell: gate, features, forward pass with the activations kept in registers
+//                 (each layer's MFMA output is the next layer's operand); accepted cells are
+//                 written, rejected cells get a bit in a mask for the plain solver
 //   k_predict     the same forward pass without the gate (validation, evaluation)
 //   k_train_grad  quantisation-aware forward and backward of a minibatch (MFMA), one gradient
 //                 partial per 64 samples (summed in fixed order: deterministic)
@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 
 #include <math.h>
+
+#include <algorithm>
 
 #include "arc_chem.h"
 #include "arc_mlp.h"
@@ -62,8 +64,9 @@ __device__ __forceinline__ void wave_sync()
 __device__ __forceinline__ int perm_k(int s, int q, int i) { return 32 * s + (i < 4 ? 4 * q + i : 12 + 4 * q + i); }
 
 // The weights as the operand fragments each lane supplies, in LDS (shared by the block):
-// frag[f][lane] for f = 0..3 layer 1 (M-tile t = f), 4..11 layer 2 (t = (f - 4) / 2,
-// k-step s = (f - 4) % 2), 12..13 layer 3 (k-step s = f - 12); biases as float4 per four rows.
+// frag[f][lane] for f = 0..3 layer 1 (M-tile t = f, the eight inputs repeated in the four depth
+// groups), 4..11 layer 2 (t = (f - 4) / 2, k-step s = (f - 4) % 2), 12..13 layer 3 (k-step
+// s = f - 12, the two outputs repeated in rows 4j and 4j + 1); biases as float4 per four rows.
 constexpr int kFrags = 14;
 struct LdsWeights {
     bf16x8 frag[kFrags][64];
@@ -79,14 +82,14 @@ __device__ __forceinline__ void load_lds_weights(const Model* M, LdsWeights& L)
         bf16x8 v;
         if (f < 4) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = M->w1t[16 * f + m][8 * q + i];
+            for (int i = 0; i < 8; ++i) v[i] = M->w1t[16 * f + m][i];
         } else if (f < 12) {
             const int t = (f - 4) >> 1, s2 = (f - 4) & 1;
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = M->w2t[16 * t + m][perm_k(s2, q, i)];
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = M->w3t[m][perm_k(f - 12, q, i)];
+            for (int i = 0; i < 8; ++i) v[i] = M->w3t[m & 3][perm_k(f - 12, q, i)];
         }
         L.frag[f][l] = v;
     }
@@ -112,81 +115,118 @@ __device__ __forceinline__ uint32_t relu_bf16x2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, v), z));
 }
 
-// Hidden layer: ReLU and BF16 rounding of four M-tiles (biases already in the
-// accumulators), packed as the two k-steps of the next layer's B operand (elements 2j and
-// 2j + 1 of an operand are the low and high halves of its word j).
-__device__ __forceinline__ void hidden_to_operand(const f32x4 d[4], bf16x8 h[2])
+// Half a hidden layer: ReLU and BF16 rounding of two M-tiles (biases already in the
+// accumulators), packed as one k-step of the next layer's B operand (elements 2j and 2j + 1 of
+// an operand are the low and high halves of its word j).
+__device__ __forceinline__ bf16x8 hidden_to_operand(const f32x4& a, const f32x4& b)
 {
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-        const f32x4 a = d[2 * s2], b = d[2 * s2 + 1];
-        const u32x4 w = {relu_bf16x2(a[0], a[1]), relu_bf16x2(a[2], a[3]), relu_bf16x2(b[0], b[1]),
-                         relu_bf16x2(b[2], b[3])};
-        h[s2] = __builtin_bit_cast(bf16x8, w);
-    }
+    const u32x4 w = {relu_bf16x2(a[0], a[1]), relu_bf16x2(a[2], a[3]), relu_bf16x2(b[0], b[1]),
+                     relu_bf16x2(b[2], b[3])};
+    return __builtin_bit_cast(bf16x8, w);
 }
 
 // Accumulator start of M-tile t: rows 4q..4q+3 of every column carry the biases of hidden
 // units 16t + 4q .. 16t + 4q + 3, so the MFMA adds them.
-__device__ __forceinline__ f32x4 bias_acc(const float4* bias, int t)
+__device__ __forceinline__ f32x4 bias_acc(const float4* bias, int t, int lane)
 {
-    const float4 b = bias[4 * t + ((threadIdx.x & 63) >> 4)];
+    const float4 b = bias[4 * t + (lane >> 4)];
     const f32x4 v = {b.x, b.y, b.z, b.w};
     return v;
 }
 
-// One tile of 16 cells: x = the layer-1 B operand (lanes with q = 0 hold the 8 standardised
-// features of cell n, other lanes zeros). Returns rows 4q..4q+3 of the output tile; lanes
-// with q = 0 hold the two outputs of cell n in elements 0 and 1 (biases included).
-__device__ __forceinline__ f32x4 forward_tile(const LdsWeights& w, bf16x8 x)
+// An LDS object's address that the compiler takes for a new one, so that reads of it inside a
+// loop stay there instead of being kept in registers over it.
+template <class T>
+__device__ __forceinline__ const T& read_here(const T& v)
 {
-    const int lane = threadIdx.x & 63;
-    f32x4 d[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) d[t] = mfma(w.frag[t][lane], x, bias_acc(w.b1, t));
-    bf16x8 h[2];
-    hidden_to_operand(d, h);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        d[t] = mfma(w.frag[5 + 2 * t][lane], h[1], mfma(w.frag[4 + 2 * t][lane], h[0], bias_acc(w.b2, t)));
-    hidden_to_operand(d, h);
-    const bool q0 = lane < 16;
-    const f32x4 b3 = {q0 ? w.b3[0] : 0.0f, q0 ? w.b3[1] : 0.0f, 0.0f, 0.0f};
-    return mfma(w.frag[13][lane], h[1], mfma(w.frag[12][lane], h[0], b3));
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(&v) + zero);
 }
 
-// Forward pass of the 64 cells of a wave, one per lane: f = the lane's standardised
-// features; returns the lane's two outputs. Tiles of 16 cells with no bit in `need`
-// (wave-uniform) are skipped and their outputs left at zero.
+// C tiles of 16 cells at once, so that a weight fragment read from LDS serves C MFMAs. x[c] = the
+// layer-1 B operand of tile c: the lanes of one depth group hold the 8 standardised features of
+// cell n, the others zeros. out[c]: elements 0 and 1 hold the two outputs of cell n (biases
+// included) in every lane of column n.
+template <int C>
+__device__ __forceinline__ void forward_tiles(const LdsWeights& w, int lane, const bf16x8 (&x)[C], f32x4 (&out)[C])
+{
+    bf16x8 h[C][2], g[C][2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+        f32x4 d[C][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bf16x8 a = w.frag[2 * s2 + j][lane];
+            const f32x4 b = bias_acc(w.b1, 2 * s2 + j, lane);
+#pragma unroll
+            for (int c = 0; c < C; ++c) d[c][j] = mfma(a, x[c], b);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) h[c][s2] = hidden_to_operand(d[c][0], d[c][1]);
+    }
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+        f32x4 d[C][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int t = 2 * s2 + j;
+            const bf16x8 a0 = w.frag[4 + 2 * t][lane], a1 = w.frag[5 + 2 * t][lane];
+            const f32x4 b = bias_acc(w.b2, t, lane);
+#pragma unroll
+            for (int c = 0; c < C; ++c) d[c][j] = mfma(a0, h[c][0], b);
+#pragma unroll
+            for (int c = 0; c < C; ++c) d[c][j] = mfma(a1, h[c][1], d[c][j]);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) g[c][s2] = hidden_to_operand(d[c][0], d[c][1]);
+    }
+    const bf16x8 a0 = w.frag[12][lane], a1 = w.frag[13][lane];
+    const f32x4 b3 = {w.b3[0], w.b3[1], 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = mfma(a0, g[c][0], b3);
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = mfma(a1, g[c][1], out[c]);
+}
+
+// Forward pass of the 64 cells of a wave, one per lane: f = the lane's standardised features;
+// returns the lane's two outputs. Lane 16q + n is both the supplier of cell 16q + n and of depth
+// group q, column n, so tile c is the same four words in every lane with all groups but c
+// cleared, and its outputs are picked by the lanes with q = c: nothing crosses lanes. Groups of
+// kTilesAtOnce tiles with no bit in `need` (wave-uniform) are skipped, their outputs zero.
+// Two at once: four need registers that cost a wave per SIMD, one reads LDS twice as often (both
+// 3% slower).
+constexpr int kTilesAtOnce = 2;
 __device__ __forceinline__ void forward_wave(const LdsWeights& w, const float f[kIn], float& o0, float& o1,
                                              uint64_t need = ~0ull)
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
-    // the eight features as four packed BF16 pairs
-    uint32_t pk[4];
+    const int lane = threadIdx.x & 63, q = lane >> 4;
+    u32x4 pk;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const __bf16 lo = (__bf16)f[2 * j];
-        const __bf16 hi = (__bf16)f[2 * j + 1];
-        pk[j] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+        const f32x2 p = {f[2 * j], f[2 * j + 1]};
+        pk[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2));
     }
     o0 = o1 = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        if (((need >> (16 * c)) & 0xFFFFull) == 0) continue;  // no lane of these 16 cells needs it
-        bf16x8 x;
+    for (int c0 = 0; c0 < 4; c0 += kTilesAtOnce) {
+        if (((need >> (16 * c0)) & (~0ull >> (64 - 16 * kTilesAtOnce))) == 0) continue;
+        bf16x8 x[kTilesAtOnce];
+        f32x4 o[kTilesAtOnce];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t v = (uint32_t)__shfl((int)pk[j], 16 * c + n, 64);
-            x[2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(q == 0 ? v & 0xFFFFu : 0u));
-            x[2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(q == 0 ? v >> 16 : 0u));
+        for (int c = 0; c < kTilesAtOnce; ++c) {
+            u32x4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = q == c0 + c ? pk[j] : 0u;
+            x[c] = __builtin_bit_cast(bf16x8, v);
         }
-        const f32x4 o = forward_tile(w, x);
-        const float v0 = __shfl(o[0], n, 64), v1 = __shfl(o[1], n, 64);
-        if (q == c) {
-            o0 = v0;
-            o1 = v1;
-        }
+        forward_tiles<kTilesAtOnce>(read_here(w), lane, x, o);
+#pragma unroll
+        for (int c = 0; c < kTilesAtOnce; ++c)
+            if (q == c0 + c) {
+                o0 = o[c][0];
+                o1 = o[c][1];
+            }
     }
 }
 
@@ -197,18 +237,27 @@ __device__ __forceinline__ float fexp10(float v) { return __builtin_amdgcn_exp2f
 __device__ __forceinline__ float safe_log10(float v, float floor_) { return flog10(fmaxf(v, floor_)); }
 
 // Features of a cell: n_H, x_HI, T, Gamma_HI, dt [s], h = photoheating per H atom, x_HeII, x_HeI.
-__device__ __forceinline__ void cell_features(float nh, float x, float T, float gam, float ldt, float h, float xheii,
-                                              float xhei, float f[kIn])
+// The first five are those of the gate.
+__device__ __forceinline__ void gate_features(float nh, float x, float T, float gam, float ldt, float f[kIn])
 {
-    static_assert(kIn == 8, "eight features fill the first MFMA depth group");
+    static_assert(kIn == 8 && kGateDims == 5, "eight features fill the first MFMA depth group");
     f[0] = flog10(nh);
     f[1] = x;
     f[2] = flog10(T);
     f[3] = safe_log10(gam, kGammaFloor);
     f[4] = ldt;
+}
+__device__ __forceinline__ void other_features(float h, float xheii, float xhei, float f[kIn])
+{
     f[5] = safe_log10(h, kHeatFloor);
     f[6] = xheii;
     f[7] = xhei;
+}
+__device__ __forceinline__ void cell_features(float nh, float x, float T, float gam, float ldt, float h, float xheii,
+                                              float xhei, float f[kIn])
+{
+    gate_features(nh, x, T, gam, ldt, f);
+    other_features(h, xheii, xhei, f);
 }
 
 // Baseline of x_HI': dx/dt = a (1 - x) - b x with a = alpha_HII(T) n_e and b = Gamma_HI +
@@ -227,33 +276,55 @@ __device__ __forceinline__ float x_baseline(const chem::Coef& k, float nh, float
     return xeq + (x - xeq) * expf(-lam * dt);
 }
 
-// Reciprocals of the standardisation scales and of the gate ranges, taken once per thread
-// (correctly rounded, as on the host, so that both sides bin and scale identically).
+// The standardisation's means and the reciprocals of its scales, and the same of the gate's
+// ranges, in LDS: in registers they would be spilled through the network (correctly rounded, as
+// on the host, so that both sides bin and scale identically).
 struct Scales {
-    float isd[kIn];
-    float igate[kGateDims];
+    float mu[kIn], isd[kIn];
+    float lo[kIn], igate[kIn];
 };
 
-__device__ __forceinline__ Scales scales_of(const Model* M)
+// Called by the whole block, followed by a barrier.
+__device__ __forceinline__ void load_scales(const Model* M, Scales& z)
 {
-    Scales z;
-#pragma unroll
-    for (int k = 0; k < kIn; ++k) z.isd[k] = 1.0f / M->in_sd[k];
-#pragma unroll
-    for (int k = 0; k < kGateDims; ++k) z.igate[k] = 1.0f / (M->hi[k] - M->lo[k]);
-    return z;
+    const int k = threadIdx.x;
+    if (k >= kIn) return;
+    z.mu[k] = M->in_mu[k];
+    z.isd[k] = 1.0f / M->in_sd[k];
+    z.lo[k] = M->lo[k];
+    z.igate[k] = k < kGateDims ? 1.0f / (M->hi[k] - M->lo[k]) : 0.0f;
 }
 
-__device__ __forceinline__ void standardise(const Model* M, const Scales& z, bool valid, float f[kIn])
+__device__ __forceinline__ void standardise(const Scales& scales, bool valid, float f[kIn])
 {
+    const Scales& z = read_here(scales);
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) f[k] = valid ? (f[k] - M->in_mu[k]) * z.isd[k] : 0.0f;
+    for (int k = 0; k < kIn; ++k) f[k] = valid ? (f[k] - z.mu[k]) * z.isd[k] : 0.0f;
 }
 
 // ---------------------------------------------------------------------------------
 // Inference with the gate.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_infer(InferArgs a)
+// Per wave: (1) tiles of 64 cells through the gate's bins, which need four of the fields and turn
+// most cells away; those that pass wait in LDS until 64 of them fill a wave, then (2) the network,
+// its baseline and the screens behind it run on full waves, reading the cells' fields by index (a
+// line read a few tiles ago). 256^3 cells of which 34% end accepted, spread over 79% of the tiles:
+// 314 us, against 440 with the network on every tile that has a cell past the gate, and 646 with,
+// besides, each fragment read from LDS once per 16 cells (704 LDS cycles per tile and compute
+// unit), features and results moved across lanes, and the gate's tables read by each of 4096
+// workgroups. What bounds it is the vector instructions of the three parts, one after the other in
+// a wave (reads alone 100 us). Five waves per SIMD: four 324 us, six (one tile at once) 324; the
+// loads of the next tile issued a tile ahead change nothing.
+// The cells of a wave that are past the gate's bins and wait for the network: fewer than 64, then
+// those of one more tile of 64 cells. They come from at most 64 tiles, whose words of rejected
+// cells wait with them.
+struct Waiting {
+    unsigned long long reject[64];
+    uint32_t tile[64];
+    uint16_t cell[128];  // tile's place << 6 | cell in the tile
+};
+
+__global__ __launch_bounds__(256, kInferWavesPerSimd) void k_infer(InferArgs a)
 {
     const Model* M = a.model;
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.stamp = wall_clock64();
@@ -261,74 +332,99 @@ __global__ __launch_bounds__(256) void k_infer(InferArgs a)
     // the gate's verdict per bin (enough samples, small held-out error) as one bit each, so that
     // a cell's gate test reads LDS instead of two scattered loads from the model's tables
     __shared__ uint32_t gate_ok[kGateBins / 32];
+    __shared__ Scales z;
     load_lds_weights(M, w);
+    load_scales(M, z);
     if (a.gated) {
-        static_assert(kGateBins % 256 == 0, "whole rounds of the workgroup over the bins");
-        for (uint32_t bin = threadIdx.x; bin < (uint32_t)kGateBins; bin += blockDim.x) {
-            const bool ok = M->gate_count[bin] >= a.gate_min_count && M->gate_err[bin] <= a.gate_tol;
-            const uint64_t bits = __ballot(ok);
-            // lane 0 of each wave holds the 64 bins (two words) starting at its own bin
-            if ((threadIdx.x & 63) == 0) {
-                gate_ok[bin >> 5] = (uint32_t)bits;
-                gate_ok[(bin >> 5) + 1] = (uint32_t)(bits >> 32);
+        for (uint32_t i = threadIdx.x; i < kGateBins / 32; i += blockDim.x) {
+            const uint4* count = reinterpret_cast<const uint4*>(M->gate_count + 32 * i);
+            const float4* err = reinterpret_cast<const float4*>(M->gate_err + 32 * i);
+            uint32_t bits = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint4 n = count[j];
+                const float4 e = err[j];
+                bits |= (uint32_t)(n.x >= a.gate_min_count && e.x <= a.gate_tol) << (4 * j);
+                bits |= (uint32_t)(n.y >= a.gate_min_count && e.y <= a.gate_tol) << (4 * j + 1);
+                bits |= (uint32_t)(n.z >= a.gate_min_count && e.z <= a.gate_tol) << (4 * j + 2);
+                bits |= (uint32_t)(n.w >= a.gate_min_count && e.w <= a.gate_tol) << (4 * j + 3);
             }
+            gate_ok[i] = bits;
         }
     }
+    __shared__ Waiting waiting[4];
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    const Scales z = scales_of(M);
+    Waiting& wt = waiting[threadIdx.x >> 6];
     const float dtf = (float)a.dt, ldt = flog10(dtf);
     const float yf = (float)a.y;
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t base = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); base < a.ncell; base += stride) {
-        const uint32_t c = base + lane;
-        const bool valid = c < a.ncell;
-        float nh = 1.0f, T = 1.0f, x0 = 0.0f, xhei = 0.0f, xheii = 0.0f, gam = 0.0f, h = 0.0f, xb = 0.0f;
-        if (valid) {
-            nh = a.n_h[c];
-            T = a.temp[c];
-            x0 = a.x_hi[c];
-            xhei = a.x_hei[c];
-            xheii = a.x_heii[c];
-            gam = a.gamma[c];
-            h = a.heat[c] * x0 + yf * (a.heat[(size_t)a.ncell + c] * xhei + a.heat[2 * (size_t)a.ncell + c] * xheii);
-        }
-        float f[kIn];
-        cell_features(nh, x0, T, gam, ldt, h, xheii, xhei, f);
-        // (1) gate bins: inside the training range, in a bin with enough samples and a small
-        //     held-out error
-        bool accept = valid;
-        if (valid && a.gated) {
-            uint32_t bin = 0;
+    uint32_t nwait = 0, ntile = 0;  // cells waiting, and their tiles (wave-uniform)
+    for (uint32_t base = blockIdx.x * blockDim.x + (threadIdx.x & ~63u);; base += stride) {
+        const bool more = base < a.ncell;
+        if (more) {
+            // (1) gate bins: inside the training range, in a bin with enough samples and a small
+            //     held-out error
+            const uint32_t c = base + lane;
+            const bool valid = c < a.ncell;
+            bool pass = valid;
+            if (valid && a.gated) {
+                float f[kIn];
+                gate_features(a.n_h[c], a.x_hi[c], a.temp[c], a.gamma[c], ldt, f);
+                const Scales& zg = read_here(z);
+                uint32_t bin = 0;
 #pragma unroll
-            for (int k = kGateDims - 1; k >= 0; --k) {
-                const float u = (f[k] - M->lo[k]) * z.igate[k];
-                accept = accept && u >= 0.0f && u <= 1.0f;
-                const int b = min(kGate - 1, max(0, (int)(u * kGate)));
-                bin = bin * kGate + (uint32_t)b;
+                for (int k = kGateDims - 1; k >= 0; --k) {
+                    const float u = (f[k] - zg.lo[k]) * zg.igate[k];
+                    pass = pass && u >= 0.0f && u <= 1.0f;
+                    const int b = min(kGate - 1, max(0, (int)(u * kGate)));
+                    bin = bin * kGate + (uint32_t)b;
+                }
+                pass = pass && ((gate_ok[bin >> 5] >> (bin & 31u)) & 1u) != 0u;
             }
-            accept = accept && ((gate_ok[bin >> 5] >> (bin & 31u)) & 1u) != 0u;
+            const uint64_t through = __ballot(pass), rej = __ballot(valid && !pass);
+            if (through) {
+                if (lane == 0) {
+                    wt.reject[ntile] = (unsigned long long)rej;
+                    wt.tile[ntile] = base >> 6;
+                }
+                if (pass) wt.cell[nwait + (uint32_t)__popcll(through & __lanemask_lt())] = (uint16_t)(ntile << 6 | lane);
+                nwait += (uint32_t)__popcll(through);
+                ++ntile;
+                wave_sync();
+            } else if (lane == 0) {
+                a.reject[base >> 6] = (unsigned long long)rej;
+            }
         }
-        float xn = 0.0f, Tn = 0.0f;
-        chem::Coef k{};
-        // the network runs only for waves with a cell past the gate bins (wave-uniform branch)
-        const uint64_t cand = __ballot(accept);
-        if (cand) {
-            standardise(M, z, valid, f);
+        if (nwait >= 64u || (!more && nwait > 0u)) {
+            const uint32_t n = min(nwait, 64u);
+            const bool valid = (uint32_t)lane < n;
+            uint32_t entry = 0, c = 0;
+            float nh = 1.0f, T = 1.0f, x0 = 0.0f, xhei = 0.0f, xheii = 0.0f, gam = 0.0f, h = 0.0f;
+            if (valid) {
+                entry = wt.cell[lane];
+                c = (wt.tile[entry >> 6] << 6) + (entry & 63u);
+                nh = a.n_h[c];
+                T = a.temp[c];
+                x0 = a.x_hi[c];
+                xhei = a.x_hei[c];
+                xheii = a.x_heii[c];
+                gam = a.gamma[c];
+                h = a.heat[c] * x0 + yf * (a.heat[(size_t)a.ncell + c] * xhei + a.heat[2 * (size_t)a.ncell + c] * xheii);
+            }
+            float f[kIn];
+            cell_features(nh, x0, T, gam, ldt, h, xheii, xhei, f);
+            standardise(z, valid, f);
             float o0, o1;
-            forward_wave(w, f, o0, o1, cand);
-            // the outputs (the baseline only where they can still be used)
-            if (accept) {
-                k = chem::coefficients(T);
-                xb = x_baseline(k, nh, x0, gam, xheii, xhei, dtf, M->base_y, M->base_collisional);
-                xn = fminf(fmaxf(xb + (o0 * M->out_sd[0] + M->out_mu[0]), 0.0f), 1.0f);
-                Tn = T * fexp10(o1 * M->out_sd[1] + M->out_mu[1]);
-            }
-        }
-        if (accept) {
-            if (a.gated) {
+            forward_wave(w, f, o0, o1, ~0ull >> (64u - n));
+            const chem::Coef k = chem::coefficients(T);
+            const float xb = x_baseline(k, nh, x0, gam, xheii, xhei, dtf, M->base_y, M->base_collisional);
+            const float xn = fminf(fmaxf(xb + (o0 * M->out_sd[0] + M->out_mu[0]), 0.0f), 1.0f);
+            const float Tn = T * fexp10(o1 * M->out_sd[1] + M->out_mu[1]);
+            bool accept = valid;
+            if (accept && a.gated) {
                 // (2) physical output temperature
-                accept = accept && Tn >= a.t_floor && Tn < 1e9f;
+                accept = Tn >= a.t_floor && Tn < 1e9f;
                 // (3) helium close to steady over dt (the network does not predict helium)
                 //     (a screening test: FP32 is ample for a 1e-3 threshold)
                 if (accept && a.y > 0.0) {
@@ -343,23 +439,40 @@ __global__ __launch_bounds__(256) void k_infer(InferArgs a)
                     accept = fabsf(dhei) * dtf <= 1e-3f * nhe && fabsf(dheiii) * dtf <= 1e-3f * nhe;
                 }
             }
+            if (accept) {
+                a.x_hi[c] = xn;
+                a.temp[c] = Tn;
+            }
+            // the cells for the plain solver: what is left waiting is of the last tile
+            if (valid && !accept) atomicOr(&wt.reject[entry >> 6], 1ull << (entry & 63u));
+            wave_sync();
+            const uint32_t left = nwait - n, done = left ? ntile - 1u : ntile;
+            if ((uint32_t)lane < done) a.reject[wt.tile[lane]] = wt.reject[lane];
+            if (left) {
+                const unsigned long long rej = wt.reject[done];
+                const uint32_t tile = wt.tile[done];
+                const uint16_t next = wt.cell[64 + lane] & 63u;
+                wave_sync();
+                if (lane == 0) {
+                    wt.reject[0] = rej;
+                    wt.tile[0] = tile;
+                }
+                if ((uint32_t)lane < left) wt.cell[lane] = next;
+                wave_sync();
+            }
+            nwait = left;
+            ntile = left ? 1u : 0u;
         }
-        if (accept) {
-            a.x_hi[c] = xn;
-            a.temp[c] = Tn;
-        }
-        // the cells for the plain solver, one bit per cell of the tile
-        const uint64_t rej = __ballot(valid && !accept);
-        if (lane == 0) a.reject[base >> 6] = (unsigned long long)rej;
+        if (!more) break;
     }
 }
 
-hipError_t launch_infer(const InferArgs& a, hipStream_t s)
+hipError_t launch_infer(const InferArgs& a, int cus, hipStream_t s)
 {
-    size_t blocks = (a.ncell + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    if (blocks < 1) blocks = 1;
-    k_infer<<<(unsigned)blocks, 256, 0, s>>>(a);
+    // the waves that are resident at once: each workgroup fills its tables from the model, and
+    // more tiles per wave leave fewer of its last batches unfilled (twice as many: 333 us)
+    const size_t blocks = std::min(((size_t)a.ncell + 255) / 256, (size_t)std::max(cus, 1) * kInferWavesPerSimd);
+    k_infer<<<(unsigned)std::max<size_t>(blocks, 1), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -380,10 +493,11 @@ __global__ __launch_bounds__(256) void k_predict(const Model* M, const float* X,
                                                  float* P)
 {
     __shared__ LdsWeights w;
+    __shared__ Scales z;
     load_lds_weights(M, w);
+    load_scales(M, z);
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    const Scales z = scales_of(M);
     for (uint32_t base = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); base < m; base += gridDim.x * blockDim.x) {
         const uint32_t i = base + lane;
         const bool valid = i < m;
@@ -394,7 +508,7 @@ __global__ __launch_bounds__(256) void k_predict(const Model* M, const float* X,
             raw_features(x, f);
             xb = raw_baseline(x, M->base_y, M->base_collisional);
         }
-        standardise(M, z, valid, f);
+        standardise(z, valid, f);
         float o0, o1;
         forward_wave(w, f, o0, o1);
         if (valid) {
