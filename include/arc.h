@@ -135,8 +135,8 @@ typedef struct {
                               (src << 32) | (level << 28) | pixel; NULL = off */
     int64_t tree_cap;      /* capacity of tree_out in entries */
     double u_j_override;   /* 0 = automatic fixed-point unit; > 0 forces this unit (tests) */
-    int32_t graph;         /* batched schedules: 1 = record the call's launches in HIP graphs
-                              once and replay them while every launch argument repeats
+    int32_t graph;         /* batched schedules: 1 = record the call's launches in a HIP graph
+                              once and replay it while every launch argument repeats
                               (same grid, buffers, sources' fixed-point scales, shape);
                               results are identical to 0 */
     int32_t correction;    /* geometric correction (section 2.5), ARC_CORR_*; needs
@@ -212,7 +212,8 @@ typedef struct {
     int32_t item_delta;    /* work-item level minus the first level (ARC_SCHED_BATCHED uses 5);
                               a trace lowers it under the memory bound of tune_item_level */
     double ms_best;        /* trace time of the chosen shape [ms] (tuning sources) */
-    double ms_default;     /* trace time of the default shape [ms] (tuning sources) */
+    double ms_default;     /* trace time of the first shape tried [ms]: the default but for
+                              refill 48 (tuning sources) */
     int32_t candidates;    /* shapes timed */
     int32_t stack;         /* split rays per wave's LDS stack (64, 128, 256) */
 } arc_tune_result;
@@ -322,7 +323,7 @@ typedef struct {
     const arc_mlp* mlp;    /* trained network for the MLP modes */
     double gate_tol;       /* MLP_GATED: largest accepted held-out bin error */
     int32_t gate_min_count; /* MLP_GATED: smallest accepted training count per bin */
-    int32_t graph;         /* 1 = record the step's launches in HIP graphs once and replay them
+    int32_t graph;         /* 1 = record the step's launches in a HIP graph once and replay it
                               while every launch argument repeats; results are identical to 0 */
 } arc_chem_params;
 

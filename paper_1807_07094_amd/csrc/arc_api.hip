@@ -1026,7 +1026,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
     arc_tune_result best{};
     best.waves = 4;
     best.waves_per_cu = default_waves_per_cu(P.nb);
-    best.refill = kDefaultRefill;
+    best.refill = 48;  // of the thresholds tried below (the default, 40, is between two of them)
     best.stack = kDefaultStack;
     best.item_delta = kDefaultItemDepth;
     double ms_best;
