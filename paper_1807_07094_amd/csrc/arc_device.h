@@ -63,8 +63,8 @@ enum Photons : int { kPhotonsEscaped = 0, kPhotonsAbsorbed = kMaxBins, kPhotonsT
 
 // Sums that every wave adds to at its end. Atomics on one line are carried out one after the
 // other, about 6 ns each, so a workgroup adds to one of kCounterSlots copies and the last kernel
-// sums them (256^3 x 1024 sources with one copy: the levels before the persistent launch took 10.3
-// ms, of which 8 were this, and the rates 0.43 ms instead of 0.22).
+// sums them (256^3 x 1024 sources with one copy: the levels before the persistent launch took 10.2
+// ms instead of 3.4, the rates 0.43 instead of 0.21).
 constexpr int kCounterSlots = 64;
 struct __align__(256) CounterSlot {
     unsigned long long n[16];  // [Counter]
@@ -416,6 +416,10 @@ constexpr double kSqrtPiOver3 = 1.0233267079464885;  // width of a level-0 pixel
 // and the last bits of a midpoint depend on how its path length was summed.
 constexpr double kFaceTie = 1e-9;
 
+// The correction a kernel is built for: none, the cell's share alone (modes 1 and 3), or with
+// the rest moved to a neighbour (mode 2).
+enum Corr : int { kCorrNone = 0, kCorrShare, kCorrMove };
+
 // Geometric correction of the segment [t, t_next) in the ray's current cell (section 2.5,
 // eq:correction): D_edge is the distance from the segment's midpoint to the nearest face of
 // the cell, L_Pix the width of the ray's pixel there (r sqrt(4 pi / N_pix)); the cell keeps
@@ -424,12 +428,11 @@ constexpr double kFaceTie = 1e-9;
 // (eq:correction2); without one inside the grid the cell keeps everything. Distances in
 // FP64 from the exact boundary numerators; faces within kFaceTie count as tied, and ties go
 // to the lower axis, then the lower face.
-template <int NB>
+template <int CORR, int NB>
 __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB>& ray, float nhi, float nlo, Seg& sg)
 {
     sg.nb = kNoCell;
     sg.fc = 1.0f;
-    if (A.corr == 0) return;
     const double tm = 0.5 * (((double)ray.thi + (double)ray.tlo) + ((double)nhi + (double)nlo));
     const int level = (int)(ray.lp >> kLevelShift);
     const double lpix = tm * __builtin_ldexp(kSqrtPiOver3, -level);
@@ -453,8 +456,8 @@ __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB
     if (!(dmin < 0.5 * lpix)) return;
     // the decisions above are FP64; the share itself needs FP32 only
     float fc = 0.5f + (float)dmin * __builtin_amdgcn_rcpf((float)lpix);
-    if (A.corr == 3) fc *= fc;
-    if (A.corr == 2) {
+    if (CORR == kCorrShare && A.corr == 3) fc *= fc;
+    if constexpr (CORR == kCorrMove) {
         // the neighbour's per-axis term replaces the cell's along `axis`
         const TermAddr o0 = ray.o[0], o1 = ray.o[1], o2 = ray.o[2];
         const TermAddr oc = axis == 0 ? o0 : (axis == 1 ? o1 : o2);
@@ -476,7 +479,7 @@ __device__ __forceinline__ void geom_correction(const TraceArgs& A, const Ray<NB
 // at only within 2e-6 of the nearer of them (tlim): a boundary met before that is neither, so
 // an ordinary step is about thirty instructions (a bundle's lanes reach their ends together).
 // `term` receives the cell's index terms, whose sum the caller forms later (they come from LDS).
-template <int NB, int PREC, bool CORR = false>
+template <int NB, int PREC, int CORR = kCorrNone>
 __device__ __forceinline__ int geom_next(const TraceArgs& A, Ray<NB>& ray, Seg& sg, uint32_t (&term)[3])
 {
     constexpr float kNear = 1.000001f;
@@ -535,7 +538,7 @@ __device__ __forceinline__ int geom_next(const TraceArgs& A, Ray<NB>& ray, Seg& 
         if (m2) nlo = low(2);
         if (m1) nlo = low(1);
         if (m0) nlo = low(0);
-        geom_correction(A, ray, at_end ? ray.tend : nhi, at_end ? 0.0f : nlo, sg);
+        geom_correction<CORR>(A, ray, at_end ? ray.tend : nhi, at_end ? 0.0f : nlo, sg);
     }
     // one axis after the other under its own lanes (branches, not selects: half the instructions)
     if (m2) {
@@ -616,8 +619,8 @@ __device__ __forceinline__ void thin_bounds(const TraceArgs& A, uint32_t src, fl
 // rounds to zero field units once S is below kLiveMin, and S only falls. With the geometric
 // correction the largest of a crossing's deposits is 2 S 2^12 (the moved photons' low limb) or
 // 16 (sqrt(3) + 173) S. Optical depths are kept for every bin (termination, escape and children
-// need them). The soft bins go first: at 256^3 x 1024 sources 1.4 of the three bins are live in
-// the mean, and the trace runs 1.3 times as fast as with all three.
+// need them). The soft bins go first: 256^3 x 1024 sources 50.3 ms with all three bins to the
+// end, 45.7 with the live ones (three waves per SIMD).
 constexpr float kLiveMin = 0.0009765625f;             // 2^-10
 constexpr float kLiveMinCorr = 0.000030517578125f;    // 2^-15
 template <int NB>
@@ -772,17 +775,17 @@ __device__ __forceinline__ long long to_fixed(float v)
 // field directly (beyond it, as photons in the two-limb field M).
 constexpr float kMovedRatioJ = 16.0f;
 
-// deposit_seg with the geometric correction (section 2.5): the cell keeps fc of the
-// crossing's photons (the termination remainder included). In mode 2 the rest goes to the
+// deposit_seg with the geometric correction (section 2.5), mode 2: the cell keeps fc of the
+// crossing's photons (the termination remainder included). The rest goes to the
 // neighbour sg.nb, absorbed there at the neighbour's opacity (eq:correction2, the absorber
 // ratio per bin as the opacity ratio kappa / kappa_nb), whatever that ratio. Up to a ratio of
 // kMovedRatioJ it enters the neighbour's field directly, (1 - fc) v kappa / kappa_nb (dj);
 // beyond it the moved photons, (1 - fc) v kappa (bounded by the ray's own), go to the
 // two-limb field M (dm) and are divided by kappa_nb when the rates are formed. A neighbour
-// with no absorber of the bin (kappa_nb = 0) leaves the share in the cell. Modes 1 and 3
-// drop the removed share. dj and dm name the neighbour only when some bin uses them.
+// with no absorber of the bin (kappa_nb = 0) leaves the share in the cell. dj and dm name the
+// neighbour only when some bin uses them.
 template <int NB, int PREC, bool THIN>
-__device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
+__device__ __forceinline__ bool deposit_seg_move(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
                                                  const float kapn[NB], uint32_t live, Dep<NB>& dep, Dep<NB>& dj,
                                                  Dep<NB>& dm, bool& use_j, bool& use_m, float (&T)[NB], float& reach)
 {
@@ -794,7 +797,7 @@ __device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ra
         float keep = v[b], mj = 0.0f, mm = 0.0f;
         if (sg.fc < 1.0f) {
             if (sg.nb == kNoCell) {
-                keep = sg.fc * v[b];
+                keep = sg.fc * v[b];  // (never; as a branch it halves the kernel's spills)
             } else if (kapn[b] > 0.0f) {
                 keep = sg.fc * v[b];
                 const float moved = (1.0f - sg.fc) * v[b];
@@ -814,6 +817,19 @@ __device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ra
     return term;
 }
 
+// Modes 1 and 3: the cell keeps fc of the crossing's photons, the removed share is dropped.
+template <int NB, int PREC, bool THIN>
+__device__ __forceinline__ bool deposit_seg_share(const TraceArgs& A, Ray<NB>& ray, const Seg& sg, const float kap[NB],
+                                                  uint32_t live, Dep<NB>& dep, float (&T)[NB], float& reach)
+{
+    float v[NB];
+    const bool term = attenuate_seg<NB, PREC, THIN>(A, ray, sg, kap, live, v, T, reach);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        if (live & (1u << b)) dep.v[b] = sg.fc < 1.0f ? sg.fc * v[b] : v[b];
+    return term;
+}
+
 // Segments whose geometry is computed ahead of their deposits (opacity loads in flight per
 // lane), all deposited in one merge window. The trace is a long mix of VALU, scalar, LDS and
 // branch instructions per wave, so what counts beside their number is how many waves a SIMD has
@@ -821,12 +837,15 @@ __device__ __forceinline__ bool deposit_seg_corr(const TraceArgs& A, Ray<NB>& ra
 // persistent launch: three waves and twelve ahead 28.9 ms; four waves and eight ahead with
 // windows of eight 24.3 (0.096 field lines per crossing), of four 24.9 (0.115); six ahead 25.0,
 // five 25.9; five waves and four ahead spill registers, 35. The extra state of thin spheres leaves
-// room for six, the two opacities per segment of the geometric correction for four.
+// room for six, the geometric correction for four, with the neighbours' opacities three.
 constexpr int kSegAhead = 8;
 constexpr int kSegAheadThin = 6;
-constexpr int kSegAheadCorr = 4;
-template <bool THIN>
-constexpr int seg_ahead() { return THIN ? kSegAheadThin : kSegAhead; }
+constexpr int kSegAheadMove = 3, kSegAheadShare = 6;
+template <int CORR, bool THIN>
+constexpr int seg_ahead()
+{
+    return CORR == kCorrMove ? kSegAheadMove : CORR == kCorrShare ? kSegAheadShare : THIN ? kSegAheadThin : kSegAhead;
+}
 
 // Up to K crossings of one lane per pass: the geometry of K segments is computed first
 // and their opacities are loaded together (K loads in flight per lane), then the
@@ -892,10 +911,14 @@ __device__ __forceinline__ int trace_pass(const TraceArgs& A, Ray<NB>& ray, bool
     return ev;
 }
 
-// trace_pass with the geometric correction: up to K crossings per lane, the neighbours'
-// opacities loaded with the cells'. The crossings' cells form windows, as without the
-// correction; in mode 2 their neighbours' high limbs, then their low limbs, form two more.
-template <int NB, int PREC, int K, bool THIN, class Depositor>
+// trace_pass with the geometric correction: up to K crossings per lane. Where the rest moves to
+// a neighbour, the neighbours' opacities are loaded with the cells', and cells and neighbours
+// form one window, since a neighbour mostly shares its tile with a cell of the pass (192^3 x 128
+// sources, three ahead: 8.1 ms, 0.19 lines per crossing, against 8.5 and 0.31 with a window for
+// each; four ahead spill registers, 9.2 and 8.8). Moved photons, where a lane has any, take two
+// more, for the high and the low limbs. Where the rest is dropped, six ahead and no neighbours
+// (128^3 x 16 sources: 0.88 ms, 1.04 through the neighbours' code with four ahead).
+template <int NB, int PREC, int K, bool THIN, int CORR, class Depositor>
 __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, Ray<NB>& ray, bool active, WaveStats& st,
                                                Depositor& deposit)
 {
@@ -915,46 +938,58 @@ __device__ __forceinline__ int trace_pass_corr(const TraceArgs& A, Ray<NB>& ray,
         sg[j].nb = kNoCell;
         if (go) {
             uint32_t term[3];
-            ev = geom_next<NB, PREC, true>(A, ray, sg[j], term);
+            ev = geom_next<NB, PREC, CORR>(A, ray, sg[j], term);
             nseg = j + 1;
             go = ev == kContinue;
         }
     }
+    constexpr int N = CORR == kCorrMove ? 2 : 1;
     float kap[K][NB], kapn[K][NB];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const bool hn = sg[j].nb != kNoCell;
         kappa_at<NB>(A, sg[j].cell, kap[j]);
-        kappa_at<NB>(A, hn ? sg[j].nb : 0u, kapn[j]);
+        if constexpr (CORR == kCorrMove) {
+            const bool hn = sg[j].nb != kNoCell;
+            kappa_at<NB>(A, hn ? sg[j].nb : 0u, kapn[j]);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) kapn[j][b] = hn ? kapn[j][b] : 0.0f;
+            for (int b = 0; b < NB; ++b) kapn[j][b] = hn ? kapn[j][b] : 0.0f;
+        }
     }
     float T[NB];
     ray_transmission<NB, PREC>(ray, T);
     const uint32_t live = live_bins<NB>(ray, active, T, kLiveMinCorr);
-    Dep<NB> dep[K], dj[K], dm[K];
-    bool use_j[K], use_m[K];
+    // the crossings' own deposits, then those of their neighbours
+    Dep<NB> dep[N * K], dm[K];
+    bool on[N * K], use_m[K], moved = false;
     float reach = INFINITY;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        use_j[j] = use_m[j] = false;
         dep[j].cell = sg[j].cell;
-        dj[j].cell = dm[j].cell = sg[j].nb != kNoCell ? sg[j].nb : 0u;
-        if (j < nseg && deposit_seg_corr<NB, PREC, THIN>(A, ray, sg[j], kap[j], kapn[j], live, dep[j], dj[j], dm[j],
-                                                         use_j[j], use_m[j], T, reach)) {
+        bool term = false;
+        if constexpr (CORR == kCorrMove) {
+            on[K + j] = use_m[j] = false;
+            dep[K + j].cell = dm[j].cell = sg[j].nb != kNoCell ? sg[j].nb : 0u;
+            if (j < nseg)
+                term = deposit_seg_move<NB, PREC, THIN>(A, ray, sg[j], kap[j], kapn[j], live, dep[j], dep[K + j], dm[j],
+                                                        on[K + j], use_m[j], T, reach);
+            moved = moved || use_m[j];
+        } else if (j < nseg) {
+            term = deposit_seg_share<NB, PREC, THIN>(A, ray, sg[j], kap[j], live, dep[j], T, reach);
+        }
+        if (term) {
             nseg = j + 1;
             ev = kTerminate;
         }
     }
     st.crossings += (uint32_t)nseg;
-    bool on[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) on[j] = j < nseg;
-    deposit.template add<kWhole, K>(dep, on, live, A.J, NB);
-    if (A.corr == 2) {
-        deposit.template add<kWhole, K>(dj, use_j, live, A.J, NB);
-        deposit.template add<kMovedHi, K>(dm, use_m, live, A.M, 2 * NB);
-        deposit.template add<kMovedLo, K>(dm, use_m, live, A.M + 8 * NB, 2 * NB);
+    deposit.template add<kWhole, N * K>(dep, on, live, A.J, NB);
+    if constexpr (CORR == kCorrMove) {
+        if (__builtin_amdgcn_ballot_w64(moved)) {
+            deposit.template add<kMovedHi, K>(dm, use_m, live, A.M, 2 * NB);
+            deposit.template add<kMovedLo, K>(dm, use_m, live, A.M + 8 * NB, 2 * NB);
+        }
     }
     book_events<NB, PREC, THIN>(A, ev, ray, reach, st);
     return ev;

@@ -475,8 +475,8 @@ __host__ __device__ __forceinline__ size_t terms_bytes(const TraceArgs& A)
 // levels 136 us with one per wave, 106 now; 256^3 x 1024: 3.3 ms, 1.84 now). The waves of a
 // workgroup end together for it; their rays are neighbours.
 // -------------------------------------------------------------------------------------
-template <int NB, int PREC, bool CORR, bool THIN>
-__global__ __launch_bounds__(256, level_waves_per_simd(NB, CORR)) void k_trace_rays(TraceArgs A, const RayRec* __restrict__ in,
+template <int NB, int PREC, int CORR, bool THIN>
+__global__ __launch_bounds__(256, level_waves_per_simd(NB, CORR != kCorrNone)) void k_trace_rays(TraceArgs A, const RayRec* __restrict__ in,
                                                     const uint32_t* n_in_dev, uint32_t n_in_host,
                                                     RayRec* __restrict__ out, uint32_t* n_out, uint32_t out_cap,
                                                     int fam_out)
@@ -514,9 +514,9 @@ __global__ __launch_bounds__(256, level_waves_per_simd(NB, CORR)) void k_trace_r
         while (__any(act)) {
             int e;
             if constexpr (CORR)
-                e = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, act, st, dep);
+                e = trace_pass_corr<NB, PREC, seg_ahead<CORR, THIN>(), THIN, CORR>(A, ray, act, st, dep);
             else
-                e = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, act, st, dep);
+                e = trace_pass<NB, PREC, seg_ahead<CORR, THIN>(), THIN>(A, ray, act, st, dep);
             if (act && e != kContinue) {
                 ev = e;
                 act = false;
@@ -564,16 +564,17 @@ static hipError_t trace_rays_nb(const TraceArgs& A, int prec, const RayRec* in, 
     // at most 4096 workgroups: each fills a table of index terms and ends with the waves' counts
     const unsigned g = grid_for(n_in, 256, 4096);
     const bool thin = A.r_out != nullptr;
-    if (prec == 0 && A.corr && thin)
-        k_trace_rays<NB, 0, true, true><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
-    else if (prec == 0 && A.corr)
-        k_trace_rays<NB, 0, true, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
-    else if (prec == 0 && thin)
-        k_trace_rays<NB, 0, false, true><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
-    else if (prec == 0)
-        k_trace_rays<NB, 0, false, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+    auto launch = [&](auto* kernel) {
+        kernel<<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+    };
+    if (prec != 0)
+        launch(k_trace_rays<NB, 1, kCorrNone, false>);
+    else if (A.corr == 2)
+        launch(thin ? k_trace_rays<NB, 0, kCorrMove, true> : k_trace_rays<NB, 0, kCorrMove, false>);
+    else if (A.corr)
+        launch(thin ? k_trace_rays<NB, 0, kCorrShare, true> : k_trace_rays<NB, 0, kCorrShare, false>);
     else
-        k_trace_rays<NB, 1, false, false><<<g, 256, terms_bytes(A), s>>>(A, in, n_in_dev, n_in, out, n_out, out_cap, fam_out);
+        launch(thin ? k_trace_rays<NB, 0, kCorrNone, true> : k_trace_rays<NB, 0, kCorrNone, false>);
     return hipGetLastError();
 }
 
@@ -604,7 +605,7 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 // deposit merge then sums their crossings of a 2x2x2 tile into one 64-byte line per bin. Issue
 // bounds the kernel: 3.7 VALU wave-instructions per crossing (42 lanes active in the mean), 1.4
 // scalar ones, 0.5 branches, four waves per SIMD filling each other's gaps (256^3 x 1024 sources:
-// 24.3 ms, 1.70e11 crossings/s; with a merge per cell, an index computed per step, every bin
+// 24.0 ms, 1.71e11 crossings/s; with a merge per cell, an index computed per step, every bin
 // attenuated to the end and three waves per SIMD 49.1 ms). The LDS stack is a ring: when it would overflow, its oldest
 // entries move to the top of the spill area, so the pair behaves as one LIFO stack and
 // the wave works depth first. Waves share nothing but the work-queue head, so each wave ends
@@ -614,7 +615,7 @@ hipError_t launch_trace_rays(const TraceArgs& A, int prec, const RayRec* in, con
 // wave, a power of two of at least 64 (a split round of all lanes must fit the ring), chosen at
 // launch (the autotuner's LDS stack depth).
 
-template <int NB, int PREC, int WPB, bool CORR, bool THIN>
+template <int NB, int PREC, int WPB, int CORR, bool THIN>
 __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_trace_persistent(TraceArgs A, const RayRec* __restrict__ items,
                                                                const uint32_t* n_items_dev, uint32_t* head,
                                                                RayRec* __restrict__ spill_all, uint32_t spill_cap,
@@ -659,9 +660,9 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
         int ev = kContinue;
         if (__any(has)) {
             if constexpr (CORR)
-                ev = trace_pass_corr<NB, PREC, kSegAheadCorr, THIN>(A, ray, has, st, dep);
+                ev = trace_pass_corr<NB, PREC, seg_ahead<CORR, THIN>(), THIN, CORR>(A, ray, has, st, dep);
             else
-                ev = trace_pass<NB, PREC, seg_ahead<THIN>(), THIN>(A, ray, has, st, dep);
+                ev = trace_pass<NB, PREC, seg_ahead<CORR, THIN>(), THIN>(A, ray, has, st, dep);
         }
         // splits: one family record each
         const uint64_t sp = __ballot(ev == kSplit);
@@ -761,7 +762,7 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
     if (lane == 0 && spilled) atomicAdd(&my_slot(A.slots).n[kSpills], (unsigned long long)spilled);
 }
 
-template <int NB, int PREC, bool CORR, bool THIN>
+template <int NB, int PREC, int CORR, bool THIN>
 static hipError_t persistent_nb(const TraceArgs& A, const RayRec* items, const uint32_t* n_items, uint32_t* head,
                                 RayRec* spill, uint32_t spill_cap, int blocks, int waves, int refill, int fam,
                                 int stack_cap, hipStream_t s)
@@ -784,11 +785,13 @@ static hipError_t persistent_variant(const TraceArgs& A, int prec, const RayRec*
                                      int refill, int fam, int stack_cap, hipStream_t s)
 {
     const bool thin = A.r_out != nullptr;
-    if (prec != 0) return persistent_nb<NB, 1, false, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
-    if (A.corr && thin) return persistent_nb<NB, 0, true, true>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
-    if (A.corr) return persistent_nb<NB, 0, true, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
-    if (thin) return persistent_nb<NB, 0, false, true>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
-    return persistent_nb<NB, 0, false, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (prec != 0) return persistent_nb<NB, 1, kCorrNone, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (A.corr == 2 && thin) return persistent_nb<NB, 0, kCorrMove, true>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (A.corr == 2) return persistent_nb<NB, 0, kCorrMove, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (A.corr && thin) return persistent_nb<NB, 0, kCorrShare, true>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (A.corr) return persistent_nb<NB, 0, kCorrShare, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    if (thin) return persistent_nb<NB, 0, kCorrNone, true>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
+    return persistent_nb<NB, 0, kCorrNone, false>(A, items, n_items, head, spill, spill_cap, blocks, waves, refill, fam, stack_cap, s);
 }
 
 hipError_t launch_trace_persistent(const TraceArgs& A, int prec, const RayRec* items, const uint32_t* n_items,
