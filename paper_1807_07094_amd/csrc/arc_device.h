@@ -587,10 +587,11 @@ __device__ __forceinline__ int geom_next(const TraceArgs& A, Ray<NB>& ray, Seg& 
 
 // Section 2.6: the least path length at which the ray's depth in the softest bin reaches
 // kTauThin, within this segment (ts: depth at its start, dts: its increment, ks: its
-// opacity), bounds the source's thin radius.
+// opacity), bounds the source's thin radius. FP32 start plus increment can round to kTauThin where
+// the compensated sum stays below it, so a ray may reach it twice: the lesser length counts.
 __device__ __forceinline__ void thin_reach(const Seg& sg, float ts, float dts, float ks, float& reach)
 {
-    if (ts < kTauThin && ts + dts >= kTauThin) reach = (sg.t1 - sg.ds) + (kTauThin - ts) / ks;
+    if (ts < kTauThin && ts + dts >= kTauThin) reach = fminf(reach, (sg.t1 - sg.ds) + (kTauThin - ts) / ks);
 }
 
 // Bounds of the wave's lanes (+inf: none) on their sources' thin radii. Called by all 64 lanes.
@@ -744,7 +745,7 @@ __device__ __forceinline__ void book_events(const TraceArgs& A, int ev, const Ra
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (b == A.ksoft) tsp = PREC == 0 ? ray.tau[b] + ray.taulo[b] : ray.tau[b];
-            if (tsp < kTauThin) reach = ray.thi;
+            if (tsp < kTauThin) reach = fminf(reach, ray.thi);
         }
     }
     if constexpr (THIN) thin_bounds(A, ray.src, reach);
