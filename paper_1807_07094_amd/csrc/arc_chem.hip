@@ -110,18 +110,18 @@ __device__ __forceinline__ bool chem_substep(const ChemArgs& a, ChemCell& s)
             }
         }
     }
-    // three quotients from one reciprocal
+    // a reciprocal each: one of the product would be NaN for all three species where one factor is
+    // not finite (and saves nothing: 256^3 cells, relaxed gas 243 us, with fronts 2.48 ms, either way)
     const double d1 = fma(loss_hi, h, 1.0), d2 = fma(fma((double)k.k_hei, s.ne, (double)s.ghei), h, 1.0),
                  d3 = fma((double)k.a_heiii * s.ne, h, 1.0);
-    const double p12 = d1 * d2, r = rcp64(p12 * d3), r12 = r * d3;
     // (the clamps are comparisons, which let a NaN through, not fmin and fmax)
-    s.nhi = fma(gain_hi * s.nhii, h, s.nhi) * (r12 * d2);
+    s.nhi = fma(gain_hi * s.nhii, h, s.nhi) * rcp64(d1);
     if (s.nhi > s.nh) s.nhi = s.nh;
     s.nhii = s.nh - s.nhi;
-    double nhei_new = fma((double)k.a_heii * s.ne * s.nheii, h, s.nhei) * (r12 * d1);
+    double nhei_new = fma((double)k.a_heii * s.ne * s.nheii, h, s.nhei) * rcp64(d2);
     if (nhei_new > s.nhe) nhei_new = s.nhe;
     const double up = fma((double)k.k_heii, s.ne, (double)s.gheii) * s.nheii;
-    s.nheiii = fma(up, h, s.nheiii) * (r * p12);
+    s.nheiii = fma(up, h, s.nheiii) * rcp64(d3);
     if (s.nheiii > s.nhe - nhei_new) s.nheiii = s.nhe - nhei_new;
     s.nhei = nhei_new;
     s.nheii = s.nhe - s.nhei - s.nheiii;
