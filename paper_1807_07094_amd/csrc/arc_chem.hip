@@ -147,7 +147,7 @@ __device__ __forceinline__ void chem_store(const ChemArgs& a, const ChemCell& s)
 {
     const double inh = rcp64(s.nh);
     a.x_hi[s.c] = (float)(s.nhi * inh);
-    if (a.y > 0.0) {
+    if (s.nhe > 0.0) {  // (an empty cell keeps its helium fractions)
         const double inhe = inh * a.inv_y;
         a.x_hei[s.c] = (float)(s.nhei * inhe);
         a.x_heii[s.c] = (float)(s.nheii * inhe);
