@@ -124,7 +124,7 @@ typedef struct {
     void* stream;          /* hipStream_t, NULL = default stream */
     int32_t tune_waves;    /* batched: waves per workgroup (0 = default) */
     int32_t tune_blocks;   /* batched: workgroups in the persistent grid (0 = default) */
-    int32_t tune_refill;   /* batched: refill a wave once this many lanes idle (0 = 40) */
+    int32_t tune_refill;   /* batched: refill a wave once this many lanes idle (0 = 48) */
     int32_t tune_item_level; /* batched: HEALPix level whose rays become the persistent
                                 launch's work items; earlier levels are traced level by
                                 level (0 = five levels below the first; level 6 from
@@ -209,11 +209,10 @@ typedef struct {
     int32_t waves;         /* waves per workgroup of the persistent launch (1, 2, 4, 8) */
     int32_t waves_per_cu;  /* resident waves per compute unit the grid is sized for */
     int32_t refill;        /* refill a wave once this many lanes idle */
-    int32_t item_delta;    /* work-item level minus the first level (ARC_SCHED_BATCHED uses 5);
-                              a trace lowers it under the memory bound of tune_item_level */
+    int32_t item_delta;    /* work-item level minus the first level (ARC_SCHED_BATCHED: see
+                              tune_item_level, whose memory bound lowers it in a trace) */
     double ms_best;        /* trace time of the chosen shape [ms] (tuning sources) */
-    double ms_default;     /* trace time of the first shape tried [ms]: the default but for
-                              refill 48 (tuning sources) */
+    double ms_default;     /* trace time of the default shape [ms] (tuning sources) */
     int32_t candidates;    /* shapes timed */
     int32_t stack;         /* split rays per wave's LDS stack (64, 128, 256) */
 } arc_tune_result;

@@ -598,11 +598,13 @@ constexpr int kDefaultItemDepth = 5;
 // 4 us more.
 constexpr double kDeeperItems = 4 * 12 * 1024;
 
-// Default refill threshold of the persistent launch: a wave refills once 40 of its lanes are
+// Default refill threshold of the persistent launch: a wave refills once 48 of its lanes are
 // idle, so that many rays, mostly children of the same splits, start together and share the
-// tiles of their deposits (256^3 x 1024 sources: refill at 32, 40, 48 and 64 idle lanes 24.9,
-// 24.3, 24.3 and 25.6 ms; 128^3 x 16 sources, where idle lanes cost more, 40 beats 48 by 2%).
-constexpr int kDefaultRefill = 40;
+// tiles of their deposits; one of the thresholds the autotuner tries. Refill at 32, 40, 48 and 56 idle
+// lanes: 256^3 x 1024 sources 27.1, 26.1, 26.0 and 26.3 ms, 128^3 x 64 1.58, 1.50, 1.47 and 1.49,
+// 203x100x37 x 200 3.44, 3.21, 3.10 and 3.09; where idle lanes cost more the lower ones are level or
+// ahead by 1%: 128^3 x 16 0.70, 0.70, 0.72 and 0.72, corrected 192^3 x 128 7.87, 7.95, 8.02 and 8.11.
+constexpr int kDefaultRefill = 48;
 
 // Default grid of the persistent launch: the waves that are resident at once. Their first work
 // items are theirs by their place in the grid, so a wave that has to wait for another's end would
@@ -623,6 +625,14 @@ hipError_t grow_rays(arc_ctx* c, int i, size_t n)
     return e;
 }
 
+// Work-item level of the default shape, before shape_batched's bounds.
+int default_item_level(const TracePlan& P)
+{
+    const int level0 = P.A.level0, litem = level0 + kDefaultItemDepth;
+    const double rays = (double)P.nsrc * 12.0 * std::ldexp(1.0, 2 * litem);  // of that level, at most
+    return litem < 6 && rays >= kDeeperItems ? 6 : litem;
+}
+
 // Launch shape of the batched schedule and the buffers it needs. item_level: the HEALPix
 // level whose rays are the persistent launch's work items (0: the default depth); it is
 // clamped to [level0, lmax] and to the memory bound.
@@ -636,8 +646,7 @@ arc_status shape_batched(arc_ctx* c, TracePlan& P, int waves, int blocks, int re
     const double n_roots = (double)P.nsrc * npix0;
     // rays of level l at most (every ray reaches it)
     auto rays_at = [&](int l) { return n_roots * std::ldexp(1.0, 2 * (l - level0)); };
-    int litem = item_level > 0 ? item_level : level0 + kDefaultItemDepth;
-    if (item_level <= 0 && litem < 6 && rays_at(litem) >= kDeeperItems) litem = 6;
+    int litem = item_level > 0 ? item_level : default_item_level(P);
     litem = std::max(level0, std::min(lmax, litem));
     while (litem > level0 &&
            (rays_at(litem) > (double)0xFFFFFFF0u || rays_at(litem) * sizeof(RayRec) > (double)c->item_bytes))
@@ -903,9 +912,9 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
     return ARC_OK;
 }
 
-const arc_tune_result* find_tuned(const arc_ctx* c, const arc_grid* g, const TracePlan& P)
+arc_tune_result* find_tuned(arc_ctx* c, const arc_grid* g, const TracePlan& P)
 {
-    for (const auto& t : c->tuned)
+    for (auto& t : c->tuned)
         if (t.nx == g->nx && t.ny == g->ny && t.nz == g->nz && t.nb == P.nb && t.level0 == P.A.level0 &&
             t.lmax == P.lmax && t.precision == P.precision)
             return &t.shape;
@@ -1023,12 +1032,13 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
         *ms_out = best;
         return ARC_OK;
     };
+    // the default shape comes first
     arc_tune_result best{};
     best.waves = 4;
     best.waves_per_cu = default_waves_per_cu(P.nb);
-    best.refill = 48;  // of the thresholds tried below (the default, 40, is between two of them)
+    best.refill = kDefaultRefill;
     best.stack = kDefaultStack;
-    best.item_delta = kDefaultItemDepth;
+    best.item_delta = default_item_level(P) - P.A.level0;
     double ms_best;
     if ((rc = time_shape(best, &ms_best)) != ARC_OK) return rc;
     const double ms_default = ms_best;
@@ -1042,12 +1052,13 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
         }
         return ARC_OK;
     };
-    // (1) work-item level (levels below the first; the run clamps it to the memory bound). Only
-    // levels at or below the default: higher ones win on a source sample, whose subtrees are few,
+    // (1) work-item level (levels below the first; the run clamps it to the memory bound). Five
+    // below the first and on: higher ones win on a source sample, whose subtrees are few,
     // but on the full run their subtrees outgrow the LDS stacks (1024^3 x 16384 sources, four
     // levels below the first: 3.8e8 rays spilled and 760 ms against 712 ms at five).
     const arc_tune_result base1 = best;
-    for (int d : {kDefaultItemDepth + 1, kDefaultItemDepth + 2}) {
+    for (int d : {kDefaultItemDepth, kDefaultItemDepth + 1, kDefaultItemDepth + 2}) {
+        if (d == base1.item_delta) continue;
         arc_tune_result t = base1;
         t.item_delta = d;
         if ((rc = consider(t)) != ARC_OK) return rc;
@@ -1080,14 +1091,10 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
     best.ms_best = ms_best;
     best.ms_default = ms_default;
     best.candidates = ncand;
-    bool stored = false;
-    for (auto& t : c->tuned)
-        if (t.nx == g->nx && t.ny == g->ny && t.nz == g->nz && t.nb == P.nb && t.level0 == P.A.level0 &&
-            t.lmax == P.lmax && t.precision == P.precision) {
-            t.shape = best;
-            stored = true;
-        }
-    if (!stored) c->tuned.push_back({g->nx, g->ny, g->nz, P.nb, P.A.level0, P.lmax, P.precision, best});
+    if (arc_tune_result* known = find_tuned(c, g, P))
+        *known = best;
+    else
+        c->tuned.push_back({g->nx, g->ny, g->nz, P.nb, P.A.level0, P.lmax, P.precision, best});
     *res = best;
     return ARC_OK;
 }
