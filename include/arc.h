@@ -224,9 +224,9 @@ typedef struct {
  * of the waves' LDS stacks. Every
  * shape's fixed-point field is checked against the first one's bit for bit (two 64-bit
  * checksums); a difference returns ARC_E_MISMATCH. The best shape is cached in the context
- * for this grid size, bin count, level range and precision, where ARC_SCHED_BATCHED_TUNED
- * finds it. params->schedule and tune_* are ignored. The field and rates afterwards are
- * those of the last shape timed. */
+ * for this grid size, bin count, level range, precision, correction and use of thin spheres,
+ * where ARC_SCHED_BATCHED_TUNED finds it. params->schedule and tune_* are ignored. The field
+ * and rates afterwards are those of the last shape timed. */
 arc_status arc_autotune(arc_ctx* ctx, const arc_grid* grid, const arc_sources* src, const arc_freq_bins* bins,
                         double dt, const arc_trace_params* params, arc_rates* out, arc_tune_result* result);
 

@@ -79,7 +79,7 @@ struct arc_ctx {
     unsigned long long* sums = nullptr;  // field checksums of the autotuner
     unsigned long long* static_scratch = nullptr;  // this device's copy of `scratch`
     struct Tuned {
-        int nx, ny, nz, nb, level0, lmax, precision;
+        int nx, ny, nz, nb, level0, lmax, precision, corr, thin;  // (kernels differ by the last three)
         arc_tune_result shape;
     };
     std::vector<Tuned> tuned;
@@ -916,7 +916,7 @@ arc_tune_result* find_tuned(arc_ctx* c, const arc_grid* g, const TracePlan& P)
 {
     for (auto& t : c->tuned)
         if (t.nx == g->nx && t.ny == g->ny && t.nz == g->nz && t.nb == P.nb && t.level0 == P.A.level0 &&
-            t.lmax == P.lmax && t.precision == P.precision)
+            t.lmax == P.lmax && t.precision == P.precision && t.corr == P.A.corr && t.thin == P.thin)
             return &t.shape;
     return nullptr;
 }
@@ -956,8 +956,10 @@ arc_status arc_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const 
                 nd.push_back(s->ndot[i]);
                 if (s->r_thin) rt.push_back(s->r_thin[i]);
             }
+            // (radii out make it a trace with thin spheres, also where the subset has none)
+            std::vector<double> rout(P.thin ? nd.size() : 0);
             const arc_sources sub{(int32_t)nd.size(), pos.data(), nd.data(), s->r_thin ? rt.data() : nullptr,
-                                  nullptr};
+                                  P.thin ? rout.data() : nullptr};
             if ((rc = autotune_impl(c, g, &sub, b, dt, p, out, &fresh)) != ARC_OK) return rc;
             t = &fresh;
             // the tuning runs changed the plan's buffers: plan again for all sources
@@ -1094,7 +1096,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
     if (arc_tune_result* known = find_tuned(c, g, P))
         *known = best;
     else
-        c->tuned.push_back({g->nx, g->ny, g->nz, P.nb, P.A.level0, P.lmax, P.precision, best});
+        c->tuned.push_back({g->nx, g->ny, g->nz, P.nb, P.A.level0, P.lmax, P.precision, P.A.corr, P.thin, best});
     *res = best;
     return ARC_OK;
 }
