@@ -652,10 +652,11 @@ arc_status shape_batched(arc_ctx* c, TracePlan& P, int waves, int blocks, int re
            (rays_at(litem) > (double)0xFFFFFFF0u || rays_at(litem) * sizeof(RayRec) > (double)c->item_bytes))
         --litem;
     if (rays_at(litem) > (double)0xFFFFFFF0u) return fail(c, ARC_E_UNSUPPORTED, "too many work items");
-    // buffer b holds the levels l with (l - level0) % 2 == b: the count of its deepest one
+    // buffer b holds the levels l with (l - level0) % 2 == b: the count of its deepest one. The
+    // items of litem are families, a record per ray of the level before (else the root rays)
     size_t need[2] = {1, 1};
     for (int l = level0; l <= litem; ++l)
-        need[(l - level0) & 1] = std::max(need[(l - level0) & 1], (size_t)rays_at(l));
+        need[(l - level0) & 1] = std::max(need[(l - level0) & 1], (size_t)rays_at(l < litem ? l : std::max(level0, l - 1)));
     for (int i = 0; i < 2; ++i)
         if (need[i] > c->rcap[i]) HIP_TRY(c, grow_rays(c, i, need[i]));
     const uint32_t spill_cap = P.spill_cap_req > 0 ? (uint32_t)P.spill_cap_req : 4096u;
