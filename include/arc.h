@@ -127,8 +127,9 @@ typedef struct {
     int32_t tune_refill;   /* batched: refill a wave once this many lanes idle (0 = 48) */
     int32_t tune_item_level; /* batched: HEALPix level whose rays become the persistent
                                 launch's work items; earlier levels are traced level by
-                                level (0 = five levels below the first; level 6 from
-                                level 0 with four sources or more). Lowered while the
+                                level (0 = five levels below the first; from level
+                                0 level 6 with 4 to 512 sources, or to 64 in
+                                boxes that do not reach level 8). Lowered while the
                                 rays of that level could exceed a sixth of the device
                                 memory (48-byte records). */
     uint64_t* tree_out;    /* optional device array: every ray traced is appended as

@@ -592,11 +592,16 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
 // from 1.4e8 to 4e5). Lowered while the larger ray buffer would exceed item_bytes.
 constexpr int kDefaultItemDepth = 5;
 
-// From level 0, level 6 instead of 5 where the rays of level 5 may number this many (four
-// sources): 32 sources in 64^3 0.70 ms instead of 1.13, in 192^3 1.42 instead of 1.89, 4 in 64^3
-// 0.28 instead of 0.32. With fewer the added launch costs what it saves: 1 source in thick gas
-// 4 us more.
-constexpr double kDeeperItems = 4 * 12 * 1024;
+// From level 0, level 6 instead of 5 for 4 to 512 sources, in boxes that do not reach level 8 (up
+// to 36^3 with four rays per cell) for 4 to 64: it gives more waves items, which few sources lack at
+// level 5; with more of them the rays traced level by level cost more than that gives. Level 5 and
+// 6 [ms], gas of the density-field test:
+//   32^3   1 source 0.153, 0.161; 4: 0.196, 0.194; 32: 0.598, 0.369; 128: 0.838, 0.974; 512: 2.15, 3.16
+//   64^3   1: 0.206, 0.211; 4: 0.341, 0.326; 32: 1.13, 0.70; 512: 7.29, 7.20; 2048: 26.2, 27.1
+//   192^3  1: 0.411, 0.426; 4: 0.559, 0.573; 32: 1.83, 1.38; 512: 14.7, 14.0
+// Thin gas gains more (64^3 x 32 4.22, 1.78; 256^3 x 4 50.8, 51.3, x 32 301, 104); in thick gas, where
+// hardly a ray gets that far, the launch costs 1 to 5 us of 90 to 560.
+constexpr int kDeeperSources = 4, kDeeperSourcesEnd = 512, kDeeperSourcesEndSmall = 64;
 
 // Default refill threshold of the persistent launch: a wave refills once 48 of its lanes are
 // idle, so that many rays, mostly children of the same splits, start together and share the
@@ -628,9 +633,9 @@ hipError_t grow_rays(arc_ctx* c, int i, size_t n)
 // Work-item level of the default shape, before shape_batched's bounds.
 int default_item_level(const TracePlan& P)
 {
-    const int level0 = P.A.level0, litem = level0 + kDefaultItemDepth;
-    const double rays = (double)P.nsrc * 12.0 * std::ldexp(1.0, 2 * litem);  // of that level, at most
-    return litem < 6 && rays >= kDeeperItems ? 6 : litem;
+    const int litem = P.A.level0 + kDefaultItemDepth;
+    const bool deeper = P.nsrc >= kDeeperSources && P.nsrc <= (P.lmax >= 8 ? kDeeperSourcesEnd : kDeeperSourcesEndSmall);
+    return litem < 6 && deeper ? 6 : litem;
 }
 
 // Launch shape of the batched schedule and the buffers it needs. item_level: the HEALPix
