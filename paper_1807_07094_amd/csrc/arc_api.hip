@@ -113,12 +113,15 @@ arc_status fail(arc_ctx* c, arc_status s, const char* fmt, ...)
     return s;
 }
 
+// (the runtime keeps a failed call's error until it is asked for: the next launch would report it)
 #define HIP_TRY(ctx, expr)                                                                        \
     do {                                                                                          \
         hipError_t e_ = (expr);                                                                   \
-        if (e_ != hipSuccess)                                                                     \
+        if (e_ != hipSuccess) {                                                                   \
+            (void)hipGetLastError();                                                              \
             return fail(ctx, e_ == hipErrorOutOfMemory ? ARC_E_NOMEM : ARC_E_DEVICE, "%s: %s (%s:%d)", \
                         #expr, hipGetErrorString(e_), __FILE__, __LINE__);                        \
+        }                                                                                         \
     } while (0)
 
 template <typename T>
@@ -668,8 +671,9 @@ arc_status shape_batched(arc_ctx* c, TracePlan& P, int waves, int blocks, int re
     const size_t spill_need = (size_t)blocks * waves * spill_cap;
     if (spill_need > c->spill_entries) {
         size_t cap_bytes = c->spill_entries * sizeof(RayRec);
-        HIP_TRY(c, grow(&c->spill, &cap_bytes, spill_need * sizeof(RayRec)));
-        c->spill_entries = spill_need;
+        const hipError_t e = grow(&c->spill, &cap_bytes, spill_need * sizeof(RayRec));
+        c->spill_entries = cap_bytes / sizeof(RayRec);  // none where the allocation failed
+        HIP_TRY(c, e);
     }
     P.waves = waves;
     P.blocks = blocks;
