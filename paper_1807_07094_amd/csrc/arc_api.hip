@@ -437,9 +437,11 @@ arc_status plan_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const
     {
         const size_t kb = nblocked * (nb == 1 ? sizeof(float) : sizeof(float4));
         HIP_TRY(c, grow(&c->kappa, &c->kappa_bytes, kb));
-        HIP_TRY(c, grow(&c->J, &c->J_bytes, nblocked * nb * sizeof(unsigned long long)));
-        if (p->correction == ARC_CORR_CONSERVING)
-            HIP_TRY(c, grow(&c->M, &c->M_bytes, nblocked * 2 * nb * sizeof(unsigned long long)));
+        const size_t jb = nblocked * nb * sizeof(unsigned long long);
+        const size_t mb = p->correction == ARC_CORR_CONSERVING ? 2 * jb : 0;
+        if (jb > c->J_bytes || mb > c->M_bytes) c->have_field = false;
+        HIP_TRY(c, grow(&c->J, &c->J_bytes, jb));
+        if (mb) HIP_TRY(c, grow(&c->M, &c->M_bytes, mb));
         if (s->n > c->src_cap) {
             void* old[] = {c->src, c->src_fill, c->r_out};
             void* old_pinned[] = {c->src_stage, c->r_stage};
@@ -841,6 +843,7 @@ arc_status run_trace(arc_ctx* c, const TracePlan& P, const arc_sources* s, doubl
                      hipStream_t st, arc_ledger* ledger)
 {
     const bool batched = schedule != ARC_SCHED_PLAIN;
+    c->have_field = false;  // until this one's is whole
     if (s->n > 0) {
         const size_t n = (size_t)s->n;
         const SourceUpload up(n);
