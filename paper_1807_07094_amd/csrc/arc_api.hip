@@ -616,15 +616,20 @@ constexpr int kDeeperSources = 4, kDeeperSourcesEnd = 512, kDeeperSourcesEndSmal
 // ahead by 1%: 128^3 x 16 0.70, 0.70, 0.72 and 0.72, corrected 192^3 x 128 7.87, 7.95, 8.02 and 8.11.
 constexpr int kDefaultRefill = 48;
 
-// Default grid of the persistent launch: the waves that are resident at once. Their first work
-// items are theirs by their place in the grid, so a wave that has to wait for another's end would
-// start its items late (128^3 x 16 sources, three waves per SIMD: 768 workgroups of four waves
-// 0.53 ms, 1024 0.63 ms).
-int default_waves_per_cu(int nb) { return 4 * persistent_waves_per_simd(nb); }
-
 // Default depth of each wave's LDS stack: 64 split rays (2 KB), a full split round of the
 // wave; deeper stacks spill less but hold fewer waves per compute unit.
 constexpr int kDefaultStack = 64;
+
+// Default grid of the persistent launch: the workgroups that are resident at once. Their first work
+// items are theirs by their place in the grid, so a wave that has to wait for another's end would
+// start its items late (128^3 x 16 sources, three waves per SIMD: 768 workgroups of four waves
+// 0.53 ms, 1024 0.63 ms; where the LDS holds three workgroups, three per compute unit and four:
+// 2048x2048x32 x 16 sources, long tables of index terms, 0.50 and 0.56, 128^3 x 16 with stacks of
+// 256 records 0.64 and 0.70).
+int default_workgroups_per_cu(const TracePlan& P, int waves, int stack)
+{
+    return persistent_workgroups_per_cu(P.nb, P.A.nx + P.A.ny + P.A.nz, waves, stack);
+}
 
 // Records of a ray buffer, without keeping its contents.
 hipError_t grow_rays(arc_ctx* c, int i, size_t n)
@@ -952,9 +957,9 @@ arc_status arc_trace(arc_ctx* c, const arc_grid* g, const arc_sources* s, const 
     hipStream_t st = (hipStream_t)p->stream;
     if (p->schedule == ARC_SCHED_BATCHED) {
         const int waves = p->tune_waves > 0 ? p->tune_waves : 4;
-        const int blocks = p->tune_blocks > 0 ? p->tune_blocks : std::max(1, c->cus * default_waves_per_cu(P.nb) / std::max(1, waves));
         const int refill = p->tune_refill > 0 ? p->tune_refill : kDefaultRefill;
         const int stack = p->tune_stack > 0 ? p->tune_stack : kDefaultStack;
+        const int blocks = p->tune_blocks > 0 ? p->tune_blocks : c->cus * default_workgroups_per_cu(P, waves, stack);
         if ((rc = shape_batched(c, P, waves, blocks, refill, p->tune_item_level, stack)) != ARC_OK)
             return rc;
     } else if (p->schedule == ARC_SCHED_BATCHED_TUNED) {
@@ -1050,7 +1055,7 @@ arc_status autotune_impl(arc_ctx* c, const arc_grid* g, const arc_sources* s, co
     // the default shape comes first
     arc_tune_result best{};
     best.waves = 4;
-    best.waves_per_cu = default_waves_per_cu(P.nb);
+    best.waves_per_cu = best.waves * default_workgroups_per_cu(P, best.waves, kDefaultStack);
     best.refill = kDefaultRefill;
     best.stack = kDefaultStack;
     best.item_delta = default_item_level(P) - P.A.level0;

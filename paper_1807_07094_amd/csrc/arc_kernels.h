@@ -122,7 +122,10 @@ hipError_t launch_trace_persistent(const TraceArgs& A, int prec, const RayRec* i
                                    int refill, int fam, int stack_cap, hipStream_t s);
 // Waves per SIMD that the persistent kernel's registers allow (a compute unit has four SIMDs).
 constexpr int persistent_waves_per_simd(int nb) { return nb <= 3 ? 4 : 3; }
-// The same for a level's kernel: the fourth wave is worth its spills but with the correction
+// Workgroups of the persistent kernel that a compute unit holds at once, by their registers and by
+// their LDS. sides: nx + ny + nz.
+int persistent_workgroups_per_cu(int nb, int sides, int waves, int stack_cap);
+// The waves per SIMD of a level's kernel: the fourth wave is worth its spills but with the correction
 // (256^3 x 1024 sources: levels 2.08 ms with three, 1.84 with four; corrected 192^3 x 128: 0.60
 // and 0.73).
 constexpr int level_waves_per_simd(int nb, bool corr) { return corr ? 3 : persistent_waves_per_simd(nb); }

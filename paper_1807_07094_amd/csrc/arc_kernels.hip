@@ -762,6 +762,18 @@ __global__ __launch_bounds__(WPB * 64, persistent_waves_per_simd(NB)) void k_tra
     if (lane == 0 && spilled) atomicAdd(&my_slot(A.slots).n[kSpills], (unsigned long long)spilled);
 }
 
+int persistent_workgroups_per_cu(int nb, int sides, int waves, int stack_cap)
+{
+    constexpr size_t kLdsPerCu = 160 * 1024, kLdsUnit = 1280;
+    TraceArgs A{};
+    A.nx = sides;
+    const size_t record = 2 * sizeof(uint32_t) + 2 * sizeof(float) * (size_t)nb;  // StackRec<nb>
+    const size_t lds = waves * (sizeof(DepScratch) + stack_cap * record) + terms_bytes(A);
+    const size_t fit = kLdsPerCu / ((lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit);
+    return std::max(1, std::min(4 * persistent_waves_per_simd(nb) / waves, (int)fit));
+}
+static_assert(sizeof(StackRec<1>) == 16 && sizeof(StackRec<4>) == 40, "records of the LDS stacks");
+
 template <int NB, int PREC, int CORR, bool THIN>
 static hipError_t persistent_nb(const TraceArgs& A, const RayRec* items, const uint32_t* n_items, uint32_t* head,
                                 RayRec* spill, uint32_t spill_cap, int blocks, int waves, int refill, int fam,
