@@ -278,7 +278,9 @@ hipError_t launch_chem_end(ChemBlock* run, ChemResult* out, hipStream_t s)
 template <bool RATES, bool THERMAL, bool COLL>
 static hipError_t chem_go(const ChemArgs& a, int cus, hipStream_t s)
 {
-    // resident waves only (six per SIMD): every wave loops until the chunks run out
+    // every wave loops until the chunks run out. Six waves per SIMD of the eight that the registers
+    // allow: 256^3 cells of relaxed gas 242 us, with eight 260; with fronts, 13 sub-steps in the mean,
+    // 2.48 ms and 2.42.
     const size_t want = ((size_t)a.ncell + 255) / 256;
     const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>(want, (size_t)std::max(1, cus) * 6));
     // Two chunks per wave and more on large grids (the second half goes to whoever is free), at

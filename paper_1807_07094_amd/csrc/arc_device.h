@@ -776,7 +776,7 @@ __device__ __forceinline__ long long to_fixed(float v)
 // field directly (beyond it, as photons in the two-limb field M).
 constexpr float kMovedRatioJ = 16.0f;
 
-// deposit_seg with the geometric correction (section 2.5), mode 2: the cell keeps fc of the
+// A segment's deposits with the geometric correction (section 2.5), mode 2: the cell keeps fc of the
 // crossing's photons (the termination remainder included). The rest goes to the
 // neighbour sg.nb, absorbed there at the neighbour's opacity (eq:correction2, the absorber
 // ratio per bin as the opacity ratio kappa / kappa_nb), whatever that ratio. Up to a ratio of
@@ -798,7 +798,9 @@ __device__ __forceinline__ bool deposit_seg_move(const TraceArgs& A, Ray<NB>& ra
         float keep = v[b], mj = 0.0f, mm = 0.0f;
         if (sg.fc < 1.0f) {
             if (sg.nb == kNoCell) {
-                keep = sg.fc * v[b];  // (never; as a branch it halves the kernel's spills)
+                // (never: a share is moved only where there is a neighbour. With the branch 192^3 x 128
+                // sources take 8.03 ms, without it 8.75, though two registers are spilled and not nine)
+                keep = sg.fc * v[b];
             } else if (kapn[b] > 0.0f) {
                 keep = sg.fc * v[b];
                 const float moved = (1.0f - sg.fc) * v[b];
@@ -837,8 +839,10 @@ __device__ __forceinline__ bool deposit_seg_share(const TraceArgs& A, Ray<NB>& r
 // to fill the gaps: eight ahead fit the 128 registers of four waves. 256^3 x 1024 sources,
 // persistent launch: three waves and twelve ahead 28.9 ms; four waves and eight ahead with
 // windows of eight 24.3 (0.096 field lines per crossing), of four 24.9 (0.115); six ahead 25.0,
-// five 25.9; five waves and four ahead spill registers, 35. The extra state of thin spheres leaves
-// room for six, the geometric correction for four, with the neighbours' opacities three.
+// five 25.9; five waves and four ahead spill registers, 35. With thin spheres and where the
+// correction drops the rest six ahead, with the neighbours' opacities three. With three bins those
+// kernels spill: 4 registers with thin spheres, 9 with neighbours (16 with both), 31 with thin
+// spheres in the modes that drop the rest; with one, two and four bins none.
 constexpr int kSegAhead = 8;
 constexpr int kSegAheadThin = 6;
 constexpr int kSegAheadMove = 3, kSegAheadShare = 6;

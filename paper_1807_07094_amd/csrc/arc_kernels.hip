@@ -779,7 +779,7 @@ static hipError_t persistent_nb(const TraceArgs& A, const RayRec* items, const u
                                 RayRec* spill, uint32_t spill_cap, int blocks, int waves, int refill, int fam,
                                 int stack_cap, hipStream_t s)
 {
-    // terms and stacks; with the deposit scratch at most 137 KB (eight waves of four bins, 256
+    // terms and stacks; with the deposit scratch at most 139 KB (eight waves of four bins, 256
     // records each, 2048 cells per axis) of a compute unit's 160 KB
     const size_t dyn = terms_bytes(A) + (size_t)waves * stack_cap * sizeof(StackRec<NB>);
     switch (waves) {
